@@ -485,13 +485,22 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
     });
 }
 
+// Threads per row (as a shift) of the passes over modes (for_modes): a quarter of the row's M
+// values, so that a thread has its four loads in flight, at most a workgroup's 256.
+static inline int row_threads_shift(int64_t M)
+{
+    int tps = 0;
+    while (tps < 8 && (int64_t(4) << tps) < M) ++tps;
+    return tps;
+}
+
 template <typename T>
 hipError_t launch_set_mass(const T *psi, int64_t n, double *partial, cx<T> *state, hipStream_t s)
 {
     hipLaunchKernelGGL((sum_kernel<T>), dim3(kReduceBlocks), dim3(256), 0, s, psi, n, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((set_mass_kernel<T>), dim3(1), dim3(64), 0, s, partial, kReduceBlocks, state);
+    hipLaunchKernelGGL((set_mass_kernel<T>), dim3(1), dim3(256), 0, s, partial, kReduceBlocks, state);
     return hipGetLastError();
 }
 
@@ -500,15 +509,12 @@ hipError_t launch_energy(const Geom &g, const T *psi, const cx<T> *state, const 
                          double R1, int model, double dV, double *partial, double *out, hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((energy_spec_kernel<T>), dim3(kReduceBlocks), dim3(256), 0, s, state, g.n0, g.nrows, g.M,
-                       fk[0], fk[1], fk[2], r, q1sq, R1, model, partial, pack_of(g));
+    const int64_t ntot = g.n0 * g.nrows * g.nx;
+    hipLaunchKernelGGL((energy_kernel<T>), dim3(2 * kReduceBlocks), dim3(256), 0, s, state, psi, g.n0, g.nrows, g.M,
+                       row_threads_shift(g.M), fk[0], fk[1], fk[2], r, q1sq, R1, model, kReduceBlocks, partial, pack_of(g));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t ntot = g.n0 * g.nrows * g.nx;
-    hipLaunchKernelGGL((quartic_kernel<T>), dim3(kReduceBlocks), dim3(256), 0, s, psi, ntot, partial + kReduceBlocks);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((energy_final_kernel<T>), dim3(1), dim3(64), 0, s, partial, partial + kReduceBlocks,
+    hipLaunchKernelGGL((energy_final_kernel<T>), dim3(1), dim3(256), 0, s, partial, partial + kReduceBlocks,
                        kReduceBlocks, dV, (double)ntot, state, out);
     return hipGetLastError();
 }
@@ -517,9 +523,9 @@ template <typename T>
 hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
-    const int64_t n = g.n0 * g.nrows * (g.M + 1);
-    const int64_t blocks = cdiv(n, 256) < 65536 ? cdiv(n, 256) : 65536;
-    hipLaunchKernelGGL((export_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, state, out, g.n0, g.nrows, g.M,
+    const int tps = row_threads_shift(g.M);
+    const int64_t blocks = cdiv((g.n0 * g.nrows) << tps, 256);
+    hipLaunchKernelGGL((export_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, state, out, g.n0, g.nrows, g.M, tps,
                        pack_of(g));
     return hipGetLastError();
 }

@@ -157,11 +157,11 @@ __host__ __device__ inline Pack row_pack(int64_t M) { return Pack{1, M, 0, 0}; }
 template <typename T, class PL, int ROWS, bool CUBE, bool PAD = false, bool NT = false, bool FROM_LDS = false>
 __device__ __forceinline__ void x_r2c_block(const T *__restrict__ in, cx<T> *__restrict__ out, int64_t nrows,
                                             const cx<T> *__restrict__ tw, int lt_shift, int64_t bid, cx<T> *sh,
-                                            const Pack &pk)
+                                            const Pack &pk, const int tid = (int)threadIdx.x)
 {
     constexpr int M = PL::L, Tp = PL::Tp, R0 = PL::first, Rl = PL::last, Rmax = PL::Rmax;
     constexpr int LD = XPitch<T, M, PAD>::value;  // row pitch in LDS
-    const int tid = threadIdx.x, p = tid / Tp, t = tid - p * Tp;
+    const int p = tid / Tp, t = tid - p * Tp;
     const int64_t rho = bid * ROWS + p;  // position in the pass's row order (Pack::x_row)
     const bool valid = rho < nrows;
     int64_t obase;
@@ -308,12 +308,12 @@ template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = f
           bool TO_LDS = false>
 __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nrows, const cx<T> *__restrict__ tw,
                                             int lt_shift, T sc, const AdjEpi<T> &ea, int64_t bid, cx<T> *sh,
-                                            const Pack &pk)
+                                            const Pack &pk, const int tid = (int)threadIdx.x)
 {
     static_assert(!TO_LDS || EPI == EPI_PLAIN, "staging only for the plain epilogue");
     constexpr int M = PL::L, Tp = PL::Tp, Rl = PL::last, Rmax = PL::Rmax;
     constexpr int LD = XPitch<T, M, PAD>::value;
-    const int tid = threadIdx.x, p = tid / Tp, t = tid - p * Tp;
+    const int p = tid / Tp, t = tid - p * Tp;
     const int64_t rho = bid * ROWS + p;  // position in the pass's row order (Pack::x_row)
     const bool valid = rho < nrows;
     int64_t ibase;
@@ -416,7 +416,7 @@ struct XFused {
 template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false>
 __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int64_t nrows,
                                                 const cx<T> *__restrict__ tw, int lt_shift, T sc, int64_t bid,
-                                                cx<T> *sh, const Pack &pk)
+                                                cx<T> *sh, const Pack &pk, const int tid = (int)threadIdx.x)
 {
     using F = XFused<PLI, PLF, NTH>;
     static_assert(F::ok && PLI::L == PLF::L, "schedules must share the workgroup");
@@ -426,12 +426,12 @@ __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int
     for (int s = 0; s < F::R / F::RI; ++s)
         x_c2r_block<T, PLI, F::RI, EPI_PLAIN, PAD, false, NT, true>(in, nullptr, nrows, tw, lt_shift, sc, ea,
                                                                     bid * (F::R / F::RI) + s, sh + s * F::RI * LD,
-                                                                    pk);
+                                                                    pk, tid);
     __syncthreads();  // all staged rows written
 #pragma unroll
     for (int s = 0; s < F::R / F::RF; ++s)
         x_r2c_block<T, PLF, F::RF, true, PAD, NT, true>(nullptr, out, nrows, tw, lt_shift, bid * (F::R / F::RF) + s,
-                                                        sh + s * F::RF * LD, pk);
+                                                        sh + s * F::RF * LD, pk, tid);
 }
 
 // The fused x pass of the single-plan step between two steps: one workgroup of NTH threads (one
@@ -539,10 +539,11 @@ struct DerivArgs {
 template <typename T, class PL, int WMAX, int DIR, bool NT = false, int G = 1, bool DERIV = false>
 __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int W, int64_t ncols, const AxisMap &am,
                                                int64_t tiles_per_batch, const cx<T> *__restrict__ tw, int lt_shift,
-                                               int64_t bid, cx<T> *sh, const DerivArgs &da = DerivArgs{})
+                                               int64_t bid, cx<T> *sh, const DerivArgs &da = DerivArgs{},
+                                               const int tid = (int)threadIdx.x)
 {
     constexpr int L = PL::L, Tp = PL::Tp, R0 = PL::first, Rl = PL::last, Rmax = PL::Rmax;
-    const int tid = threadIdx.x, p = tid % WMAX, t = tid / WMAX;
+    const int p = tid % WMAX, t = tid / WMAX;
     const int64_t batch = bid / tiles_per_batch, tile = bid - batch * tiles_per_batch;
     const int64_t col = tile * W + p;
     const bool valid = p < W && col < ncols;
@@ -1219,40 +1220,99 @@ __global__ __launch_bounds__(C *PL::Tp) void r2c_natural_chunk_kernel(const cx<T
 // ------------------------------------------------------------------------------------------------
 // Reductions (FP64 accumulation, fixed grid and order: deterministic).
 
+// The passes below read whole grids once and are bound by HBM bandwidth, so what matters is bytes in
+// flight: a thread issues its loads in groups (four 16-byte loads, or four modes of a row) before it
+// uses the first.  Measured with scalar loads and 64-bit divisions per mode, then in this form,
+// 256^3 FP32: sum 21 -> 12 us (5.5 TB/s), energy 52 + 22 -> 33 us (one launch, 4.1 TB/s), export 35 ->
+// 25 us (5.4 TB/s).  The final sums over the block partials are a chain of load latencies in one
+// thread, so a workgroup shares them: mass 58 -> 4 us, energy 112 -> 5 us.
+
+// Adds f(x[i]) over a grid-stride range of n values, block `blk` of `nblk`; x 16-byte aligned.
+template <typename T, class F>
+__device__ __forceinline__ double stream_sum(const T *__restrict__ x, int64_t n, int64_t blk, int64_t nblk, F &&f)
+{
+    constexpr int V = 16 / (int)sizeof(T), U = 4;
+    typedef T vec __attribute__((ext_vector_type(V)));
+    const vec *xv = reinterpret_cast<const vec *>(x);
+    const int64_t nv = n / V, step = nblk * blockDim.x;
+    double acc[U] = {};
+    for (int64_t i = blk * blockDim.x + threadIdx.x; i < nv; i += U * step) {
+        vec v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = i + u * step < nv ? xv[i + u * step] : vec(T(0));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < V; ++k) acc[u] += f(v[u][k]);
+    }
+    const int64_t tail = nv * V + blk * blockDim.x + threadIdx.x;
+    if (tail < n) acc[0] += f(x[tail]);
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// Calls f(e, row, kx, s) for every mode of a packed spectrum, s its value: groups of 2^tps threads
+// take whole rows (one 32-bit division per row), each thread four modes at a time.
+template <typename T, class F>
+__device__ __forceinline__ void for_modes(const cx<T> *__restrict__ state, int64_t L, int64_t nrows, int64_t M, int tps,
+                                          const Pack &pk, int64_t blk, int64_t nblk, F &&f)
+{
+    constexpr int U = 4;
+    const int tpr = 1 << tps, rows = (int)(L * nrows), stride = (int)(nblk * (blockDim.x >> tps));
+    for (int r = (int)(blk * (blockDim.x >> tps)) + (int)(threadIdx.x >> tps); r < rows; r += stride) {
+        const int e = (int)((unsigned)r / (unsigned)nrows), row = r - e * (int)nrows;
+        const cx<T> *src = state + pk.row_base(e, row);
+        for (int k = (int)(threadIdx.x & (unsigned)(tpr - 1)); k < M; k += U * tpr) {
+            cx<T> v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = k + u * tpr < M ? src[pk.col(k + u * tpr)] : cx<T>{T(0), T(0)};
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u * tpr < M) f(e, row, k + u * tpr, v[u]);
+        }
+    }
+}
+
 // partial[block] = sum of x over a grid-stride range.
 template <typename T>
 __global__ __launch_bounds__(256) void sum_kernel(const T *__restrict__ x, int64_t n, double *partial)
 {
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        acc += (double)x[i];
+    const double acc = stream_sum(x, n, blockIdx.x, gridDim.x, [](T v) { return (double)v; });
     __shared__ double red[4];
     const double s = block_sum(acc, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// Sum of partial[0..np) by one workgroup, valid in thread 0 (fixed order for a given np and
+// workgroup size).  red: >= blockDim.x / 64 doubles of LDS.
+__device__ __forceinline__ double partial_sum(const double *partial, int np, double *red)
+{
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < np; i += blockDim.x) acc += partial[i];
+    return block_sum(acc, red);
+}
+
 // state[0].x = (T) sum(partial[0..np)) -- the mass mode from an FP64 sum of the field.
 template <typename T>
-__global__ void set_mass_kernel(const double *partial, int np, cx<T> *state)
+__global__ __launch_bounds__(256) void set_mass_kernel(const double *partial, int np, cx<T> *state)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < np; ++i) s += partial[i];
-        state[0].x = (T)s;
-    }
+    __shared__ double red[4];
+    const double s = partial_sum(partial, np, red);
+    if (threadIdx.x == 0) state[0].x = (T)s;
 }
 
 // *acc += coef * sum(partial[0..np))
 __global__ void accumulate_kernel(const double *partial, int np, double coef, double *acc);
 
-// Spectral quadratic part of the energy: sum over the full spectrum of (r + L(q)) |psi_hat|^2,
-// from the native state (FP64 throughout).  Geometry as in the last-axis pass.
+// Partial sums of the energy (FP64 throughout): the first np workgroups the spectral quadratic part,
+// sum over the full spectrum of (r + L(q)) |psi_hat|^2 from the native state (geometry as in the
+// last-axis pass), into partial[0..np); the next np the quartic part, sum of psi^4 / 4, into
+// partial[np..2np).
 template <typename T>
-__global__ __launch_bounds__(256) void energy_spec_kernel(const cx<T> *__restrict__ state, int64_t L, int64_t nrows,
-                                                          int64_t M, double fk0, double fk1, double fk2, double r,
-                                                          double q1sq, double R1, int model, double *partial, Pack pk)
+__global__ __launch_bounds__(256) void energy_kernel(const cx<T> *__restrict__ state, const T *__restrict__ psi,
+                                                     int64_t L, int64_t nrows, int64_t M, int tps, double fk0, double fk1,
+                                                     double fk2, double r, double q1sq, double R1, int model, int np,
+                                                     double *partial, Pack pk)
 {
-    const int64_t n = L * nrows * M;
     auto corr = [&](double q) {
         double a = (1.0 - q) * (1.0 - q);
         if (model == 0) return a;
@@ -1260,34 +1320,26 @@ __global__ __launch_bounds__(256) void energy_spec_kernel(const cx<T> *__restric
         return a * (b * b + R1);
     };
     double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t kx = i % M, rest = i / M, row = rest % nrows, e = rest / nrows;
-        const double kz = fk0 * signed_index(e, L), ky = fk1 * signed_index(row, nrows);
-        const cx<T> s = state[pk.at(e, row, kx)];
-        if (kx != 0) {
-            const double k = fk2 * (double)kx, q = kz * kz + ky * ky + k * k;
-            acc += 2.0 * (r + corr(q)) * ((double)s.x * s.x + (double)s.y * s.y);
-        } else {
-            const int64_t ep = (L - e) % L, rp = (nrows - row) % nrows;
-            const cx<T> sp = state[pk.at(ep, rp, 0)];
-            const double ax = 0.5 * ((double)s.x + sp.x), ay = 0.5 * ((double)s.y - sp.y);
-            const double bx = 0.5 * ((double)s.y + sp.y), by = 0.5 * ((double)sp.x - s.x);
-            const double q0 = kz * kz + ky * ky, kn = fk2 * (double)M, qn = q0 + kn * kn;
-            acc += (r + corr(q0)) * (ax * ax + ay * ay) + (r + corr(qn)) * (bx * bx + by * by);
-        }
-    }
-    __shared__ double red[4];
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void quartic_kernel(const T *__restrict__ psi, int64_t n, double *partial)
-{
-    double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double v = (double)psi[i] * (double)psi[i];
-        acc += 0.25 * v * v;
+    if ((int)blockIdx.x < np) {
+        for_modes(state, L, nrows, M, tps, pk, blockIdx.x, np, [&](int e, int row, int kx, cx<T> s) {
+            const double kz = fk0 * signed_index(e, L), ky = fk1 * signed_index(row, nrows);
+            if (kx != 0) {
+                const double k = fk2 * (double)kx, q = kz * kz + ky * ky + k * k;
+                acc += 2.0 * (r + corr(q)) * ((double)s.x * s.x + (double)s.y * s.y);
+            } else {
+                const int64_t ep = e == 0 ? 0 : L - e, rp = row == 0 ? 0 : nrows - row;
+                const cx<T> sp = state[pk.at(ep, rp, 0)];
+                const double ax = 0.5 * ((double)s.x + sp.x), ay = 0.5 * ((double)s.y - sp.y);
+                const double bx = 0.5 * ((double)s.y + sp.y), by = 0.5 * ((double)sp.x - s.x);
+                const double q0 = kz * kz + ky * ky, kn = fk2 * (double)M, qn = q0 + kn * kn;
+                acc += (r + corr(q0)) * (ax * ax + ay * ay) + (r + corr(qn)) * (bx * bx + by * by);
+            }
+        });
+    } else {
+        acc = stream_sum(psi, 2 * M * L * nrows, blockIdx.x - np, np, [](T p) {
+            const double v = (double)p * (double)p;
+            return 0.25 * v * v;
+        });
     }
     __shared__ double red[4];
     const double s = block_sum(acc, red);
@@ -1296,35 +1348,35 @@ __global__ __launch_bounds__(256) void quartic_kernel(const T *__restrict__ psi,
 
 // out[0] = dV (sum(ps)/(2N) + sum(pq)), out[1] = state[0].x / N.
 template <typename T>
-__global__ void energy_final_kernel(const double *ps, const double *pq, int np, double dV, double ntot,
-                                    const cx<T> *state, double *out)
+__global__ __launch_bounds__(256) void energy_final_kernel(const double *ps, const double *pq, int np, double dV,
+                                                           double ntot, const cx<T> *state, double *out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double a = 0.0, b = 0.0;
-        for (int i = 0; i < np; ++i) a += ps[i];
-        for (int i = 0; i < np; ++i) b += pq[i];
+    __shared__ double red[4];
+    const double a = partial_sum(ps, np, red);
+    const double b = partial_sum(pq, np, red);
+    if (threadIdx.x == 0) {
         out[0] = dV * (a / (2.0 * ntot) + b);
         out[1] = (double)state[0].x / ntot;
     }
 }
 
-// Native state -> natural half spectrum [L][nrows][M+1].
+// Native state -> natural half spectrum [L][nrows][M+1].  The thread of a row's folded column writes
+// both of its planes, kx = 0 and kx = M.
 template <typename T>
 __global__ __launch_bounds__(256) void export_kernel(const cx<T> *__restrict__ state, cx<T> *__restrict__ out,
-                                                     int64_t L, int64_t nrows, int64_t M, Pack pk)
+                                                     int64_t L, int64_t nrows, int64_t M, int tps, Pack pk)
 {
-    const int64_t n = L * nrows * (M + 1);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t kx = i % (M + 1), rest = i / (M + 1), row = rest % nrows, e = rest / nrows;
-        if (kx > 0 && kx < M) {
-            out[i] = state[pk.at(e, row, kx)];
+    for_modes(state, L, nrows, M, tps, pk, blockIdx.x, gridDim.x, [&](int e, int row, int kx, cx<T> s) {
+        cx<T> *dst = out + ((int64_t)e * nrows + row) * (M + 1);
+        if (kx != 0) {
+            dst[kx] = s;
         } else {
-            const int64_t ep = (L - e) % L, rp = (nrows - row) % nrows;
-            const cx<T> s = state[pk.at(e, row, 0)], sp = state[pk.at(ep, rp, 0)];
+            const cx<T> sp = state[pk.at(e == 0 ? 0 : L - e, row == 0 ? 0 : nrows - row, 0)];
             const T h = T(0.5);
-            out[i] = (kx == 0) ? cx<T>{(s.x + sp.x) * h, (s.y - sp.y) * h} : cx<T>{(s.y + sp.y) * h, (sp.x - s.x) * h};
+            dst[0] = {(s.x + sp.x) * h, (s.y - sp.y) * h};
+            dst[M] = {(s.y + sp.y) * h, (sp.x - s.x) * h};
         }
-    }
+    });
 }
 
 }  // namespace pfc

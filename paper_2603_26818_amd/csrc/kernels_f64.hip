@@ -4,13 +4,11 @@
 namespace pfc {
 PFC_INSTANTIATE(double)
 
-__global__ void accumulate_kernel(const double *partial, int np, double coef, double *acc)
+__global__ __launch_bounds__(256) void accumulate_kernel(const double *partial, int np, double coef, double *acc)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < np; ++i) s += partial[i];
-        acc[0] += coef * s;
-    }
+    __shared__ double red[4];
+    const double s = partial_sum(partial, np, red);
+    if (threadIdx.x == 0) acc[0] += coef * s;
 }
 
 int step_candidates(const Geom &g, int pass)
@@ -40,7 +38,7 @@ int step_candidates(const Geom &g, int pass)
 
 hipError_t launch_accumulate(const double *partial, int np, double coef, double *acc, hipStream_t s)
 {
-    hipLaunchKernelGGL(accumulate_kernel, dim3(1), dim3(64), 0, s, partial, np, coef, acc);
+    hipLaunchKernelGGL(accumulate_kernel, dim3(1), dim3(256), 0, s, partial, np, coef, acc);
     return hipGetLastError();
 }
 }  // namespace pfc
