@@ -155,32 +155,32 @@ __device__ __forceinline__ void batch_pass(int pass, const BatchInst<T> *in, int
 {
     if (pass == 0) {
         switch (in->M) {
-            PFC_BCASE(16, XFwdCands, batch_x_fwd, in->vx)
-            PFC_BCASE(32, XFwdCands, batch_x_fwd, in->vx)
-            PFC_BCASE(64, XFwdCands, batch_x_fwd, in->vx)
-            PFC_BCASE(128, XFwdCands, batch_x_fwd, in->vx)
-            PFC_BCASE(256, XFwdCands, batch_x_fwd, in->vx)
-            PFC_BCASE(512, XFwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(16, X2FwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(32, X2FwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(64, X2FwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(128, X2FwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(256, X2FwdCands, batch_x_fwd, in->vx)
+            PFC_BCASE(512, X2FwdCands, batch_x_fwd, in->vx)
         default: break;
         }
     } else if (pass == 1) {
         switch (in->n0) {
-            PFC_BCASE(32, LastCands, batch_y_step, in->vy)
-            PFC_BCASE(64, LastCands, batch_y_step, in->vy)
-            PFC_BCASE(128, LastCands, batch_y_step, in->vy)
-            PFC_BCASE(256, LastCands, batch_y_step, in->vy)
-            PFC_BCASE(512, LastCands, batch_y_step, in->vy)
-            PFC_BCASE(1024, LastCands, batch_y_step, in->vy)
+            PFC_BCASE(32, Last2Cands, batch_y_step, in->vy)
+            PFC_BCASE(64, Last2Cands, batch_y_step, in->vy)
+            PFC_BCASE(128, Last2Cands, batch_y_step, in->vy)
+            PFC_BCASE(256, Last2Cands, batch_y_step, in->vy)
+            PFC_BCASE(512, Last2Cands, batch_y_step, in->vy)
+            PFC_BCASE(1024, Last2Cands, batch_y_step, in->vy)
         default: break;
         }
     } else {
         switch (in->M) {
-            PFC_BCASE(16, XInvCands, batch_x_inv, in->vc)
-            PFC_BCASE(32, XInvCands, batch_x_inv, in->vc)
-            PFC_BCASE(64, XInvCands, batch_x_inv, in->vc)
-            PFC_BCASE(128, XInvCands, batch_x_inv, in->vc)
-            PFC_BCASE(256, XInvCands, batch_x_inv, in->vc)
-            PFC_BCASE(512, XInvCands, batch_x_inv, in->vc)
+            PFC_BCASE(16, X2InvCands, batch_x_inv, in->vc)
+            PFC_BCASE(32, X2InvCands, batch_x_inv, in->vc)
+            PFC_BCASE(64, X2InvCands, batch_x_inv, in->vc)
+            PFC_BCASE(128, X2InvCands, batch_x_inv, in->vc)
+            PFC_BCASE(256, X2InvCands, batch_x_inv, in->vc)
+            PFC_BCASE(512, X2InvCands, batch_x_inv, in->vc)
         default: break;
         }
     }
@@ -194,8 +194,8 @@ constexpr int kBatchLdsElems = kBatchThreads * 16;
 // LDS, cube and x r2c of the same rows (f_rows is XFused<..>::R of the two schedules).
 #define PFC_FCASE(LEN)                                                                                     \
     case LEN:                                                                                              \
-        with_plan<typename XInvCands<LEN>::type>(in->vc, [&](auto pi) {                                    \
-            return with_plan<typename XFwdCands<LEN>::type>(in->vx, [&](auto pf) {                         \
+        with_plan<typename X2InvCands<LEN>::type>(in->vc, [&](auto pi) {                                    \
+            return with_plan<typename X2FwdCands<LEN>::type>(in->vx, [&](auto pf) {                         \
                 batch_x_fused<T, decltype(pi), decltype(pf)>(in, item, tw, lt);                            \
                 return 0;                                                                                  \
             });                                                                                            \

@@ -38,8 +38,8 @@ bool batch_tiles(int n0, int M, int vx, int vy, int vc, bool f64, int *x_rows, i
         switch (m) {
 #define PFC_XCASE(MM)                                                                                   \
     case MM:                                                                                            \
-        with_plan<typename XFwdCands<MM>::type>(vx, [&](auto p) { *x_rows = BRows<decltype(p)>::value; return 0; }); \
-        with_plan<typename XInvCands<MM>::type>(vc, [&](auto p) { *c_rows = BRows<decltype(p)>::value; return 0; }); \
+        with_plan<typename X2FwdCands<MM>::type>(vx, [&](auto p) { *x_rows = BRows<decltype(p)>::value; return 0; }); \
+        with_plan<typename X2InvCands<MM>::type>(vc, [&](auto p) { *c_rows = BRows<decltype(p)>::value; return 0; }); \
         break;
             PFC_XCASE(16) PFC_XCASE(32) PFC_XCASE(64) PFC_XCASE(128) PFC_XCASE(256) PFC_XCASE(512)
 #undef PFC_XCASE
@@ -50,7 +50,7 @@ bool batch_tiles(int n0, int M, int vx, int vy, int vc, bool f64, int *x_rows, i
         switch (l) {
 #define PFC_YCASE(LL)                                                                                   \
     case LL:                                                                                            \
-        with_plan<typename LastCands<LL>::type>(vy, [&](auto p) {                                         \
+        with_plan<typename Last2Cands<LL>::type>(vy, [&](auto p) {                                         \
             using P0 = decltype(p);                                                                     \
             *y_pencils = f64 ? kBatchThreads / SpreadIf<P0, PencilTile<double, LL>::E>::Tp               \
                              : kBatchThreads / SpreadIf<P0, PencilTile<float, LL>::E>::Tp;               \
@@ -73,7 +73,7 @@ int batch_candidates(int n0, int M, int pass)
     switch (len) {
 #define PFC_CCASE(LL)                                                                                   \
     case LL:                                                                                            \
-        return pass == 0 ? XFwdCands<LL>::type::size : pass == 1 ? LastCands<LL>::type::size : XInvCands<LL>::type::size;
+        return pass == 0 ? X2FwdCands<LL>::type::size : pass == 1 ? Last2Cands<LL>::type::size : X2InvCands<LL>::type::size;
         PFC_CCASE(16) PFC_CCASE(32) PFC_CCASE(64) PFC_CCASE(128) PFC_CCASE(256) PFC_CCASE(512) PFC_CCASE(1024)
 #undef PFC_CCASE
     default: return 0;

@@ -87,6 +87,21 @@ static inline AxisMap last_map(const Geom &g)
     return AxisMap{0, pk.e_stride(), pk.Mp << pk.zs, g.M, 0, pk.zs, pk.zs, pk.cs};
 }
 
+// Column tiles below which a strided pass takes narrow tiles (NarrowTile in kernels.hpp): one per CU for
+// the two transforms of the step and of the adjoint, half of that for a single transform.  Measured per
+// step, full tiles then narrow ones: 512^2 FP32 (16 tiles) 17.5 -> 6.5 us for the last-axis pass, 1024 x 32
+// x 64 (64 tiles) 82 -> 48 us, 1024 x 64 x 64 (128) 93 -> 69 us; single transforms of 512 x 64 x 64 (128
+// tiles) are 5 % slower narrow (hydrodynamic step 2.35 against 2.48 ms), of 512^2 (16) 30 % faster.
+constexpr int64_t kFillTiles = 256, kFillTiles1 = 128;
+
+// Calls f with the candidate `variant` of the 2D or the 3D list.
+template <class C2, class C3, class F>
+static hipError_t with_cands(const Geom &g, int variant, F &&f)
+{
+    if (g.ndim == 2) return with_plan<C2>(variant, f);
+    return with_plan<C3>(variant, f);
+}
+
 // Largest even width <= w (w >= 2).
 static inline int even_width(int w) { return w > 1 ? (w & ~1) : w; }
 
@@ -123,6 +138,13 @@ hipError_t launch_x_r2c(const Geom &g, const T *in, cx<T> *out, bool cube, const
             auto run = [&](auto plc, auto cubec) -> hipError_t {
                 using PL = decltype(plc);
                 constexpr bool CUBE = decltype(cubec)::value;
+                // 2D grids (at most 2048 rows): one wavefront per workgroup, which spreads them over more CUs
+                if (g.ndim == 2) {
+                    constexpr int R1 = XInvRows<PL>::value;
+                    hipLaunchKernelGGL((x_r2c_kernel<T, PL, R1, CUBE, is_pow2c(M), false, true>), dim3((unsigned)cdiv(g.xrows, R1)),
+                                       dim3(R1 * PL::Tp), 0, s, in, out, g.xrows, tw + g.tw_x, g.lt_shift, pack_of(g));
+                    return hipGetLastError();
+                }
                 constexpr int ROWS = XRows<PL>::value;
                 const dim3 grid((unsigned)cdiv(g.xrows, ROWS)), block(ROWS * PL::Tp);
                 // non-temporal hints measured faster at M = 256 and slower at M = 1024; mixed-radix
@@ -134,8 +156,12 @@ hipError_t launch_x_r2c(const Geom &g, const T *in, cx<T> *out, bool cube, const
                     return hipGetLastError();
                 });
             };
-            if (!cube) return run(typename XFwdPlan<M>::type{}, std::false_type{});
-            return with_plan<typename XFwdCands<M>::type>(variant, [&](auto plc) { return run(plc, std::true_type{}); });
+            using C2 = typename X2FwdCands<M>::type;
+            using C3 = typename XFwdCands<M>::type;
+            if (!cube)
+                return with_cands<PlanList<typename ListAt<0, C2>::type>, PlanList<typename ListAt<0, C3>::type>>(
+                    g, 0, [&](auto plc) { return run(plc, std::false_type{}); });
+            return with_cands<C2, C3>(g, variant, [&](auto plc) { return run(plc, std::true_type{}); });
         }
     });
 }
@@ -149,12 +175,17 @@ hipError_t launch_x_c2r(const Geom &g, const cx<T> *in, T *out, const cx<T> *tw,
         if constexpr (M > 1024) {
             return hipErrorInvalidValue;
         } else {
-            return with_plan<typename XInvCands<M>::type>(variant, [&](auto plc) -> hipError_t {
+            return with_cands<typename X2InvCands<M>::type, typename XInvCands<M>::type>(g, variant, [&](auto plc) -> hipError_t {
                 using PL = decltype(plc);
                 constexpr int ROWS = XInvRows<PL>::value;
                 const dim3 grid((unsigned)cdiv(g.xrows, ROWS)), block(ROWS * PL::Tp);
                 const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
                 AdjEpi<T> ea{};
+                if (g.ndim == 2) {
+                    hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_PLAIN, false, false, false, true>), grid, block, 0, s, in,
+                                       out, g.xrows, tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
+                    return hipGetLastError();
+                }
                 // unpadded LDS rows: padded ones measured slower here (512^3 FP32 0.224 against
                 // 0.215 ms, FP64 0.419 against 0.396 ms, 2048^3 FP32 18.5 against 18.0 ms)
                 return with_nt(g.nt && is_pow2c(M), [&](auto ntc) -> hipError_t {
@@ -187,7 +218,9 @@ bool x_fused_ok(const Geom &g)
     bool ok = false;
     (void)by_length(g.M, [&](auto Mc) -> hipError_t {
         constexpr int M = decltype(Mc)::value;
-        if constexpr (M <= 1024) ok = XStepFused<typename XInvPlan<M>::type, typename XFwdPlan<M>::type>::ok;
+        if constexpr (M <= 1024)
+            ok = g.ndim == 2 ? XStepFused<typename X2InvPlan<M>::type, typename X2FwdPlan<M>::type>::ok
+                             : XStepFused<typename XInvPlan<M>::type, typename XFwdPlan<M>::type>::ok;
         return hipSuccess;
     });
     return ok;
@@ -202,8 +235,9 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStre
         if constexpr (M > 1024) {
             return hipErrorInvalidValue;
         } else {
-            using PLI = typename XInvPlan<M>::type;
-            using PLF = typename XFwdPlan<M>::type;
+            auto run = [&](auto pic, auto pfc, auto latc) -> hipError_t {
+            using PLI = decltype(pic);
+            using PLF = decltype(pfc);
             if constexpr (!XStepFused<PLI, PLF>::ok) {
                 return hipErrorInvalidValue;
             } else {
@@ -214,10 +248,13 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStre
                 // measured 1.3 % slower per 512^3 FP32 step, the same in FP64.  Padded LDS rows
                 // (power-of-two M): FP64 steps 438 against 431 steps/s at 512^3, 2768 against 2671
                 // at 256^3; FP32 even.
-                hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M)>), grid, block, 0, s, data, g.xrows,
+                hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), decltype(latc)::value>), grid, block, 0, s, data, g.xrows,
                                    tw + g.tw_x, g.lt_shift, sc, pack_of(g));
                 return hipGetLastError();
             }
+            };
+            if (g.ndim == 2) return run(typename X2InvPlan<M>::type{}, typename X2FwdPlan<M>::type{}, std::true_type{});
+            return run(typename XInvPlan<M>::type{}, typename XFwdPlan<M>::type{}, std::false_type{});
         }
     });
 }
@@ -232,16 +269,22 @@ hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu,
         if constexpr (M > 1024) {
             return hipErrorInvalidValue;
         } else {
-            using PL = typename XInvPlan<M>::type;
-            constexpr int ROWS = XRows<PL>::value;
-            const int64_t nb = cdiv(g.xrows, ROWS);
-            *nblocks = nb;
-            const dim3 grid((unsigned)nb), block(ROWS * PL::Tp);
-            const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-            AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial};
-            hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_ADJOINT>), grid, block, 0, s, mu, out, g.xrows,
-                               tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
-            return hipGetLastError();
+            auto run = [&](auto plc, auto rowsc, auto latc) -> hipError_t {
+                using PL = decltype(plc);
+                constexpr int ROWS = decltype(rowsc)::value;
+                const int64_t nb = cdiv(g.xrows, ROWS);
+                *nblocks = nb;
+                const dim3 grid((unsigned)nb), block(ROWS * PL::Tp);
+                const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
+                AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial};
+                hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_ADJOINT, false, false, false, decltype(latc)::value>), grid, block, 0, s, mu, out, g.xrows,
+                                   tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
+                return hipGetLastError();
+            };
+            using P2 = typename X2InvPlan<M>::type;
+            using P3 = typename XInvPlan<M>::type;
+            if (g.ndim == 2) return run(P2{}, std::integral_constant<int, XInvRows<P2>::value>{}, std::true_type{});  // as launch_x_r2c
+            return run(P3{}, std::integral_constant<int, XRows<P3>::value>{}, std::false_type{});
         }
     });
 }
@@ -256,16 +299,18 @@ hipError_t launch_x_c2r_mac(const Geom &g, const cx<T> *in, T *out, const T *w, 
         if constexpr (M > 1024) {
             return hipErrorInvalidValue;
         } else {
-            using PL = typename XInvPlan<M>::type;
-            constexpr int ROWS = XInvRows<PL>::value;
-            const dim3 grid((unsigned)cdiv(g.xrows, ROWS)), block(ROWS * PL::Tp);
-            const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-            AdjEpi<T> ea{};
-            ea.w = w;
-            ea.add = add ? 1 : 0;
-            hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_MAC>), grid, block, 0, s, in, out, g.xrows, tw + g.tw_x,
-                               g.lt_shift, sc, ea, pack_of(g));
-            return hipGetLastError();
+            return with_cands<PlanList<typename X2InvPlan<M>::type>, PlanList<typename XInvPlan<M>::type>>(g, 0, [&](auto plc) -> hipError_t {
+                using PL = decltype(plc);
+                constexpr int ROWS = XInvRows<PL>::value;
+                const dim3 grid((unsigned)cdiv(g.xrows, ROWS)), block(ROWS * PL::Tp);
+                const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
+                AdjEpi<T> ea{};
+                ea.w = w;
+                ea.add = add ? 1 : 0;
+                hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_MAC>), grid, block, 0, s, in, out, g.xrows, tw + g.tw_x,
+                                   g.lt_shift, sc, ea, pack_of(g));
+                return hipGetLastError();
+            });
         }
     });
 }
@@ -312,6 +357,24 @@ hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hi
                 constexpr int WM = TL::W;
                 const int W = (int)(g.M < WM ? g.M : WM);
                 const int64_t tiles = cdiv(g.M, W);
+                using PN = typename TO::plan;
+                constexpr int WN = NarrowTile<PN>::W;
+                if constexpr (WN < WM) {
+                    if (variant == 0 && tiles * g.n0 < kFillTiles1) {
+                        const int w = (int)(g.M < WN ? g.M : WN);
+                        const int64_t nt = cdiv(g.M, w);
+                        const AxisMap am = y_map(g);
+                        if (dir < 0)
+                            hipLaunchKernelGGL((axis_c2c_kernel<T, PN, WN, -1, 1, false, 1, true>), dim3((unsigned)(nt * g.n0)),
+                                               dim3(WN * PN::Tp), 0, s, data, data, w, g.M, am, nt, tw + g.tw_y, g.lt_shift,
+                                               line_group<T>(w));
+                        else
+                            hipLaunchKernelGGL((axis_c2c_kernel<T, PN, WN, +1, 1, false, 1, true>), dim3((unsigned)(nt * g.n0)),
+                                               dim3(WN * PN::Tp), 0, s, data, data, w, g.M, am, nt, tw + g.tw_y, g.lt_shift,
+                                               line_group<T>(w));
+                        return hipGetLastError();
+                    }
+                }
                 const dim3 grid((unsigned)(tiles * g.n0)), block(WM * PL::Tp);
                 // whole-line tiles: whole planes per XCD (xg = 0, see axis_c2c_kernel), except the
                 // grouped power-of-two tiles (2048 points), where it measured slower
@@ -348,14 +411,31 @@ hipError_t launch_last_c2c(const Geom &g, const cx<T> *src, cx<T> *dst, int dir,
         if constexpr (L < 4) {
             return hipErrorInvalidValue;
         } else {
-            using PL = typename AxisPlan<L>::type;
-            if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
             constexpr int WM = WMax<T, L>::value;
             const int64_t ncols = g.nrows * g.M;
             const int W = (int)(ncols < WM ? ncols : WM);
             const int64_t tiles = cdiv(ncols, W);
-            const dim3 grid((unsigned)tiles), block(WM * PL::Tp);
             const AxisMap am = last_map(g);
+            auto narrow = [&](auto plc) -> hipError_t {
+                using PN = decltype(plc);
+                if (!z_steps_ok<PN>(g.zs)) return hipErrorInvalidValue;
+                constexpr int WN = NarrowTile<PN>::W;
+                const int w = (int)(ncols < WN ? ncols : WN);
+                const int64_t nt = cdiv(ncols, w);
+                if (dir < 0)
+                    hipLaunchKernelGGL((axis_c2c_kernel<T, PN, WN, -1, 1, false, 1, true>), dim3((unsigned)nt),
+                                       dim3(WN * PN::Tp), 0, s, src, dst, w, ncols, am, nt, tw + g.tw_last, g.lt_shift,
+                                       line_group<T>(w));
+                else
+                    hipLaunchKernelGGL((axis_c2c_kernel<T, PN, WN, +1, 1, false, 1, true>), dim3((unsigned)nt),
+                                       dim3(WN * PN::Tp), 0, s, src, dst, w, ncols, am, nt, tw + g.tw_last, g.lt_shift,
+                                       line_group<T>(w));
+                return hipGetLastError();
+            };
+            using PL = typename AxisPlan<L>::type;
+            if (tiles < kFillTiles1) return g.ndim == 2 ? narrow(typename Last2Plan<L>::type{}) : narrow(PL{});
+            if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
+            const dim3 grid((unsigned)tiles), block(WM * PL::Tp);
             if (dir < 0)
                 hipLaunchKernelGGL((axis_c2c_kernel<T, PL, WM, -1>), grid, block, 0, s, src, dst, W, ncols, am, tiles,
                                    tw + g.tw_last, g.lt_shift, 1);
@@ -377,16 +457,27 @@ hipError_t launch_last_c2c_deriv(const Geom &g, const cx<T> *src, cx<T> *dst, in
         if constexpr (L < 4) {
             return hipErrorInvalidValue;
         } else {
-            using PL = typename AxisPlan<L>::type;
-            if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
             constexpr int WM = WMax<T, L>::value;
             const int64_t ncols = g.nrows * g.M;
             const int W = (int)(ncols < WM ? ncols : WM);
             const int64_t tiles = cdiv(ncols, W);
             const DerivArgs da{role, fk, g.nrows, g.M};
-            hipLaunchKernelGGL((axis_c2c_deriv_kernel<T, PL, WM>), dim3((unsigned)tiles), dim3(WM * PL::Tp), 0, s, src,
-                               dst, W, ncols, last_map(g), tw + g.tw_last, g.lt_shift, da);
-            return hipGetLastError();
+            auto run = [&](auto plc, auto wc, auto lpc, int w, int xg) -> hipError_t {
+                using PL = decltype(plc);
+                constexpr int WT = decltype(wc)::value;
+                if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
+                hipLaunchKernelGGL((axis_c2c_deriv_kernel<T, PL, WT, decltype(lpc)::value>), dim3((unsigned)cdiv(ncols, w)),
+                                   dim3(WT * PL::Tp), 0, s, src, dst, w, ncols, last_map(g), tw + g.tw_last, g.lt_shift, da, xg);
+                return hipGetLastError();
+            };
+            auto narrow = [&](auto plc) -> hipError_t {
+                constexpr int WN = NarrowTile<decltype(plc)>::W;
+                const int w = (int)(ncols < WN ? ncols : WN);
+                return run(plc, std::integral_constant<int, WN>{}, std::true_type{}, w, line_group<T>(w));
+            };
+            using PL = typename AxisPlan<L>::type;
+            if (tiles < kFillTiles1) return g.ndim == 2 ? narrow(typename Last2Plan<L>::type{}) : narrow(PL{});
+            return run(PL{}, std::integral_constant<int, WM>{}, std::false_type{}, W, 1);
         }
     });
 }
@@ -421,6 +512,22 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
             const dim3 grid((unsigned)nblocks);
             using P0 = typename LastPlan<L>::type;
             if (mode != LAST_STEP && !z_steps_ok<P0>(g.zs)) return hipErrorInvalidValue;
+            // few tiles: narrow ones (2D grids on the 2D schedules)
+            auto narrow = [&](auto plc, auto modec) -> hipError_t {
+                using PN = decltype(plc);
+                if (!z_steps_ok<PN>(g.zs)) return hipErrorInvalidValue;
+                constexpr int WN = NarrowTile<PN>::W;
+                LastAxisArgs<T> b = a;
+                b.W = even_width(g.M < WN ? (int)g.M : WN);
+                b.tiles_per_row = (int)cdiv(g.M, b.W);
+                b.xg = line_group<T>(b.W);
+                constexpr bool PF = is_pow2c(L) && PN::Rmax <= 16;
+                hipLaunchKernelGGL((last_axis_kernel<T, PN, WN, decltype(modec)::value, 1, PF, ORD_XCD_ROW, false, 1, true>),
+                                   dim3((unsigned)(g.nrows * b.tiles_per_row)), dim3(WN * PN::Tp), 0, s, b);
+                return hipGetLastError();
+            };
+            const bool few = nblocks < (mode == LAST_ADJOINT ? kFillTiles : kFillTiles1);
+            using P2 = typename Last2Plan<L>::type;
             switch (mode) {
             case LAST_STEP: {
                 auto run = [&](auto plc) -> hipError_t {
@@ -431,6 +538,8 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                     LastAxisArgs<T> b = a;
                     b.W = even_width(g.M < TL::W ? (int)g.M : TL::W);
                     b.tiles_per_row = (int)cdiv(g.M, b.W);
+                    if (variant == 0 && g.nrows * b.tiles_per_row < kFillTiles)
+                        return narrow(typename TO::plan{}, std::integral_constant<int, LA_STEP>{});
                     const int64_t nb = (g.nrows == 1) ? b.tiles_per_row : g.nrows * b.tiles_per_row;
                     return with_nt(g.nt && line_group<T>(b.W) == 1, [&](auto ntc) -> hipError_t {
                         hipLaunchKernelGGL((last_axis_kernel<T, PL, TL::W, LA_STEP, 1, TL::PF, ORD_XCD_ROW,
@@ -441,8 +550,7 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                 };
                 // 3D: the z candidates (wider tiles at some lengths); 2D: the list the batched
                 // kernel shares, so that its instances stay bitwise equal to single plans
-                if (g.ndim == 3) return with_plan<typename ZCandsOf<T, L>::type>(variant, run);
-                return with_plan<typename LastCands<L>::type>(variant, run);
+                return with_cands<typename Last2Cands<L>::type, typename ZCandsOf<T, L>::type>(g, variant, run);
             }
             // natural layout (rows of M + 1, not line-aligned): whole rows per XCD, so the lines two
             // tiles share meet in one L2 (measured at 512^3: r2c 403 -> 348 us, c2r 274 -> 262 us)
@@ -464,11 +572,19 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                         });
                     }
                 }
+                if (few) {
+                    constexpr std::integral_constant<int, LA_R2C_NATURAL> m{};
+                    return g.ndim == 2 ? narrow(P2{}, m) : narrow(P0{}, m);
+                }
                 hipLaunchKernelGGL((last_axis_kernel<T, P0, WM, LA_R2C_NATURAL, 1, true, ORD_XCD_ROW>), grid,
                                    dim3(WM * P0::Tp), 0, s, a);
                 break;
             }
             case LAST_C2R_NATURAL:
+                if (few) {
+                    constexpr std::integral_constant<int, LA_C2R_NATURAL> m{};
+                    return g.ndim == 2 ? narrow(P2{}, m) : narrow(P0{}, m);
+                }
                 return with_nt(g.nt && line_group<T>(a.W) == 1, [&](auto ntc) -> hipError_t {
                     hipLaunchKernelGGL(
                         (last_axis_kernel<T, P0, WM, LA_C2R_NATURAL, 1, true, ORD_XCD_ROW, decltype(ntc)::value>), grid,
@@ -476,6 +592,10 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                     return hipGetLastError();
                 });
             case LAST_ADJOINT:
+                if (few) {
+                    constexpr std::integral_constant<int, LA_ADJOINT> m{};
+                    return g.ndim == 2 ? narrow(P2{}, m) : narrow(P0{}, m);
+                }
                 hipLaunchKernelGGL((last_axis_kernel<T, P0, WM, LA_ADJOINT>), grid, dim3(WM * P0::Tp), 0, s, a);
                 break;
             default: return hipErrorInvalidValue;
@@ -530,25 +650,31 @@ hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStrea
     return hipGetLastError();
 }
 
-#define PFC_INSTANTIATE(T)                                                                                            \
+// Explicit instantiations, in groups: one translation unit per dtype and group, so that they build in
+// parallel.
+#define PFC_INSTANTIATE_X(T)                                                                                          \
     template hipError_t launch_x_r2c<T>(const Geom &, const T *, cx<T> *, bool, const cx<T> *, hipStream_t, int);     \
     template hipError_t launch_x_c2r<T>(const Geom &, const cx<T> *, T *, const cx<T> *, hipStream_t, int);           \
-    template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, const cx<T> *, hipStream_t);                        \
-    template bool x_fused_ok<T>(const Geom &);                                                                        \
-    template bool z_blocks_ok<T>(const Geom &, int);                                                                  \
     template hipError_t launch_x_c2r_adjoint<T>(const Geom &, const cx<T> *, const cx<T> *, const T *, const T *, T *, \
                                                 T, double *, int64_t *, const cx<T> *, hipStream_t);                  \
+    template hipError_t launch_x_c2r_mac<T>(const Geom &, const cx<T> *, T *, const T *, bool, const cx<T> *,         \
+                                            hipStream_t);
+#define PFC_INSTANTIATE_XF(T)                                                                                         \
+    template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, const cx<T> *, hipStream_t);                       \
+    template bool x_fused_ok<T>(const Geom &);
+#define PFC_INSTANTIATE_Y(T)                                                                                          \
     template hipError_t launch_y_c2c<T>(const Geom &, cx<T> *, int, const cx<T> *, hipStream_t, int);                 \
     template hipError_t launch_last_fwd<T>(const Geom &, const cx<T> *, cx<T> *, const cx<T> *, hipStream_t);         \
     template hipError_t launch_last_c2c<T>(const Geom &, const cx<T> *, cx<T> *, int, const cx<T> *, hipStream_t);    \
     template hipError_t launch_last_c2c_deriv<T>(const Geom &, const cx<T> *, cx<T> *, int, double, const cx<T> *,    \
-                                                 hipStream_t);                                                        \
-    template hipError_t launch_x_c2r_mac<T>(const Geom &, const cx<T> *, T *, const T *, bool, const cx<T> *,         \
-                                            hipStream_t);                                                             \
+                                                 hipStream_t);
+#define PFC_INSTANTIATE_LAST(T)                                                                                       \
+    template bool z_blocks_ok<T>(const Geom &, int);                                                                  \
+    template hipError_t launch_last<T>(const Geom &, int, const cx<T> *, cx<T> *, cx<T> *, cx<T> *,                   \
+                                       const ModelParams<T> &, const cx<T> *, hipStream_t, int);
+#define PFC_INSTANTIATE_GRID(T)                                                                                       \
     template hipError_t launch_spec_update<T>(const Geom &, int, cx<T> *, const cx<T> *, const cx<T> *,               \
                                               const HydroArgs &, hipStream_t);                                        \
-    template hipError_t launch_last<T>(const Geom &, int, const cx<T> *, cx<T> *, cx<T> *, cx<T> *,                   \
-                                       const ModelParams<T> &, const cx<T> *, hipStream_t, int);                      \
     template hipError_t launch_set_mass<T>(const T *, int64_t, double *, cx<T> *, hipStream_t);                       \
     template hipError_t launch_energy<T>(const Geom &, const T *, const cx<T> *, const double *, double, double,      \
                                          double, int, double, double *, double *, hipStream_t);                       \

@@ -449,6 +449,20 @@ template <> struct ZCandsOf<float, 512> {
 };
 static_assert(ZCandsOf<float, 512>::type::size == ZCands<512>::type::size, "one candidate count per length");
 
+// 2D grids (single plans and batched instances, which share these lists).  A 2D pass has at most a few
+// hundred pencils or rows, so it is bound by the latency of one workgroup's chain, not by bandwidth:
+// the default holds 8 elements per thread where the 3D lists hold 16, which halves the chain, and the
+// 3D default moves to the end (candidate numbers in between keep their meaning).
+template <int M> struct X2FwdCands { using type = typename XFwdCands<M>::type; };
+template <int M> struct X2InvCands { using type = typename XInvCands<M>::type; };
+template <int L> struct Last2Cands { using type = typename LastCands<L>::type; };
+template <> struct X2FwdCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
+template <> struct X2InvCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
+template <> struct X2FwdCands<256> { using type = PlanList<Radices<4, 8, 8>, Radices<4, 8, 8>, Radices<16, 16>>; };
+template <> struct Last2Cands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
+template <> struct Last2Cands<256> { using type = PlanList<Radices<4, 8, 8>, Radices<4, 8, 8>, Radices<16, 16>>; };
+template <> struct Last2Cands<512> { using type = PlanList<Radices<8, 8, 8>, Radices<16, 16, 2>, Radices<2, 16, 16>>; };
+
 // The radix schedule of a candidate (a Tiled candidate's own; the default candidate's schedule is
 // what the other kernels of a length take, with the length's default tile)
 template <class C, class = void>
@@ -463,6 +477,9 @@ template <int M> struct XFwdPlan { using type = typename PlanOf<typename ListAt<
 template <int M> struct XInvPlan { using type = typename PlanOf<typename ListAt<0, typename XInvCands<M>::type>::type>::type; };
 template <int L> struct AxisPlan { using type = typename PlanOf<typename ListAt<0, typename AxisCands<L>::type>::type>::type; };
 template <int L> struct LastPlan { using type = typename PlanOf<typename ListAt<0, typename LastCands<L>::type>::type>::type; };
+template <int M> struct X2FwdPlan { using type = typename PlanOf<typename ListAt<0, typename X2FwdCands<M>::type>::type>::type; };
+template <int M> struct X2InvPlan { using type = typename PlanOf<typename ListAt<0, typename X2InvCands<M>::type>::type>::type; };
+template <int L> struct Last2Plan { using type = typename PlanOf<typename ListAt<0, typename Last2Cands<L>::type>::type>::type; };
 
 // Calls f(PL{}) with the schedule number v of List (v out of range: candidate 0).
 template <class List, int I = 0, class F>
@@ -529,6 +546,53 @@ __device__ __forceinline__ void apply_twiddles(cx<T> *v, int jj, const cx<T> *__
     }
 }
 
+// A thread's twiddles of every stage of PL (forward sign), loaded ahead of the transform.  Where few
+// workgroups run (2D grids, small 3D ones), nothing else covers the latency of the table loads between
+// two exchanges, so they are issued with the pencil's own loads; elsewhere the registers are worth more.
+template <typename T, class PL>
+struct StageTw {
+    __host__ __device__ static constexpr int off(int s)
+    {
+        int n = 0;
+        for (int i = 1; i < s; ++i) n += PL::nb(PL::radix(i)) * PL::radix(i);
+        return n;
+    }
+    static constexpr int n = off(PL::nst);
+    cx<T> w[n > 0 ? n : 1];
+};
+// ... as long as they are few: at most 8 FP32 elements per thread, or 4 FP64 registers' worth
+template <typename T, class PL>
+constexpr bool preload_tw() { return (int)sizeof(T) * PL::Rmax <= 64; }
+
+template <typename T, class PL, int TWM>
+__device__ __forceinline__ void load_stage_tw(StageTw<T, PL> &o, int t, const cx<T> *__restrict__ tw, int lt_shift)
+{
+    constexpr int TW = is_pow2c(PL::L) ? TWM : TW_MIX;
+    static_for<1, PL::nst>([&](auto sc) {
+        constexpr int s = decltype(sc)::value, R = PL::radix(s), Ns = PL::prefix(s);
+#pragma unroll
+        for (int b = 0; b < PL::nb(R); ++b) {
+            const int jj = (int)((unsigned)(t + b * PL::Tp) % (unsigned)Ns);
+            cx<T> *w = &o.w[StageTw<T, PL>::off(s) + b * R];
+            if constexpr (TW == TW_LT) {
+#pragma unroll
+                for (int r = 1; r < R; ++r) w[r] = twiddle<T, -1>(tw, lt_shift, jj * r, ilog2c(Ns * R));
+            } else {
+                const cx<T> *st;
+                if constexpr (TW == TW_MIX) {
+                    using F = typename MixPlan<PL::L>::type;
+                    static_assert(same_stages<PL, F>() || same_stages<PL, typename F::Reverse>(), "stages of the table");
+                    st = tw + (same_stages<PL, F>() ? 0 : stage_blocks_off<F>(F::nst)) + stage_blocks_off<PL>(s) + jj * R;
+                } else {
+                    st = tw + (1u << lt_shift) + stage_tw_offset(Ns * R, R) + (unsigned)(jj * R);
+                }
+#pragma unroll
+                for (int r = 1; r < R; ++r) w[r] = st[r];
+            }
+        }
+    });
+}
+
 // Runs every stage of the schedule PL for one pencil.
 // On entry: v[b * R0 + r] = x[t + b Tp + r L / R0] for b < nb(R0) (R0 = first radix), where that
 // butterfly exists (jok).  On exit: v[b * Rl + r] = X[t + b Tp + r L / Rl] for b < nb(Rl) likewise
@@ -538,10 +602,11 @@ __device__ __forceinline__ void apply_twiddles(cx<T> *v, int jj, const cx<T> *__
 // write is preceded by a barrier, so the caller may have used the same LDS just before.
 // G > 1: the workgroup's pencils form G groups (this thread's is `grp`) that take turns in one
 // LDS area sized for a single group, so each exchange costs G barrier pairs and 1/G of the LDS.
-// Lengths that are not powers of two always take their own table (TW_MIX).
-template <typename T, class PL, int DIR, int TWM = TW_STAGE, int G = 1, class Lds>
+// Lengths that are not powers of two always take their own table (TW_MIX).  PRE: the twiddles are in
+// `pre` (load_stage_tw) instead.
+template <typename T, class PL, int DIR, int TWM = TW_STAGE, int G = 1, bool PRE = false, class Lds>
 __device__ __forceinline__ void fft_stages(cx<T> *v, int t, Lds &&lds, const cx<T> *__restrict__ tw, int lt_shift,
-                                           int grp = 0)
+                                           int grp = 0, const StageTw<T, PL> *pre = nullptr)
 {
     constexpr int L = PL::L;
     constexpr int Tp = PL::Tp;
@@ -586,8 +651,17 @@ __device__ __forceinline__ void fft_stages(cx<T> *v, int t, Lds &&lds, const cx<
                 }
             }
 #pragma unroll
-            for (int b = 0; b < B2; ++b)
-                apply_twiddles<T, PL, s + 1, DIR, TW>(&v[b * R2], (int)((unsigned)(t + b * Tp) % Ns2), tw, lt_shift);
+            for (int b = 0; b < B2; ++b) {
+                if constexpr (PRE) {
+#pragma unroll
+                    for (int r = 1; r < R2; ++r) {
+                        const cx<T> w = pre->w[StageTw<T, PL>::off(s + 1) + b * R2 + r];
+                        v[b * R2 + r] = cmul(v[b * R2 + r], DIR > 0 ? conj(w) : w);
+                    }
+                } else {
+                    apply_twiddles<T, PL, s + 1, DIR, TW>(&v[b * R2], (int)((unsigned)(t + b * Tp) % Ns2), tw, lt_shift);
+                }
+            }
         }
     });
 }

@@ -149,15 +149,38 @@ __device__ __forceinline__ int xidx(int e)
 // Identity layout of a packed spectrum with rows of M values (2D plans, the batched form).
 __host__ __device__ inline Pack row_pack(int64_t M) { return Pack{1, M, 0, 0}; }
 
+// Twiddles of an x pass loaded ahead (see StageTw): the stages', and the split twiddles W_{2M}^k of the
+// elements a thread holds at the real end (last radix of the r2c, FWD; first of the c2r).
+template <typename T, class PL>
+struct XTw {
+    StageTw<T, PL> st;
+    cx<T> split[PL::Rmax];
+};
+template <typename T, class PL, bool FWD>
+__device__ __forceinline__ void load_xtw(XTw<T, PL> &o, int t, const cx<T> *__restrict__ tw, int lt_shift)
+{
+    load_stage_tw<T, PL, FWD ? TW_LT : TW_STAGE>(o.st, t, tw, lt_shift);
+    constexpr int R = FWD ? PL::last : PL::first;
+#pragma unroll
+    for (int b = 0; b < PL::nb(R); ++b)
+        if (PL::jok(t + b * PL::Tp, R))
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                o.split[b * R + r] = split_twiddle<T, PL::L>(tw, lt_shift, t + b * PL::Tp + r * (PL::L / R));
+}
+
 // One block of ROWS rows (block index `bid`); `sh` holds ROWS * XPitch<T, M, PAD> LDS slots.
 // Uses threads 0 .. ROWS*Tp-1, which must be all threads of the workgroup.  FROM_LDS: the rows'
 // reals are not read from `in` but from `sh` (row p at sh[p LD], LD the row pitch, as packed
 // pairs, contiguous), where the caller
 // has left them.  Output row rr (= e nrows + row) goes to the layout `pk`.
-template <typename T, class PL, int ROWS, bool CUBE, bool PAD = false, bool NT = false, bool FROM_LDS = false>
+// PRE: the twiddles come from `pre` (load_xtw).
+template <typename T, class PL, int ROWS, bool CUBE, bool PAD = false, bool NT = false, bool FROM_LDS = false,
+          bool PRE = false>
 __device__ __forceinline__ void x_r2c_block(const T *__restrict__ in, cx<T> *__restrict__ out, int64_t nrows,
                                             const cx<T> *__restrict__ tw, int lt_shift, int64_t bid, cx<T> *sh,
-                                            const Pack &pk, const int tid = (int)threadIdx.x)
+                                            const Pack &pk, const int tid = (int)threadIdx.x,
+                                            const XTw<T, PL> *pre = nullptr)
 {
     constexpr int M = PL::L, Tp = PL::Tp, R0 = PL::first, Rl = PL::last, Rmax = PL::Rmax;
     constexpr int LD = XPitch<T, M, PAD>::value;  // row pitch in LDS
@@ -182,7 +205,8 @@ __device__ __forceinline__ void x_r2c_block(const T *__restrict__ in, cx<T> *__r
             v[b * R0 + r] = z;
         }
     auto lds = [&](int e) -> cx<T> & { return sh[p * LD + xidx<T, M, PAD>(e)]; };
-    fft_stages<T, PL, -1, TW_LT>(v, t, lds, tw, lt_shift);  // measured faster here than TW_STAGE
+    // measured faster here than TW_STAGE
+    fft_stages<T, PL, -1, TW_LT, 1, PRE>(v, t, lds, tw, lt_shift, 0, PRE ? &pre->st : nullptr);
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < PL::nb(Rl); ++b)
@@ -206,19 +230,23 @@ __device__ __forceinline__ void x_r2c_block(const T *__restrict__ in, cx<T> *__r
                 const cx<T> Zp = lds(M - k);
                 const cx<T> E = {(Zk.x + Zp.x) * h, (Zk.y - Zp.y) * h};
                 const cx<T> O = {(Zk.y + Zp.y) * h, (Zp.x - Zk.x) * h};
-                X = E + cmul(split_twiddle<T, M>(tw, lt_shift, k), O);
+                X = E + cmul(PRE ? pre->split[b * Rl + r] : split_twiddle<T, M>(tw, lt_shift, k), O);
             }
             if (valid) st_grid<NT>(&dst[pk.col(k)], X);
         }
 }
 
-template <typename T, class PL, int ROWS, bool CUBE, bool PAD = false, bool NT = false>
+template <typename T, class PL, int ROWS, bool CUBE, bool PAD = false, bool NT = false, bool LAT = false>
 __global__ __launch_bounds__(ROWS *PL::Tp) void x_r2c_kernel(const T *__restrict__ in, cx<T> *__restrict__ out,
                                                               int64_t nrows, const cx<T> *__restrict__ tw,
                                                               int lt_shift, Pack pk)
 {
     __shared__ cx<T> sh[ROWS * XPitch<T, PL::L, PAD>::value];
-    x_r2c_block<T, PL, ROWS, CUBE, PAD, NT>(in, out, nrows, tw, lt_shift, blockIdx.x, sh, pk);
+    constexpr bool PRE = LAT && preload_tw<T, PL>();
+    XTw<T, PL> pre;
+    if constexpr (PRE) load_xtw<T, PL, true>(pre, (int)threadIdx.x % PL::Tp, tw, lt_shift);
+    x_r2c_block<T, PL, ROWS, CUBE, PAD, NT, false, PRE>(in, out, nrows, tw, lt_shift, blockIdx.x, sh, pk,
+                                                        (int)threadIdx.x, &pre);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -249,9 +277,10 @@ struct AdjEpi {
 // Pre-combination of one row for the c2r: own elements X(k) from `src` (column k at src[pk.col(k)]);
 // the mirror X(M-k) either through LDS (PG = false) or straight from `src` (PG = true: a second,
 // reversed but coalesced load of the same cache lines, without the LDS round trip and its barrier).
-template <typename T, class PL, int ROWS, bool PAD, bool PG = false, bool NT = false>
+template <typename T, class PL, int ROWS, bool PAD, bool PG = false, bool NT = false, bool PRE = false>
 __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid, int t, cx<T> *rowlds,
-                                          const cx<T> *__restrict__ tw, int lt_shift, const Pack &pk)
+                                          const cx<T> *__restrict__ tw, int lt_shift, const Pack &pk,
+                                          const XTw<T, PL> *pre = nullptr)
 {
     constexpr int M = PL::L, Tp = PL::Tp, R0 = PL::first, Rmax = PL::Rmax;
     cx<T> mir[PG ? Rmax : 1];
@@ -296,7 +325,7 @@ __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid
                     c = rowlds[xidx<T, M, PAD>(M - k)];
                 const cx<T> E = {(a.x + c.x) * h, (a.y - c.y) * h};
                 const cx<T> D = {(a.x - c.x) * h, (a.y + c.y) * h};
-                const cx<T> O = cmul(conj(split_twiddle<T, M>(tw, lt_shift, k)), D);
+                const cx<T> O = cmul(conj(PRE ? pre->split[b * R0 + r] : split_twiddle<T, M>(tw, lt_shift, k)), D);
                 v[b * R0 + r] = {E.x - O.y, E.y + O.x};
             }
         }
@@ -305,10 +334,11 @@ __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid
 // TO_LDS (EPI_PLAIN): the scaled reals of row p are left in sh[p LD] (LD the row pitch, as packed
 // pairs, contiguous) instead of being stored to `out`.
 template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = false, bool NT = false,
-          bool TO_LDS = false>
+          bool TO_LDS = false, bool PRE = false>
 __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nrows, const cx<T> *__restrict__ tw,
                                             int lt_shift, T sc, const AdjEpi<T> &ea, int64_t bid, cx<T> *sh,
-                                            const Pack &pk, const int tid = (int)threadIdx.x)
+                                            const Pack &pk, const int tid = (int)threadIdx.x,
+                                            const XTw<T, PL> *pre = nullptr)
 {
     static_assert(!TO_LDS || EPI == EPI_PLAIN, "staging only for the plain epilogue");
     constexpr int M = PL::L, Tp = PL::Tp, Rl = PL::last, Rmax = PL::Rmax;
@@ -320,8 +350,8 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
     const int64_t r0 = pk.x_row(valid ? rho : 0, &ibase);  // real-field row
     auto lds = [&](int e) -> cx<T> & { return sh[p * LD + xidx<T, M, PAD>(e)]; };
     cx<T> v[Rmax];
-    x_c2r_row<T, PL, ROWS, PAD, PG, NT>(v, in + ibase, valid, t, &sh[p * LD], tw, lt_shift, pk);
-    fft_stages<T, PL, +1>(v, t, lds, tw, lt_shift);
+    x_c2r_row<T, PL, ROWS, PAD, PG, NT, PRE>(v, in + ibase, valid, t, &sh[p * LD], tw, lt_shift, pk, pre);
+    fft_stages<T, PL, +1, TW_STAGE, 1, PRE>(v, t, lds, tw, lt_shift, 0, PRE ? &pre->st : nullptr);
     cx<T> *dst = reinterpret_cast<cx<T> *>(out) + r0 * M;
     if constexpr (EPI == EPI_MAC) {
         if (valid) {
@@ -356,8 +386,9 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
         }
     } else {
         cx<T> w[Rmax];
-        x_c2r_row<T, PL, ROWS, PAD, PG>(w, ea.in2 + r0 * M, valid, t, &sh[p * LD], tw, lt_shift, row_pack(M));
-        fft_stages<T, PL, +1>(w, t, lds, tw, lt_shift);
+        x_c2r_row<T, PL, ROWS, PAD, PG, false, PRE>(w, ea.in2 + r0 * M, valid, t, &sh[p * LD], tw, lt_shift,
+                                                    row_pack(M), pre);
+        fft_stages<T, PL, +1, TW_STAGE, 1, PRE>(w, t, lds, tw, lt_shift, 0, PRE ? &pre->st : nullptr);
         const cx<T> *pn = reinterpret_cast<const cx<T> *>(ea.psi_n) + r0 * M;
         const cx<T> *pn1 = reinterpret_cast<const cx<T> *>(ea.psi_np1) + r0 * M;
         double acc = 0.0;
@@ -380,13 +411,17 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
     }
 }
 
-template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = false, bool NT = false>
+template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = false, bool NT = false, bool LAT = false>
 __global__ __launch_bounds__(ROWS *PL::Tp) void x_c2r_kernel(const cx<T> *in, T *out, int64_t nrows,
                                                               const cx<T> *__restrict__ tw, int lt_shift, T sc,
                                                               AdjEpi<T> ea, Pack pk)
 {
     __shared__ cx<T> sh[ROWS * XPitch<T, PL::L, PAD>::value];
-    x_c2r_block<T, PL, ROWS, EPI, PAD, PG, NT>(in, out, nrows, tw, lt_shift, sc, ea, blockIdx.x, sh, pk);
+    constexpr bool PRE = LAT && preload_tw<T, PL>();
+    XTw<T, PL> pre;
+    if constexpr (PRE) load_xtw<T, PL, false>(pre, (int)threadIdx.x % PL::Tp, tw, lt_shift);
+    x_c2r_block<T, PL, ROWS, EPI, PAD, PG, NT, false, PRE>(in, out, nrows, tw, lt_shift, sc, ea, blockIdx.x, sh, pk,
+                                                           (int)threadIdx.x, &pre);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -413,7 +448,7 @@ struct XFused {
 // One block of R rows (block index `bid`) of packed spectra in the layout `pk`; `sh` holds
 // R XPitch<T, M, PAD> LDS slots; NTH threads.  In place (in == out) is safe: the block reads all its
 // rows before it writes.
-template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false>
+template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false, bool LAT = false>
 __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int64_t nrows,
                                                 const cx<T> *__restrict__ tw, int lt_shift, T sc, int64_t bid,
                                                 cx<T> *sh, const Pack &pk, const int tid = (int)threadIdx.x)
@@ -422,26 +457,33 @@ __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int
     static_assert(F::ok && PLI::L == PLF::L, "schedules must share the workgroup");
     constexpr int LD = XPitch<T, PLI::L, PAD>::value;
     const AdjEpi<T> ea{};
+    constexpr bool PRE = LAT && preload_tw<T, PLI>() && preload_tw<T, PLF>();
+    XTw<T, PLI> prei;
+    XTw<T, PLF> pref;
+    if constexpr (PRE) {
+        load_xtw<T, PLI, false>(prei, tid % PLI::Tp, tw, lt_shift);
+        load_xtw<T, PLF, true>(pref, tid % PLF::Tp, tw, lt_shift);
+    }
 #pragma unroll
     for (int s = 0; s < F::R / F::RI; ++s)
-        x_c2r_block<T, PLI, F::RI, EPI_PLAIN, PAD, false, NT, true>(in, nullptr, nrows, tw, lt_shift, sc, ea,
-                                                                    bid * (F::R / F::RI) + s, sh + s * F::RI * LD,
-                                                                    pk, tid);
+        x_c2r_block<T, PLI, F::RI, EPI_PLAIN, PAD, false, NT, true, PRE>(in, nullptr, nrows, tw, lt_shift, sc, ea,
+                                                                         bid * (F::R / F::RI) + s, sh + s * F::RI * LD,
+                                                                         pk, tid, &prei);
     __syncthreads();  // all staged rows written
 #pragma unroll
     for (int s = 0; s < F::R / F::RF; ++s)
-        x_r2c_block<T, PLF, F::RF, true, PAD, NT, true>(nullptr, out, nrows, tw, lt_shift, bid * (F::R / F::RF) + s,
-                                                        sh + s * F::RF * LD, pk, tid);
+        x_r2c_block<T, PLF, F::RF, true, PAD, NT, true, PRE>(nullptr, out, nrows, tw, lt_shift, bid * (F::R / F::RF) + s,
+                                                             sh + s * F::RF * LD, pk, tid, &pref);
 }
 
 // The fused x pass of the single-plan step between two steps: one workgroup of NTH threads (one
 // wavefront in the step) takes XFused<PLI, PLF, NTH>::R rows of the packed spectrum, in place.
-template <typename T, class PLI, class PLF, int NTH, bool NT, bool PAD>
+template <typename T, class PLI, class PLF, int NTH, bool NT, bool PAD, bool LAT = false>
 __global__ __launch_bounds__(NTH) void x_c2r_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw,
                                                         int lt_shift, T sc, Pack pk)
 {
     __shared__ cx<T> sh[XFused<PLI, PLF, NTH>::R * XPitch<T, PLI::L, PAD>::value];
-    x_c2r_r2c_block<T, PLI, PLF, NTH, NT, PAD>(data, data, nrows, tw, lt_shift, sc, blockIdx.x, sh, pk);
+    x_c2r_r2c_block<T, PLI, PLF, NTH, NT, PAD, LAT>(data, data, nrows, tw, lt_shift, sc, blockIdx.x, sh, pk);
 }
 
 
@@ -484,6 +526,24 @@ struct PencilTile<float, 2048> {
     static constexpr int W = 16, E = 32, G = 2;  // whole 128-byte lines; 1024 threads, 128 KB
     static constexpr bool PF = false;
 };
+// Narrow tiles of the strided passes, for launches whose full-width tiles would not fill the chip (the
+// launcher's rule, kFillTiles): as many pencils as make one wavefront, at least two (pair tiles are
+// split in halves).  A pass over few pencils is bound by the latency of one workgroup's chain of loads,
+// exchanges and stores, and most CUs have none: one 512-point tile of 16 pencils per CU puts a 512^2
+// step's whole last-axis pass on 16 of 256 CUs.  Narrow tiles read and write parts of a 128-byte line;
+// the tiles that share one run on one XCD (xcd_tile_order), and such grids fit the L2s.
+template <class PL>
+struct NarrowTile {
+    static constexpr int W = 64 / PL::Tp < 2 ? 2 : 64 / PL::Tp;
+};
+// LDS slot of element e: with LP (narrow tiles) one spare slot after every 8.  A pencil's slots are
+// then only a few words wide, and the first stage's writes, R elements apart between neighbouring
+// threads, would meet on two bank positions.
+template <bool LP>
+__host__ __device__ constexpr int pencil_slot(int e)
+{
+    return LP ? e + (e >> 3) : e;
+}
 template <class PL, int E>
 using SpreadIf = std::conditional_t<(E > 0), Spread<PL, (E > 0 ? E : PL::Rmax)>, PL>;
 
@@ -536,7 +596,7 @@ struct DerivArgs {
 // the launcher checks).  A workgroup handles W adjacent columns (W <= WMAX); its threads are laid out
 // column-fastest so each load/store instruction moves W * sizeof(cx) contiguous bytes per element
 // row (within one 128-byte column chunk).  `bid` is the logical tile index (see xcd_tile_order).
-template <typename T, class PL, int WMAX, int DIR, bool NT = false, int G = 1, bool DERIV = false>
+template <typename T, class PL, int WMAX, int DIR, bool NT = false, int G = 1, bool DERIV = false, bool LP = false>
 __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int W, int64_t ncols, const AxisMap &am,
                                                int64_t tiles_per_batch, const cx<T> *__restrict__ tw, int lt_shift,
                                                int64_t bid, cx<T> *sh, const DerivArgs &da = DerivArgs{},
@@ -549,6 +609,8 @@ __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int
     const bool valid = p < W && col < ncols;
     const int64_t base = am.base(batch, valid ? col : 0) + am.elem(t);
     const int64_t estride = am.estride;
+    constexpr bool PRE = LP && preload_tw<T, PL>();
+    StageTw<T, PL> pre;
     cx<T> v[Rmax];
 #pragma unroll
     for (int b = 0; b < PL::nb(R0); ++b)
@@ -577,8 +639,9 @@ __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int
             }
     }
     constexpr int GW = WMAX / G;  // pencils per LDS group (see fft_stages)
-    auto lds = [&](int e) -> cx<T> & { return sh[e * GW + p % GW]; };
-    fft_stages<T, PL, DIR, TW_STAGE, G>(v, t, lds, tw, lt_shift, p / GW);
+    auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * GW + p % GW]; };
+    if constexpr (PRE) load_stage_tw<T, PL, TW_STAGE>(pre, t, tw, lt_shift);
+    fft_stages<T, PL, DIR, TW_STAGE, G, PRE>(v, t, lds, tw, lt_shift, p / GW, &pre);
     if (valid) {
 #pragma unroll
         for (int b = 0; b < PL::nb(Rl); ++b)
@@ -605,13 +668,13 @@ __device__ __forceinline__ int64_t plane_xcd_order(int64_t b, int64_t tiles_per_
 // With batch blocks (am.bzs > 0: 2^bzs batches share the rows of one block), the plane order runs
 // over whole blocks, and inside a block over tiles first, then the batches of the block, so that
 // consecutive workgroups of an XCD read neighbouring 128-byte chunks.
-template <typename T, class PL, int WMAX, int DIR, int OCC = 1, bool NT = false, int G = 1>
+template <typename T, class PL, int WMAX, int DIR, int OCC = 1, bool NT = false, int G = 1, bool LP = false>
 __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void axis_c2c_kernel(const cx<T> *src, cx<T> *dst, int W,
                                                                  int64_t ncols, AxisMap am, int64_t tiles_per_batch,
                                                                  const cx<T> *__restrict__ tw, int lt_shift, int xg)
 {
     static_assert(WMAX % G == 0, "groups of whole pencils");
-    __shared__ cx<T> sh[PL::L * WMAX / G];
+    __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX / G];
     int64_t bid;
     if (xg == 0) {
         const int64_t tb = tiles_per_batch << am.bzs;
@@ -622,19 +685,19 @@ __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void axis_c2c_kernel(const cx<T>
     } else {
         bid = xcd_tile_order(blockIdx.x, gridDim.x, xg);
     }
-    axis_c2c_block<T, PL, WMAX, DIR, NT, G>(src, dst, W, ncols, am, tiles_per_batch, tw, lt_shift, bid, sh);
+    axis_c2c_block<T, PL, WMAX, DIR, NT, G, false, LP>(src, dst, W, ncols, am, tiles_per_batch, tw, lt_shift, bid, sh);
 }
 
 // Inverse strided FFT of the spectral derivative i k_role of `src` (DerivArgs), out of place.
-template <typename T, class PL, int WMAX>
+template <typename T, class PL, int WMAX, bool LP = false>
 __global__ __launch_bounds__(WMAX *PL::Tp) void axis_c2c_deriv_kernel(const cx<T> *src, cx<T> *dst, int W,
                                                                    int64_t ncols, AxisMap am,
                                                                    const cx<T> *__restrict__ tw, int lt_shift,
-                                                                   DerivArgs da)
+                                                                   DerivArgs da, int xg)
 {
-    __shared__ cx<T> sh[PL::L * WMAX];
-    axis_c2c_block<T, PL, WMAX, +1, false, 1, true>(src, dst, W, ncols, am, (ncols + W - 1) / W, tw, lt_shift,
-                                                    blockIdx.x, sh, da);
+    __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX];
+    axis_c2c_block<T, PL, WMAX, +1, false, 1, true, LP>(src, dst, W, ncols, am, (ncols + W - 1) / W, tw, lt_shift,
+                                                        xcd_tile_order(blockIdx.x, gridDim.x, xg), sh, da);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -658,6 +721,7 @@ struct LastAxisArgs {
     int M;
     int W;
     int tiles_per_row;
+    int xg;            // 2D: workgroups per line (xcd_tile_order), 0 or 1 for whole-line tiles
     const cx<T> *tw;
     int lt_shift;
     ModelParams<T> mp;
@@ -738,7 +802,8 @@ __device__ __forceinline__ SlotInfo la_slot(int64_t nrows, int TR, int W, int p,
 
 // G > 1 (STEP only): the pencils form G groups of WMAX / G adjacent slots that take turns in an LDS
 // area of L * WMAX / G values (see fft_stages); pair tiles then interleave their two rows.
-template <typename T, class PL, int WMAX, int MODE, bool PF = true, int ORD = ORD_TILE, bool NT = false, int G = 1>
+template <typename T, class PL, int WMAX, int MODE, bool PF = true, int ORD = ORD_TILE, bool NT = false, int G = 1,
+          bool LP = false>
 __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_t bid, cx<T> *sh)
 {
     static_assert(G == 1 || MODE == LA_STEP, "grouped LDS only in the step");
@@ -752,7 +817,7 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
     const int64_t nrows = a.nrows, M = a.M;
     const SlotInfo si = la_slot<ORD, IL>(nrows, a.tiles_per_row, W, p < W ? p : 0, bid);
     const bool valid = p < W && si.kx < M;  // the last column tile of a row may be partial
-    auto lds = [&](int e) -> cx<T> & { return sh[e * GW + p % GW]; };
+    auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * GW + p % GW]; };
     // Element e = t + k of this lane's pencil in a packed array lies at pk.at(t, row, kx) + k estride
     // (k a multiple of the layout's block size Z, which the launcher checks).  The address is split
     // into a wave-uniform part (the tile origin, the wave's first t, and k * estride: scalar
@@ -816,6 +881,10 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
     } else {
         // STEP with PF: the state values this thread updates are loaded before the forward FFT so
         // that their latency overlaps the FFT
+        constexpr bool PRE = LP && preload_tw<T, PL>();
+        constexpr bool SYM = std::is_same_v<PL, PR>;  // one set of twiddles serves both directions
+        StageTw<T, PL> pre;
+        StageTw<T, PR> prei;
         cx<T> spre[(MODE == LA_STEP && PF) ? Rmax : 1];
         if constexpr (MODE == LA_STEP && PF) {
 #pragma unroll
@@ -833,9 +902,13 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
 #pragma unroll
             for (int r = 0; r < R0; ++r)
                 v[b * R0 + r] = valid ? ld_grid<NT>(gp(a.src, b * Tp + r * (L / R0))) : cx<T>{T(0), T(0)};
-        fft_stages<T, PL, -1, TW_STAGE, G>(v, t, lds, a.tw, a.lt_shift, grp);
+        if constexpr (PRE) {
+            load_stage_tw<T, PL, TW_STAGE>(pre, t, a.tw, a.lt_shift);
+            if constexpr (!SYM && MODE == LA_STEP) load_stage_tw<T, PR, TW_STAGE>(prei, t, a.tw, a.lt_shift);
+        }
+        fft_stages<T, PL, -1, TW_STAGE, G, PRE>(v, t, lds, a.tw, a.lt_shift, grp, &pre);
         // forward spectrum in natural order: v[b*Rl + r] = X(e), e = t + b*Tp + r*L/Rl
-        auto partner_val = [&](int e) -> cx<T> { return sh[neg_mod<L>(e) * GW + si.partner % GW]; };
+        auto partner_val = [&](int e) -> cx<T> { return sh[pencil_slot<LP>(neg_mod<L>(e)) * GW + si.partner % GW]; };
         auto spectrum_to_lds = [&]() {
 #pragma unroll
             for (int b = 0; b < PL::nb(Rl); ++b)
@@ -879,7 +952,28 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
             // which another thread owns; the mirror's N comes from LDS now, its S in a second LDS
             // round, so no thread reads a state value that another thread has already updated.
             const T dt = mp.dt, nl = mp.nl, h = T(0.5);
-            if (si.has_pairs) {  // uniform per workgroup
+            // narrow tiles: the mirror's S goes through an LDS area of its own in the round of N, behind
+            // the tile's slots (fold_slots)
+            constexpr bool ONE = LP && PF;
+            cx<T> *const sh2 = sh + pencil_slot<LP>(L) * GW;
+            auto fold = [&](int q) { return nrows == 1 || q == 0 ? 0 : 1; };  // folded pencil in slot q
+            if constexpr (ONE) {
+                if (si.has_pairs) {  // uniform per workgroup
+                    __syncthreads();
+                    if (si.partner >= 0 && valid) {  // (slots past W repeat slot 0)
+#pragma unroll
+                        for (int b = 0; b < PL::nb(Rl); ++b)
+                            if (PL::jok(t + b * Tp, Rl))
+#pragma unroll
+                            for (int r = 0; r < Rl; ++r) {
+                                const int e = t + b * Tp + r * (L / Rl);
+                                lds(e) = v[b * Rl + r];
+                                sh2[fold(p) * L + e] = spre[b * Rl + r];
+                            }
+                    }
+                    __syncthreads();
+                }
+            } else if (si.has_pairs) {  // uniform per workgroup
 #pragma unroll
                 for (int gg = 0; gg < G; ++gg) {
                     const bool mine = (G == 1) || (grp == gg);
@@ -928,7 +1022,33 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
                         v[b * Rl + r] = Snew;
                     }
             }
-            if (si.has_pairs) {  // uniform per workgroup
+            if constexpr (ONE) {
+                if (si.partner >= 0) {
+#pragma unroll
+                    for (int b = 0; b < PL::nb(Rl); ++b)
+                        if (PL::jok(t + b * Tp, Rl))
+#pragma unroll
+                        for (int r = 0; r < Rl; ++r) {
+                            const int e = t + b * Tp + r * (L / Rl);
+                            const T kz = mp.fk[0] * (T)signed_index(e, L);
+                            const T q0 = kz * kz + ky * ky, qn = q0 + kxn * kxn;
+                            const T A0 = amult(mp, q0), AN = amult(mp, qn);
+                            // the operations of the two rounds below, in their order
+                            const cx<T> Nr = partner_val(e), Sp = sh2[fold(si.partner) * L + neg_mod<L>(e)];
+                            const cx<T> N = {v[b * Rl + r].x * nl, v[b * Rl + r].y * nl}, S = spre[b * Rl + r];
+                            const cx<T> Np = {Nr.x * nl, Nr.y * nl};
+                            const cx<T> N0 = {(N.x + Np.x) * h, (N.y - Np.y) * h};
+                            const cx<T> NN = {(N.y + Np.y) * h, (Np.x - N.x) * h};
+                            const T g0 = dt * q0 * A0, gn = dt * qn * AN;
+                            const cx<T> Gt = {-g0 * N0.x + gn * NN.y, -g0 * N0.y - gn * NN.x};
+                            const cx<T> S0 = {(S.x + Sp.x) * h, (S.y - Sp.y) * h};
+                            const cx<T> SN = {(S.y + Sp.y) * h, (Sp.x - S.x) * h};
+                            const cx<T> Snew = {A0 * S0.x - AN * SN.y + Gt.x, A0 * S0.y + AN * SN.x + Gt.y};
+                            if (valid) st_grid<NT>(gp(a.state, b * Tp + r * (L / Rl)), Snew);
+                            v[b * Rl + r] = Snew;
+                        }
+                }
+            } else if (si.has_pairs) {  // uniform per workgroup
 #pragma unroll
                 for (int gg = 0; gg < G; ++gg) {
                     const bool mine = (G == 1) || (grp == gg);
@@ -975,7 +1095,10 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
                     }
                 }
             }
-            fft_stages<T, PR, +1, TW_STAGE, G>(v, t, lds, a.tw, a.lt_shift, grp);
+            if constexpr (PRE && SYM)
+                fft_stages<T, PR, +1, TW_STAGE, G, true>(v, t, lds, a.tw, a.lt_shift, grp, &pre);
+            else
+                fft_stages<T, PR, +1, TW_STAGE, G, PRE>(v, t, lds, a.tw, a.lt_shift, grp, &prei);
             if (valid) {
                 constexpr int Rf = PR::last;
 #pragma unroll
@@ -1041,11 +1164,14 @@ __device__ __forceinline__ void last_axis_block(const LastAxisArgs<T> &a, int64_
 }
 
 template <typename T, class PL, int WMAX, int MODE, int OCC = 1, bool PF = true, int ORD = ORD_TILE, bool NT = false,
-          int G = 1>
+          int G = 1, bool LP = false>
 __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void last_axis_kernel(LastAxisArgs<T> a)
 {
-    __shared__ cx<T> sh[PL::L * WMAX / G];
-    last_axis_block<T, PL, WMAX, MODE, PF, ORD, NT, G>(a, blockIdx.x, sh);
+    // narrow step tiles: two folded pencils' state values behind the tile's slots
+    constexpr int fold_slots = (LP && PF && MODE == LA_STEP) ? 2 * PL::L : 0;
+    __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX / G + fold_slots];
+    const int64_t bid = LP && a.nrows == 1 ? xcd_tile_order(blockIdx.x, gridDim.x, a.xg) : blockIdx.x;
+    last_axis_block<T, PL, WMAX, MODE, PF, ORD, NT, G, LP>(a, bid, sh);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1,6 +1,6 @@
-// FP32 instantiation of the PFC kernels and their launchers.
+// FP32: passes over grids and modes.
 #include "dispatch_impl.hpp"
 
 namespace pfc {
-PFC_INSTANTIATE(float)
+PFC_INSTANTIATE_GRID(float)
 }  // namespace pfc

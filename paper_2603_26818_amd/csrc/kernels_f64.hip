@@ -1,8 +1,8 @@
-// FP64 instantiation of the PFC kernels and their launchers.
+// FP64: passes over grids and modes; candidate counts.
 #include "dispatch_impl.hpp"
 
 namespace pfc {
-PFC_INSTANTIATE(double)
+PFC_INSTANTIATE_GRID(double)
 
 __global__ __launch_bounds__(256) void accumulate_kernel(const double *partial, int np, double coef, double *acc)
 {
@@ -19,10 +19,10 @@ int step_candidates(const Geom &g, int pass)
     auto count = [&](auto lc, auto kind) -> hipError_t {
         constexpr int L = decltype(lc)::value;
         constexpr int K = decltype(kind)::value;
-        if constexpr (K == 0) n = XFwdCands<L>::type::size;
+        if constexpr (K == 0) n = (g.ndim == 3) ? XFwdCands<L>::type::size : X2FwdCands<L>::type::size;
         else if constexpr (K == 1) n = AxisCands<L>::type::size;
-        else if constexpr (K == 2) n = (g.ndim == 3) ? ZCands<L>::type::size : LastCands<L>::type::size;
-        else n = XInvCands<L>::type::size;
+        else if constexpr (K == 2) n = (g.ndim == 3) ? ZCands<L>::type::size : Last2Cands<L>::type::size;
+        else n = (g.ndim == 3) ? XInvCands<L>::type::size : X2InvCands<L>::type::size;
         return hipSuccess;
     };
     switch (id) {

@@ -1,0 +1,6 @@
+// F64: fused x pass.
+#include "dispatch_impl.hpp"
+
+namespace pfc {
+PFC_INSTANTIATE_XF(double)
+}  // namespace pfc

@@ -1,0 +1,6 @@
+// F32: y and last-axis transforms.
+#include "dispatch_impl.hpp"
+
+namespace pfc {
+PFC_INSTANTIATE_Y(float)
+}  // namespace pfc
