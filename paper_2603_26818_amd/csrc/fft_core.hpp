@@ -435,6 +435,8 @@ struct Tiled {
 // x forward (r2c, contiguous rows), x inverse (c2r), strided middle axis, last axis
 template <int M> struct XFwdCands { using type = typename AltPlans<M>::type; };
 template <int M> struct XInvCands { using type = typename AltPlans<M>::type; };
+template <> struct XFwdCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
+template <> struct XInvCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
 template <> struct XInvCands<256> { using type = PlanList<Radices<8, 4, 8>, Radices<16, 16>>; };
 // x rows of 375 and 700 points (the x passes of the 750^3 and 1400^3 grids): the radices ragged
 // over 32 or 64 threads, so that every row starts at a half or a whole wavefront, then the lcm or
@@ -504,8 +506,6 @@ static_assert(ZCandsOf<float, 512>::type::size == ZCands<512>::type::size, "one 
 template <int M> struct X2FwdCands { using type = typename XFwdCands<M>::type; };
 template <int M> struct X2InvCands { using type = typename XInvCands<M>::type; };
 template <int L> struct Last2Cands { using type = typename LastCands<L>::type; };
-template <> struct X2FwdCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
-template <> struct X2InvCands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
 template <> struct X2FwdCands<256> { using type = PlanList<Radices<4, 8, 8>, Radices<4, 8, 8>, Radices<16, 16>>; };
 template <> struct Last2Cands<128> { using type = PlanList<Radices<4, 4, 8>, Radices<16, 8>, Radices<8, 16>>; };
 template <> struct Last2Cands<256> { using type = PlanList<Radices<4, 8, 8>, Radices<4, 8, 8>, Radices<16, 16>>; };
