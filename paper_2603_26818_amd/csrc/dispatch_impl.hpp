@@ -290,58 +290,6 @@ hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu,
 }
 
 template <typename T>
-hipError_t launch_x_c2r_mac(const Geom &g, const cx<T> *in, T *out, const T *w, bool add, const cx<T> *tw,
-                            hipStream_t s)
-{
-    if (!layout_ok(g)) return hipErrorInvalidValue;
-    return by_length(g.M, [&](auto Mc) -> hipError_t {
-        constexpr int M = decltype(Mc)::value;
-        if constexpr (M > 1024) {
-            return hipErrorInvalidValue;
-        } else {
-            return with_cands<PlanList<typename X2InvPlan<M>::type>, PlanList<typename XInvPlan<M>::type>>(g, 0, [&](auto plc) -> hipError_t {
-                using PL = decltype(plc);
-                constexpr int ROWS = XInvRows<PL>::value;
-                const dim3 grid((unsigned)cdiv(g.xrows, ROWS)), block(ROWS * PL::Tp);
-                const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-                AdjEpi<T> ea{};
-                ea.w = w;
-                ea.add = add ? 1 : 0;
-                hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_MAC>), grid, block, 0, s, in, out, g.xrows, tw + g.tw_x,
-                                   g.lt_shift, sc, ea, pack_of(g));
-                return hipGetLastError();
-            });
-        }
-    });
-}
-
-template <typename T>
-hipError_t launch_spec_update(const Geom &g, int op, cx<T> *out, const cx<T> *x0, const cx<T> *x1,
-                              const HydroArgs &h, hipStream_t s)
-{
-    if (!layout_ok(g)) return hipErrorInvalidValue;
-    static_assert(HYDRO_PSI == HY_PSI && HYDRO_MU == HY_MU && HYDRO_VEL == HY_VEL, "mode codes");
-    const int64_t n = g.n0 * g.nrows * g.M;
-    const dim3 grid((unsigned)(cdiv(n, 256) < 16384 ? cdiv(n, 256) : 16384)), block(256);
-    switch (op) {
-    case HY_PSI:
-        hipLaunchKernelGGL((spec_update_kernel<T, HY_PSI>), grid, block, 0, s, out, x0, x1, g.n0, g.nrows, g.M, h,
-                           pack_of(g));
-        break;
-    case HY_MU:
-        hipLaunchKernelGGL((spec_update_kernel<T, HY_MU>), grid, block, 0, s, out, x0, x1, g.n0, g.nrows, g.M, h,
-                           pack_of(g));
-        break;
-    case HY_VEL:
-        hipLaunchKernelGGL((spec_update_kernel<T, HY_VEL>), grid, block, 0, s, out, x0, x1, g.n0, g.nrows, g.M, h,
-                           pack_of(g));
-        break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hipStream_t s, int variant)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
@@ -443,41 +391,6 @@ hipError_t launch_last_c2c(const Geom &g, const cx<T> *src, cx<T> *dst, int dir,
                 hipLaunchKernelGGL((axis_c2c_kernel<T, PL, WM, +1>), grid, block, 0, s, src, dst, W, ncols, am, tiles,
                                    tw + g.tw_last, g.lt_shift, 1);
             return hipGetLastError();
-        }
-    });
-}
-
-template <typename T>
-hipError_t launch_last_c2c_deriv(const Geom &g, const cx<T> *src, cx<T> *dst, int role, double fk, const cx<T> *tw,
-                                 hipStream_t s)
-{
-    if (!layout_ok(g)) return hipErrorInvalidValue;
-    return by_length(g.n0, [&](auto Lc) -> hipError_t {
-        constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
-            return hipErrorInvalidValue;
-        } else {
-            constexpr int WM = WMax<T, L>::value;
-            const int64_t ncols = g.nrows * g.M;
-            const int W = (int)(ncols < WM ? ncols : WM);
-            const int64_t tiles = cdiv(ncols, W);
-            const DerivArgs da{role, fk, g.nrows, g.M};
-            auto run = [&](auto plc, auto wc, auto lpc, int w, int xg) -> hipError_t {
-                using PL = decltype(plc);
-                constexpr int WT = decltype(wc)::value;
-                if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
-                hipLaunchKernelGGL((axis_c2c_deriv_kernel<T, PL, WT, decltype(lpc)::value>), dim3((unsigned)cdiv(ncols, w)),
-                                   dim3(WT * PL::Tp), 0, s, src, dst, w, ncols, last_map(g), tw + g.tw_last, g.lt_shift, da, xg);
-                return hipGetLastError();
-            };
-            auto narrow = [&](auto plc) -> hipError_t {
-                constexpr int WN = NarrowTile<decltype(plc)>::W;
-                const int w = (int)(ncols < WN ? ncols : WN);
-                return run(plc, std::integral_constant<int, WN>{}, std::true_type{}, w, line_group<T>(w));
-            };
-            using PL = typename AxisPlan<L>::type;
-            if (tiles < kFillTiles1) return g.ndim == 2 ? narrow(typename Last2Plan<L>::type{}) : narrow(PL{});
-            return run(PL{}, std::integral_constant<int, WM>{}, std::false_type{}, W, 1);
         }
     });
 }
@@ -656,25 +569,19 @@ hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStrea
     template hipError_t launch_x_r2c<T>(const Geom &, const T *, cx<T> *, bool, const cx<T> *, hipStream_t, int);     \
     template hipError_t launch_x_c2r<T>(const Geom &, const cx<T> *, T *, const cx<T> *, hipStream_t, int);           \
     template hipError_t launch_x_c2r_adjoint<T>(const Geom &, const cx<T> *, const cx<T> *, const T *, const T *, T *, \
-                                                T, double *, int64_t *, const cx<T> *, hipStream_t);                  \
-    template hipError_t launch_x_c2r_mac<T>(const Geom &, const cx<T> *, T *, const T *, bool, const cx<T> *,         \
-                                            hipStream_t);
+                                                T, double *, int64_t *, const cx<T> *, hipStream_t);
 #define PFC_INSTANTIATE_XF(T)                                                                                         \
     template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, const cx<T> *, hipStream_t);                       \
     template bool x_fused_ok<T>(const Geom &);
 #define PFC_INSTANTIATE_Y(T)                                                                                          \
     template hipError_t launch_y_c2c<T>(const Geom &, cx<T> *, int, const cx<T> *, hipStream_t, int);                 \
     template hipError_t launch_last_fwd<T>(const Geom &, const cx<T> *, cx<T> *, const cx<T> *, hipStream_t);         \
-    template hipError_t launch_last_c2c<T>(const Geom &, const cx<T> *, cx<T> *, int, const cx<T> *, hipStream_t);    \
-    template hipError_t launch_last_c2c_deriv<T>(const Geom &, const cx<T> *, cx<T> *, int, double, const cx<T> *,    \
-                                                 hipStream_t);
+    template hipError_t launch_last_c2c<T>(const Geom &, const cx<T> *, cx<T> *, int, const cx<T> *, hipStream_t);
 #define PFC_INSTANTIATE_LAST(T)                                                                                       \
     template bool z_blocks_ok<T>(const Geom &, int);                                                                  \
     template hipError_t launch_last<T>(const Geom &, int, const cx<T> *, cx<T> *, cx<T> *, cx<T> *,                   \
                                        const ModelParams<T> &, const cx<T> *, hipStream_t, int);
 #define PFC_INSTANTIATE_GRID(T)                                                                                       \
-    template hipError_t launch_spec_update<T>(const Geom &, int, cx<T> *, const cx<T> *, const cx<T> *,               \
-                                              const HydroArgs &, hipStream_t);                                        \
     template hipError_t launch_set_mass<T>(const T *, int64_t, double *, cx<T> *, hipStream_t);                       \
     template hipError_t launch_energy<T>(const Geom &, const T *, const cx<T> *, const double *, double, double,      \
                                          double, int, double, double *, double *, hipStream_t);                       \

@@ -69,6 +69,13 @@ __device__ __forceinline__ void st_grid(cx<T> *p, cx<T> a)
     }
 }
 
+// i k z in FP64, rounded once: a spectral derivative
+template <typename T>
+__device__ __forceinline__ cx<T> mul_ik(cx<T> z, double k)
+{
+    return {(T)(-k * (double)z.y), (T)(k * (double)z.x)};
+}
+
 __device__ __forceinline__ int signed_index(int64_t i, int64_t n) { return (int)(i <= n / 2 ? i : i - n); }
 
 // (-e) mod L for 0 <= e < L
@@ -260,8 +267,7 @@ __global__ __launch_bounds__(ROWS *PL::Tp) void x_r2c_kernel(const T *__restrict
 // the real row r) and stores
 //   out = mu - c3 * psi_n^2 * nu,   and writes the block's FP64 sum of nu * psi_np1 to partial[].
 // `in2` and `out` may be the same buffer: each block reads its rows completely before writing them.
-// EPI_MAC (hydrodynamic step) stores out = w * x (+ out when `add`), w a real field.
-enum { EPI_PLAIN = 0, EPI_ADJOINT = 1, EPI_MAC = 2 };
+enum { EPI_PLAIN = 0, EPI_ADJOINT = 1 };
 
 template <typename T>
 struct AdjEpi {
@@ -270,17 +276,17 @@ struct AdjEpi {
     const T *psi_np1;
     T c3;
     double *partial;
-    const T *w;  // EPI_MAC
-    int add;     // EPI_MAC
 };
 
 // Pre-combination of one row for the c2r: own elements X(k) from `src` (column k at src[pk.col(k)]);
 // the mirror X(M-k) either through LDS (PG = false) or straight from `src` (PG = true: a second,
 // reversed but coalesced load of the same cache lines, without the LDS round trip and its barrier).
-template <typename T, class PL, int ROWS, bool PAD, bool PG = false, bool NT = false, bool PRE = false>
+// DX: X(k) is replaced by i (k fkx) X(k), the spectral x derivative (0 for the planes k = 0 and k = M
+// of slot 0), computed in FP64 and rounded once, unless fkx is 0.
+template <typename T, class PL, int ROWS, bool PAD, bool PG = false, bool NT = false, bool PRE = false, bool DX = false>
 __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid, int t, cx<T> *rowlds,
                                           const cx<T> *__restrict__ tw, int lt_shift, const Pack &pk,
-                                          const XTw<T, PL> *pre = nullptr)
+                                          const XTw<T, PL> *pre = nullptr, double fkx = 0.0)
 {
     constexpr int M = PL::L, Tp = PL::Tp, R0 = PL::first, Rmax = PL::Rmax;
     cx<T> mir[PG ? Rmax : 1];
@@ -303,6 +309,8 @@ __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid
             for (int r = 0; r < R0; ++r) {
                 const int k = t + b * Tp + r * (M / R0);
                 v[b * R0 + r] = valid ? ld_grid<NT>(&src[pk.col(k)]) : cx<T>{T(0), T(0)};
+                if constexpr (DX)
+                    if (fkx != 0.0) v[b * R0 + r] = mul_ik(v[b * R0 + r], fkx * (double)k);
                 rowlds[xidx<T, M, PAD>(k)] = v[b * R0 + r];
             }
         __syncthreads();
@@ -332,9 +340,9 @@ __device__ __forceinline__ void x_c2r_row(cx<T> *v, const cx<T> *src, bool valid
 }
 
 // TO_LDS (EPI_PLAIN): the scaled reals of row p are left in sh[p LD] (LD the row pitch, as packed
-// pairs, contiguous) instead of being stored to `out`.
+// pairs, contiguous) instead of being stored to `out` (STORE: as well as).
 template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = false, bool NT = false,
-          bool TO_LDS = false, bool PRE = false>
+          bool TO_LDS = false, bool PRE = false, bool STORE = false>
 __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nrows, const cx<T> *__restrict__ tw,
                                             int lt_shift, T sc, const AdjEpi<T> &ea, int64_t bid, cx<T> *sh,
                                             const Pack &pk, const int tid = (int)threadIdx.x,
@@ -353,28 +361,18 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
     x_c2r_row<T, PL, ROWS, PAD, PG, NT, PRE>(v, in + ibase, valid, t, &sh[p * LD], tw, lt_shift, pk, pre);
     fft_stages<T, PL, +1, TW_STAGE, 1, PRE>(v, t, lds, tw, lt_shift, 0, PRE ? &pre->st : nullptr);
     cx<T> *dst = reinterpret_cast<cx<T> *>(out) + r0 * M;
-    if constexpr (EPI == EPI_MAC) {
-        if (valid) {
-            const cx<T> *wr = reinterpret_cast<const cx<T> *>(ea.w) + r0 * M;
-#pragma unroll
-            for (int b = 0; b < PL::nb(Rl); ++b)
-                if (PL::jok(t + b * Tp, Rl))
-#pragma unroll
-                    for (int r = 0; r < Rl; ++r) {
-                        const int m = t + b * Tp + r * (M / Rl);
-                        const cx<T> x = scale(v[b * Rl + r], sc), w = wr[m];
-                        cx<T> o = {w.x * x.x, w.y * x.y};
-                        if (ea.add) o = o + dst[m];
-                        dst[m] = o;
-                    }
-        }
-    } else if constexpr (EPI == EPI_PLAIN && TO_LDS) {
+    if constexpr (EPI == EPI_PLAIN && TO_LDS) {
         __syncthreads();  // every thread of the row is past its last exchange read
 #pragma unroll
         for (int b = 0; b < PL::nb(Rl); ++b)
             if (PL::jok(t + b * Tp, Rl))
 #pragma unroll
-            for (int r = 0; r < Rl; ++r) sh[p * LD + t + b * Tp + r * (M / Rl)] = scale(v[b * Rl + r], sc);
+            for (int r = 0; r < Rl; ++r) {
+                const cx<T> x = scale(v[b * Rl + r], sc);
+                sh[p * LD + t + b * Tp + r * (M / Rl)] = x;
+                if constexpr (STORE)
+                    if (valid) st_grid<NT>(&dst[t + b * Tp + r * (M / Rl)], x);
+            }
     } else if constexpr (EPI == EPI_PLAIN) {
         if (valid) {
 #pragma unroll
@@ -447,11 +445,12 @@ struct XFused {
 };
 // One block of R rows (block index `bid`) of packed spectra in the layout `pk`; `sh` holds
 // R XPitch<T, M, PAD> LDS slots; NTH threads.  In place (in == out) is safe: the block reads all its
-// rows before it writes.
-template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false, bool LAT = false>
+// rows before it writes.  STORE: the field in between is also stored, to `real`.
+template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false, bool LAT = false, bool STORE = false>
 __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int64_t nrows,
                                                 const cx<T> *__restrict__ tw, int lt_shift, T sc, int64_t bid,
-                                                cx<T> *sh, const Pack &pk, const int tid = (int)threadIdx.x)
+                                                cx<T> *sh, const Pack &pk, const int tid = (int)threadIdx.x,
+                                                T *real = nullptr)
 {
     using F = XFused<PLI, PLF, NTH>;
     static_assert(F::ok && PLI::L == PLF::L, "schedules must share the workgroup");
@@ -466,7 +465,7 @@ __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int
     }
 #pragma unroll
     for (int s = 0; s < F::R / F::RI; ++s)
-        x_c2r_block<T, PLI, F::RI, EPI_PLAIN, PAD, false, NT, true, PRE>(in, nullptr, nrows, tw, lt_shift, sc, ea,
+        x_c2r_block<T, PLI, F::RI, EPI_PLAIN, PAD, false, NT, true, PRE, STORE>(in, real, nrows, tw, lt_shift, sc, ea,
                                                                          bid * (F::R / F::RI) + s, sh + s * F::RI * LD,
                                                                          pk, tid, &prei);
     __syncthreads();  // all staged rows written
@@ -578,17 +577,6 @@ __device__ __forceinline__ int64_t xcd_tile_order(int64_t b, int64_t n, int G)
     return (grp * 8 + (w & 7)) * G + (w >> 3);
 }
 
-// Spectral first derivative applied on load by the strided FFT (DERIV): multiplies element e of
-// pencil column col = row * M + kx by i k, k along `role` (0: this axis, index e of length L; 1: the
-// rows; 2: x), with k = 0 at a Nyquist index (a first derivative of a real field has no real Nyquist
-// component), computed in FP64 and rounded once.  On the folded column kx = 0 of the packed layout
-// the multiplier is the same for both planes (0 for x), so it applies to X0 + i XN as stored.
-struct DerivArgs {
-    int role;
-    double fk;
-    int64_t nrows, M;
-};
-
 // ------------------------------------------------------------------------------------------------
 // Strided complex FFT along one axis, out of place or in place (src == dst).
 // Pencil (batch, col), col < ncols, has element e = t + k at am.base(batch, col) + am.elem(t) +
@@ -596,10 +584,10 @@ struct DerivArgs {
 // the launcher checks).  A workgroup handles W adjacent columns (W <= WMAX); its threads are laid out
 // column-fastest so each load/store instruction moves W * sizeof(cx) contiguous bytes per element
 // row (within one 128-byte column chunk).  `bid` is the logical tile index (see xcd_tile_order).
-template <typename T, class PL, int WMAX, int DIR, bool NT = false, int G = 1, bool DERIV = false, bool LP = false>
+template <typename T, class PL, int WMAX, int DIR, bool NT = false, int G = 1, bool LP = false>
 __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int W, int64_t ncols, const AxisMap &am,
                                                int64_t tiles_per_batch, const cx<T> *__restrict__ tw, int lt_shift,
-                                               int64_t bid, cx<T> *sh, const DerivArgs &da = DerivArgs{},
+                                               int64_t bid, cx<T> *sh,
                                                const int tid = (int)threadIdx.x)
 {
     constexpr int L = PL::L, Tp = PL::Tp, R0 = PL::first, Rl = PL::last, Rmax = PL::Rmax;
@@ -619,25 +607,6 @@ __device__ __forceinline__ void axis_c2c_block(const cx<T> *src, cx<T> *dst, int
         for (int r = 0; r < R0; ++r)
             v[b * R0 + r] = valid ? ld_grid<NT>(&src[base + (int64_t)(b * Tp + r * (L / R0)) * estride])
                                   : cx<T>{T(0), T(0)};
-    if constexpr (DERIV) {
-        const int64_t crow = valid ? col / da.M : 0, ckx = valid ? col - crow * da.M : 0;
-#pragma unroll
-        for (int b = 0; b < PL::nb(R0); ++b)
-            if (PL::jok(t + b * Tp, R0))
-#pragma unroll
-            for (int r = 0; r < R0; ++r) {
-                const int e = t + b * Tp + r * (L / R0);
-                double k;
-                if (da.role == 0)
-                    k = (2 * e == L) ? 0.0 : da.fk * signed_index(e, L);
-                else if (da.role == 1)
-                    k = (2 * crow == da.nrows) ? 0.0 : da.fk * signed_index(crow, da.nrows);
-                else
-                    k = da.fk * (double)ckx;
-                const cx<T> z = v[b * R0 + r];
-                v[b * R0 + r] = {(T)(-k * (double)z.y), (T)(k * (double)z.x)};
-            }
-    }
     constexpr int GW = WMAX / G;  // pencils per LDS group (see fft_stages)
     auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * GW + p % GW]; };
     if constexpr (PRE) load_stage_tw<T, PL, TW_STAGE>(pre, t, tw, lt_shift);
@@ -668,6 +637,15 @@ __device__ __forceinline__ int64_t plane_xcd_order(int64_t b, int64_t tiles_per_
 // With batch blocks (am.bzs > 0: 2^bzs batches share the rows of one block), the plane order runs
 // over whole blocks, and inside a block over tiles first, then the batches of the block, so that
 // consecutive workgroups of an XCD read neighbouring 128-byte chunks.
+__device__ __forceinline__ int64_t axis_tile(const AxisMap &am, int64_t tiles_per_batch, int xg)
+{
+    if (xg != 0) return xcd_tile_order(blockIdx.x, gridDim.x, xg);
+    const int64_t tb = tiles_per_batch << am.bzs;
+    const int64_t u = plane_xcd_order(blockIdx.x, tb, gridDim.x);
+    const int64_t sb = u / tb, w = u - sb * tb;
+    const int64_t batch = (sb << am.bzs) + (w & ((int64_t(1) << am.bzs) - 1));
+    return batch * tiles_per_batch + (w >> am.bzs);
+}
 template <typename T, class PL, int WMAX, int DIR, int OCC = 1, bool NT = false, int G = 1, bool LP = false>
 __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void axis_c2c_kernel(const cx<T> *src, cx<T> *dst, int W,
                                                                  int64_t ncols, AxisMap am, int64_t tiles_per_batch,
@@ -675,29 +653,8 @@ __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void axis_c2c_kernel(const cx<T>
 {
     static_assert(WMAX % G == 0, "groups of whole pencils");
     __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX / G];
-    int64_t bid;
-    if (xg == 0) {
-        const int64_t tb = tiles_per_batch << am.bzs;
-        const int64_t u = plane_xcd_order(blockIdx.x, tb, gridDim.x);
-        const int64_t sb = u / tb, w = u - sb * tb;
-        const int64_t batch = (sb << am.bzs) + (w & ((int64_t(1) << am.bzs) - 1));
-        bid = batch * tiles_per_batch + (w >> am.bzs);
-    } else {
-        bid = xcd_tile_order(blockIdx.x, gridDim.x, xg);
-    }
-    axis_c2c_block<T, PL, WMAX, DIR, NT, G, false, LP>(src, dst, W, ncols, am, tiles_per_batch, tw, lt_shift, bid, sh);
-}
-
-// Inverse strided FFT of the spectral derivative i k_role of `src` (DerivArgs), out of place.
-template <typename T, class PL, int WMAX, bool LP = false>
-__global__ __launch_bounds__(WMAX *PL::Tp) void axis_c2c_deriv_kernel(const cx<T> *src, cx<T> *dst, int W,
-                                                                   int64_t ncols, AxisMap am,
-                                                                   const cx<T> *__restrict__ tw, int lt_shift,
-                                                                   DerivArgs da, int xg)
-{
-    __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX];
-    axis_c2c_block<T, PL, WMAX, +1, false, 1, true, LP>(src, dst, W, ncols, am, (ncols + W - 1) / W, tw, lt_shift,
-                                                        xcd_tile_order(blockIdx.x, gridDim.x, xg), sh, da);
+    const int64_t bid = axis_tile(am, tiles_per_batch, xg);
+    axis_c2c_block<T, PL, WMAX, DIR, NT, G, LP>(src, dst, W, ncols, am, tiles_per_batch, tw, lt_shift, bid, sh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1172,84 +1129,6 @@ __global__ __launch_bounds__(WMAX *PL::Tp, OCC) void last_axis_kernel(LastAxisAr
     __shared__ cx<T> sh[pencil_slot<LP>(PL::L) * WMAX / G + fold_slots];
     const int64_t bid = LP && a.nrows == 1 ? xcd_tile_order(blockIdx.x, gridDim.x, a.xg) : blockIdx.x;
     last_axis_block<T, PL, WMAX, MODE, PF, ORD, NT, G, LP>(a, bid, sh);
-}
-
-// ------------------------------------------------------------------------------------------------
-// Hydrodynamic PFC: pointwise operations on packed spectra (layout: element (e, row, kx) at
-// (e nrows + row) M + kx; column kx = 0 holds the planes kx = 0 and kx = M as X0 + i XN).
-
-__device__ __forceinline__ double hy_corr(const HydroArgs &h, double q)
-{
-    const double a = (1.0 - q) * (1.0 - q);
-    if (h.model == 0) return a;
-    const double b = h.q1sq - q;
-    return a * (b * b + h.R1);
-}
-
-enum { HY_PSI = 0, HY_MU = 1, HY_VEL = 2 };
-
-// The update of one mode for its q, with real coefficients (so it maps Hermitian planes to
-// Hermitian planes):
-//   HY_PSI: S <- (S - dt q nl N - dt B) / (1 + dt q (r + L(q)))    (out = S, x0 = N, x1 = B)
-//   HY_MU:  A <- nl A + (r + L(q)) S                                 (out = A, x0 = S)
-//   HY_VEL: V <- (V - c G(q) B) / (1 + c Gamma q), G = exp(-a0^2 q/2) (out = V, x0 = B)
-template <int OP>
-__device__ __forceinline__ void hy_mode(const HydroArgs &h, double q, double o[2], const double a[2], const double b[2])
-{
-    if constexpr (OP == HY_PSI) {
-        const double den = 1.0 + h.dt * q * (h.r + hy_corr(h, q)), f = -h.dt * q * h.nl;
-        for (int c = 0; c < 2; ++c) o[c] = (o[c] + f * a[c] - h.dt * b[c]) / den;
-    } else if constexpr (OP == HY_MU) {
-        const double m = h.r + hy_corr(h, q);
-        for (int c = 0; c < 2; ++c) o[c] = h.nl * o[c] + m * a[c];
-    } else {
-        const double g = h.c * exp(-0.5 * h.a0 * h.a0 * q), den = 1.0 + h.c * h.gamma * q;
-        for (int c = 0; c < 2; ++c) o[c] = (o[c] - g * a[c]) / den;
-    }
-}
-
-// Applies hy_mode to every mode of a packed spectrum, in place on `out`.  On the folded column a
-// thread takes the pair (k, -k): it separates X0 and XN of every operand with the mirror element,
-// updates each plane with its own q (q0 or q0 + kx_Nyquist^2) and writes both elements.
-template <typename T, int OP>
-__global__ __launch_bounds__(256) void spec_update_kernel(cx<T> *out, const cx<T> *__restrict__ x0,
-                                                          const cx<T> *__restrict__ x1, int64_t L, int64_t nrows,
-                                                          int64_t M, HydroArgs h, Pack pk)
-{
-    const int64_t n = L * nrows * M;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t kx = i % M, rest = i / M, row = rest % nrows, e = rest / nrows;
-        const int64_t j = pk.at(e, row, kx);  // i: logical index, j: its place in memory
-        const double kz = h.fk[0] * signed_index(e, L), ky = h.fk[1] * signed_index(row, nrows);
-        const cx<T> zx1 = x1 ? x1[j] : cx<T>{T(0), T(0)};
-        if (kx != 0) {
-            const double kk = h.fk[2] * (double)kx, q = kz * kz + ky * ky + kk * kk;
-            double o[2] = {(double)out[j].x, (double)out[j].y}, a[2] = {(double)x0[j].x, (double)x0[j].y},
-                   b[2] = {(double)zx1.x, (double)zx1.y};
-            hy_mode<OP>(h, q, o, a, b);
-            out[j] = {(T)o[0], (T)o[1]};
-            continue;
-        }
-        const int64_t em = (L - e) % L, rm = (nrows - row) % nrows;
-        const int64_t im = (em * nrows + rm) * M;
-        if (im < i) continue;  // the pair is updated by the thread of its lower (logical) index
-        const int64_t jm = pk.at(em, rm, 0);
-        const cx<T> mx1 = x1 ? x1[jm] : cx<T>{T(0), T(0)};
-        const cx<T> Z[3] = {out[j], x0[j], zx1}, Zm[3] = {out[jm], x0[jm], mx1};
-        double p0[3][2], pn[3][2];  // X0 and XN of each operand at k
-        for (int j = 0; j < 3; ++j) {
-            p0[j][0] = 0.5 * ((double)Z[j].x + (double)Zm[j].x);
-            p0[j][1] = 0.5 * ((double)Z[j].y - (double)Zm[j].y);
-            pn[j][0] = 0.5 * ((double)Z[j].y + (double)Zm[j].y);
-            pn[j][1] = 0.5 * ((double)Zm[j].x - (double)Z[j].x);
-        }
-        const double kn = h.fk[2] * (double)M, q0 = kz * kz + ky * ky, qn = q0 + kn * kn;
-        hy_mode<OP>(h, q0, p0[0], p0[1], p0[2]);
-        hy_mode<OP>(h, qn, pn[0], pn[1], pn[2]);
-        // Y = Y0 + i YN at k; at -k the planes are conjugated: conj Y0 + i conj YN
-        out[j] = {(T)(p0[0][0] - pn[0][1]), (T)(p0[0][1] + pn[0][0])};
-        if (im != i) out[jm] = {(T)(p0[0][0] + pn[0][1]), (T)(pn[0][0] - p0[0][1])};
-    }
 }
 
 // ------------------------------------------------------------------------------------------------

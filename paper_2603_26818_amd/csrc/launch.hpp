@@ -90,24 +90,33 @@ hipError_t launch_last_fwd(const Geom &g, const cx<T> *src, cx<T> *dst, const cx
 template <typename T>
 hipError_t launch_last_c2c(const Geom &g, const cx<T> *src, cx<T> *dst, int dir, const cx<T> *tw, hipStream_t s);
 
-// last-axis inverse FFT of the spectral derivative i k of src along a grid role (0 last axis,
-// 1 rows, 2 x; wavenumber step fk; k = 0 at a Nyquist index), out of place
+// Hydrodynamic passes (hydro.hpp).
+// Last-axis pass of an operation: HYDRO_DERIV o0 = inv(s), o1 = inv(i k_last s); HYDRO_MU the same of
+// mu = nl fwd(a) + (r + L) s; HYDRO_PSI updates s with fwd(a) = FFT(psi^3) and fwd(b) = FFT(v . grad psi),
+// o0 = inv(s); HYDRO_VEL updates s with fwd(a) = FFT(psi grad_j mu), o0 = inv(s).  o0 may be a or b.
+enum HydroOp { HYDRO_DERIV = 0, HYDRO_MU = 1, HYDRO_PSI = 2, HYDRO_VEL = 3 };
 template <typename T>
-hipError_t launch_last_c2c_deriv(const Geom &g, const cx<T> *src, cx<T> *dst, int role, double fk, const cx<T> *tw,
-                                 hipStream_t s);
-
-// x_c2r with the hydrodynamic epilogue: out = w * x (+ out when add), w a real field
+hipError_t launch_hydro_last(const Geom &g, int op, const cx<T> *a, const cx<T> *b, cx<T> *s, cx<T> *o0, cx<T> *o1,
+                             const HydroArgs &h, const cx<T> *tw, hipStream_t s_);
+// 3D middle axis, inverse: dk = inv(i k_y data), then data = inv(data) in place
 template <typename T>
-hipError_t launch_x_c2r_mac(const Geom &g, const cx<T> *in, T *out, const T *w, bool add, const cx<T> *tw,
-                            hipStream_t s);
-
-// hydrodynamic spectral updates (kernels.hpp), in place: HY_PSI / HY_MU / HY_VEL
+hipError_t launch_hydro_y(const Geom &g, cx<T> *data, cx<T> *dk, double fk, const cx<T> *tw, hipStream_t s);
+// x pass: field_j = x c2r of spec[j] (for the last component, x, of i k_x spec[j]); with `out`, out = x
+// r2c of sum_j w[j] field_j (may be a spec); without, spec[j] = x r2c of w[0] field_j
 template <typename T>
-hipError_t launch_spec_update(const Geom &g, int op, cx<T> *out, const cx<T> *x0, const cx<T> *x1,
-                              const HydroArgs &h, hipStream_t s);
+struct HydroFlow {
+    cx<T> *spec[3];
+    const T *w[3];
+    cx<T> *out;
+    double fkx;
+};
+template <typename T>
+hipError_t launch_hydro_x(const Geom &g, const HydroFlow<T> &f, const cx<T> *tw, hipStream_t s);
+// x pass of the new density: real = x c2r of in, out = x r2c of real^3 (out may be in)
+template <typename T>
+hipError_t launch_hydro_psi_x(const Geom &g, const cx<T> *in, T *real, cx<T> *out, const cx<T> *tw, hipStream_t s);
 
 enum LastMode { LAST_STEP = 0, LAST_R2C_NATURAL = 1, LAST_C2R_NATURAL = 2, LAST_ADJOINT = 3 };
-enum HydroOp { HYDRO_PSI = 0, HYDRO_MU = 1, HYDRO_VEL = 2 };  // the spec_update_kernel modes
 
 template <typename T>
 hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx<T> *dst2, cx<T> *state,

@@ -639,9 +639,12 @@ pfc_status do_hydro_state_init(pfc_plan *p, const void *psi, void *psi_state, co
     return st;
 }
 
-// One step after another as stated with pfc_hydro_step in pfc.h, composed of the transform passes
-// (x r2c, y, last axis, x c2r) and the pointwise spectral kernels.  Buffers: A, B packed spectra
-// and a, h real fields in `work`; the plan's own scratch is not used.
+// One step after another as stated with pfc_hydro_step in pfc.h, on the merged passes of hydro.hpp.
+// Buffers in `work`, which holds two spectra and two real fields (the plan's own scratch is not used):
+// where a spectrum fits a real field's bytes (rows without padding) four spectra, of which one keeps the
+// transform of psi^3, not yet transformed along the last axis, from the density's x pass through mu to
+// the next density update; otherwise three (the two fields' bytes are one), and the cube is transformed
+// again.
 template <typename T>
 pfc_status do_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi_v, void *S_v, void *v_v, void *V_v,
                          void *work, int64_t nsteps, hipStream_t s)
@@ -652,7 +655,10 @@ pfc_status do_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi_v, v
     const size_t sb = state_bytes(p), rb = real_bytes(p);
     char *w = (char *)work;
     cx<T> *A = (cx<T> *)w, *B = (cx<T> *)(w + align256(sb));
-    T *a = (T *)(w + 2 * align256(sb)), *h = (T *)(w + 2 * align256(sb) + align256(rb));
+    cx<T> *C = (cx<T> *)(w + 2 * align256(sb)), *D = (cx<T> *)(w + 2 * align256(sb) + align256(rb));
+    const bool keep = sb <= rb;
+    // X0: the plain inverse, later per-component spectra; X1: last axis; X2: rows (3D)
+    cx<T> *X0 = keep ? B : A, *X1 = keep ? C : B, *X2 = keep ? D : C;
     T *psi = (T *)psi_v;
     cx<T> *S = (cx<T> *)S_v;
     auto vj = [&](int j) { return (T *)((char *)v_v + j * rb); };
@@ -668,34 +674,23 @@ pfc_status do_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi_v, v
     ha.c = p->d.dt / hp->rho0;
     ha.gamma = hp->gamma;
     ha.a0 = hp->a0;
-    // grid axis j -> (role of the spectral index, its wavenumber step)
-    auto role = [&](int j) { return d == 3 ? j : (j == 0 ? 0 : 2); };
-    auto fwd = [&](const T *real, bool cube, cx<T> *out) -> pfc_status {
-        pfc_status st = fwd_xy<T>(p, real, cube, out, s);
-        if (st) return st;
-        PFC_TRY(pfc::launch_last_c2c<T>(g, out, out, -1, b.tw, s), "last-axis forward launch");
+    // component j (grid axis j): its spectrum, and the x component
+    auto Xj = [&](int j) { return j == 0 ? X1 : (j == d - 1 ? X0 : X2); };
+    pfc::HydroFlow<T> flow{};
+    for (int j = 0; j < d; ++j) flow.spec[j] = Xj(j);
+    flow.fkx = p->fk[2];
+    auto y = [&](cx<T> *x, int dir) -> pfc_status {
+        if (d == 3) PFC_TRY(pfc::launch_y_c2c<T>(g, x, dir, b.tw, s), "y launch");
         return PFC_OK;
     };
-    // inverse of spectrum `spec` through B into the real field `out`: plain, or out = w x (+ out)
-    auto inv = [&](const cx<T> *spec, T *out, const T *wf, bool add) -> pfc_status {
-        PFC_TRY(pfc::launch_last_c2c<T>(g, spec, B, +1, b.tw, s), "last-axis inverse launch");
-        if (d == 3) PFC_TRY(pfc::launch_y_c2c<T>(g, B, +1, b.tw, s), "y inverse launch");
-        if (wf)
-            PFC_TRY(pfc::launch_x_c2r_mac<T>(g, B, out, wf, add, b.tw, s), "x_c2r launch");
-        else
-            PFC_TRY(pfc::launch_x_c2r<T>(g, B, out, b.tw, s), "x_c2r launch");
+    auto last = [&](int op, const cx<T> *a, const cx<T> *a2, cx<T> *st, cx<T> *o0, cx<T> *o1) -> pfc_status {
+        PFC_TRY(pfc::launch_hydro_last<T>(g, op, a, a2, st, o0, o1, ha, b.tw, s), "hydro last-axis launch");
         return PFC_OK;
     };
-    // the same for the spectral derivative i k_j of `spec`, applied as the last-axis pass loads it
-    auto inv_deriv = [&](const cx<T> *spec, int j, T *out, const T *wf, bool add) -> pfc_status {
-        PFC_TRY(pfc::launch_last_c2c_deriv<T>(g, spec, B, role(j), p->fk[role(j)], b.tw, s),
-                "last-axis derivative inverse launch");
-        if (d == 3) PFC_TRY(pfc::launch_y_c2c<T>(g, B, +1, b.tw, s), "y inverse launch");
-        if (wf)
-            PFC_TRY(pfc::launch_x_c2r_mac<T>(g, B, out, wf, add, b.tw, s), "x_c2r launch");
-        else
-            PFC_TRY(pfc::launch_x_c2r<T>(g, B, out, b.tw, s), "x_c2r launch");
-        return PFC_OK;
+    // y inverses of the gradient's parts: X0 plain and along the rows, X1
+    auto grad_y = [&]() -> pfc_status {
+        if (d == 3) PFC_TRY(pfc::launch_hydro_y<T>(g, X0, X2, p->fk[1], b.tw, s), "hydro y launch");
+        return y(X1, +1);
     };
     pfc_status st = PFC_OK;
 #define PFC_HY(call)        \
@@ -703,22 +698,35 @@ pfc_status do_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi_v, v
         st = (call);        \
         if (st) return st;  \
     } while (0)
+    const cx<T> *N = nullptr;  // FFT of psi^3 but for the last axis
     for (int64_t n = 0; n < nsteps; ++n) {
-        // density: A = FFT(psi^3), a = sum_j v_j IFFT(D_j S), B = FFT(a), S update, psi = IFFT(S)
-        PFC_HY(fwd(psi, true, A));
-        for (int j = 0; j < d; ++j) PFC_HY(inv_deriv(S, j, a, vj(j), j > 0));
-        PFC_HY(fwd(a, false, B));
-        PFC_TRY(pfc::launch_spec_update<T>(g, pfc::HYDRO_PSI, S, A, B, ha, s), "density update launch");
-        PFC_HY(inv(S, psi, nullptr, false));
-        // velocity: A = mu = FFT(psi^3) + (r + L) S; per component h = psi IFFT(D_j mu), B = FFT(h)
-        PFC_HY(fwd(psi, true, A));
-        PFC_TRY(pfc::launch_spec_update<T>(g, pfc::HYDRO_MU, A, S, (const cx<T> *)nullptr, ha, s), "mu launch");
+        // density: X0 = FFT but for the last axis of sum_j v_j IFFT(i k_j S); S and psi
+        PFC_HY(last(pfc::HYDRO_DERIV, nullptr, nullptr, S, X0, X1));
+        PFC_HY(grad_y());
+        for (int j = 0; j < d; ++j) flow.w[j] = vj(j);
+        flow.out = X0;
+        PFC_TRY(pfc::launch_hydro_x<T>(g, flow, b.tw, s), "hydro x launch");
+        PFC_HY(y(X0, -1));
+        if (!N || !keep) {
+            cx<T> *c = keep ? A : X1;
+            PFC_HY(fwd_xy<T>(p, psi, true, c, s));
+            N = c;
+        }
+        PFC_HY(last(pfc::HYDRO_PSI, N, X0, S, X0, nullptr));
+        PFC_HY(y(X0, +1));
+        PFC_TRY(pfc::launch_hydro_psi_x<T>(g, X0, psi, A, b.tw, s), "hydro density x launch");
+        PFC_HY(y(A, -1));
+        N = A;
+        // velocity: mu = FFT(psi^3) + (r + L) S; component j from psi IFFT(i k_j mu)
+        PFC_HY(last(pfc::HYDRO_MU, A, nullptr, S, X0, X1));
+        PFC_HY(grad_y());
+        flow.w[0] = psi;
+        flow.out = nullptr;
+        PFC_TRY(pfc::launch_hydro_x<T>(g, flow, b.tw, s), "hydro x launch");
         for (int j = 0; j < d; ++j) {
-            PFC_HY(inv_deriv(A, j, h, psi, false));
-            PFC_HY(fwd(h, false, B));
-            PFC_TRY(pfc::launch_spec_update<T>(g, pfc::HYDRO_VEL, Vj(j), B, (const cx<T> *)nullptr, ha, s),
-                    "velocity update launch");
-            PFC_HY(inv(Vj(j), vj(j), nullptr, false));
+            PFC_HY(y(Xj(j), -1));
+            PFC_HY(last(pfc::HYDRO_VEL, Xj(j), nullptr, Vj(j), Xj(j), nullptr));
+            PFC_HY(inv_yx<T>(p, Xj(j), vj(j), s));
         }
     }
 #undef PFC_HY
