@@ -261,13 +261,13 @@ pfc_status pfc_hydro_state_init(pfc_plan *p, const void *psi, void *psi_state, c
 pfc_status pfc_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi, void *psi_state, void *v,
                           void *v_state, void *work, size_t work_bytes, int64_t nsteps, void *stream);
 
-/* ---- Batched form: many independent 2D runs of mixed sizes in one persistent launch ----------
+/* ---- Batched form: many independent 2D runs of mixed sizes advanced together ------------------
  * Each instance is a 2D grid n0 x n1 (each a power of two in [32, 1024]) with its own model, r and
- * dt; all instances share the dtype and device.  pfc_batch_step advances every instance by nsteps
- * steps with ONE launch of a persistent kernel (replayed from a HIP graph captured on first use for
- * that nsteps): a step is three passes (x r2c with cube, y forward + update + y inverse, x c2r), each a
- * list of work items over all instances, separated by grid barriers.  The barrier wait is bounded:
- * if the workgroups cannot all be resident the launch ends early and pfc_batch_check reports it. */
+ * dt; all instances share the dtype and device.  A step is three passes (x r2c with cube, y forward +
+ * update + y inverse, x c2r; between two steps of one call the two x passes are one); instances of one
+ * shape and one choice of schedules share each pass's launch.  Where it pays, part of the groups runs
+ * on a stream of the batch's own, which starts after the caller's earlier work and which the caller's
+ * stream waits for before pfc_batch_step's end on it. */
 typedef struct pfc_batch pfc_batch;
 
 /* Validate `count` (1..256) 2D descriptors and create a batch (host memory only).  Source: each
@@ -276,13 +276,13 @@ typedef struct pfc_batch pfc_batch;
  * library does no file I/O. */
 pfc_status pfc_batch_create(pfc_batch **out, const pfc_plan_desc *descs, int count);
 
-/* Device workspace bytes: twiddle table, instance table, barrier state, one packed spectrum per
+/* Device workspace bytes: twiddle table, instance table, reduction partials, one packed spectrum per
  * instance.  Source: the transforms of Listing 1, per instance (their scratch). */
 size_t pfc_batch_workspace_bytes(const pfc_batch *b);
 
 /* Bind the caller's fields: psi[i] (real, n0*n1) and state[i] (native spectrum, n0*n1/2 complex)
  * for instance i, and the workspace (>= 256-byte aligned).  Uploads the instance table and
- * twiddles and clears the barrier state (synchronous).  Drops graphs captured for earlier bindings.
+ * twiddles (synchronous).
  * Source: the fields psi and spectra of Listing 1, per instance. */
 pfc_status pfc_batch_bind(pfc_batch *b, void *const *psi, void *const *state, void *workspace, size_t bytes);
 
@@ -290,19 +290,17 @@ pfc_status pfc_batch_bind(pfc_batch *b, void *const *psi, void *const *state, vo
  * transform Listing 1 starts from, per instance. */
 pfc_status pfc_batch_state_init(pfc_batch *b, void *stream);
 
-/* Advance every instance by nsteps >= 0 steps: one graph launch of the persistent kernel.
+/* Advance every instance by nsteps >= 0 steps.
  * Source: the step of Listing 1 (Eq. (4)), per instance. */
 pfc_status pfc_batch_step(pfc_batch *b, int64_t nsteps, void *stream);
 
-/* Synchronise `stream` and report whether a grid barrier of an earlier pfc_batch_step timed out
- * (PFC_ERR_INTERNAL; the barrier state is then cleared).  Source: none in the paper (error
- * reporting of the persistent launch). */
+/* Synchronise `stream` and report an error of the work on it.  Source: none in the paper (error
+ * reporting). */
 pfc_status pfc_batch_check(pfc_batch *b, void *stream);
 
 /* Autotuner of the batched form: for each pass kind (x forward, y, x inverse) and each distinct
- * length among the instances, times every candidate radix schedule (which also sets the item shape:
- * rows per x item, pencils per y item) by launching the persistent kernel for `steps` steps, and
- * keeps the fastest.  THE BOUND FIELDS ARE ADVANCED by every trial: bind scratch fields to tune, then
+ * length among the instances, times every candidate radix schedule (which also sets the workgroup's shape:
+ * rows per x workgroup, pencils per y workgroup) over `steps` steps, and keeps the fastest.  THE BOUND FIELDS ARE ADVANCED by every trial: bind scratch fields to tune, then
  * copy the choice to the production batch with pfc_batch_get/set_tuning.  *ms_per_step (may be NULL)
  * receives the time per step of the final choice.  Blocks until done.  Source: the transforms of
  * Listing 1, per instance (schedule choice). */
@@ -314,11 +312,11 @@ pfc_status pfc_batch_autotune(pfc_batch *b, void *stream, int steps, double *ms_
 pfc_status pfc_batch_get_tuning(const pfc_batch *b, int *variants, int n);
 pfc_status pfc_batch_set_tuning(pfc_batch *b, const int *variants, int n);
 
-/* Number of persistent workgroups of the batch launch (known after pfc_batch_bind).  Source: none
- * in the paper (launch shape). */
+/* Number of workgroups of a step's y launches, all groups together (known after pfc_batch_bind).
+ * Source: none in the paper (launch shape). */
 int pfc_batch_grid(const pfc_batch *b);
 
-/* Frees the batch's host memory and its captured graphs.  Source: none in the paper (resource
+/* Frees the batch's host memory, its stream and its events.  Source: none in the paper (resource
  * handling). */
 pfc_status pfc_batch_destroy(pfc_batch *b);
 

@@ -448,7 +448,7 @@ class Plan:
 
 
 class Batch:
-    """A pfc_batch: many independent 2D runs advanced together by one persistent launch.
+    """A pfc_batch: many independent 2D runs advanced together, instances of a shape in shared launches.
 
     instances: list of dicts with the Plan keywords (shape, dtype, model, r, dt, dx, q1sq, R1, flags)."""
 

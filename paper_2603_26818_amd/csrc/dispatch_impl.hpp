@@ -426,10 +426,10 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
             using P0 = typename LastPlan<L>::type;
             if (mode != LAST_STEP && !z_steps_ok<P0>(g.zs)) return hipErrorInvalidValue;
             // few tiles: narrow ones (2D grids on the 2D schedules)
-            auto narrow = [&](auto plc, auto modec) -> hipError_t {
+            auto narrow_w = [&](auto plc, auto modec, auto wc) -> hipError_t {
                 using PN = decltype(plc);
                 if (!z_steps_ok<PN>(g.zs)) return hipErrorInvalidValue;
-                constexpr int WN = NarrowTile<PN>::W;
+                constexpr int WN = decltype(wc)::value;
                 LastAxisArgs<T> b = a;
                 b.W = even_width(g.M < WN ? (int)g.M : WN);
                 b.tiles_per_row = (int)cdiv(g.M, b.W);
@@ -438,6 +438,13 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                 hipLaunchKernelGGL((last_axis_kernel<T, PN, WN, decltype(modec)::value, 1, PF, ORD_XCD_ROW, false, 1, true>),
                                    dim3((unsigned)(g.nrows * b.tiles_per_row)), dim3(WN * PN::Tp), 0, s, b);
                 return hipGetLastError();
+            };
+            auto narrow = [&](auto plc, auto modec) -> hipError_t {
+                using NT = NarrowTile<decltype(plc)>;
+                if constexpr (sizeof(T) == 4 && decltype(modec)::value == LA_STEP && NT::W4 > NT::W)
+                    if (g.nrows * (g.M / NT::W4) >= kFillTiles)
+                        return narrow_w(plc, modec, std::integral_constant<int, NT::W4>{});
+                return narrow_w(plc, modec, std::integral_constant<int, NT::W>{});
             };
             const bool few = nblocks < (mode == LAST_ADJOINT ? kFillTiles : kFillTiles1);
             using P2 = typename Last2Plan<L>::type;

@@ -534,6 +534,9 @@ struct PencilTile<float, 2048> {
 template <class PL>
 struct NarrowTile {
     static constexpr int W = 64 / PL::Tp < 2 ? 2 : 64 / PL::Tp;
+    // four pencils where a launch of them still has a workgroup per CU: more of each line per workgroup
+    // (2048^2 FP32: 21.6 against 29.9 us; with fewer workgroups, 1024^2: 13.2 against 12.8)
+    static constexpr int W4 = W < 4 && is_pow2c(PL::L) ? 4 : W;
 };
 // LDS slot of element e: with LP (narrow tiles) one spare slot after every 8.  A pencil's slots are
 // then only a few words wide, and the first stage's writes, R elements apart between neighbouring

@@ -137,17 +137,20 @@ template <typename T>
 hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStream_t s);
 hipError_t launch_accumulate(const double *partial, int np, double coef, double *acc, hipStream_t s);
 
-// batched persistent kernel: kBatchThreads threads per workgroup, `grid` workgroups (all resident)
+// Batched form: a group of `count` instances of one shape and one choice of schedules, at table[first].
+struct BatchGroup {
+    int n0, M, vx, vy, vc, first, count;
+};
+enum { BATCH_X_FWD = 0, BATCH_X_INV = 1, BATCH_X_FUSED = 2 };  // x r2c with the cube, x c2r, both between steps
 template <typename T>
-hipError_t launch_batch(const BatchArgs<T> &a, int grid, hipStream_t s);
+hipError_t launch_batch_x(const BatchGroup &g, int pass, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
+                          hipStream_t s);
+// y forward, update, y inverse; the workgroups of that launch
 template <typename T>
-hipError_t batch_blocks_per_cu(int *blocks);
-constexpr int kBatchThreadsHost = 512;
+hipError_t launch_batch_y(const BatchGroup &g, const BatchInst<T> *table, const cx<T> *tw, int lt_shift, hipStream_t s);
+template <typename T>
+int64_t batch_y_workgroups(const BatchGroup &g);
 constexpr int kBatchMaxInstHost = 256;
-// rows per x-forward / x-inverse item and pencils per y item of the batched kernel for an n0 x 2M
-// instance of dtype FP64 (f64) or FP32 with candidate schedules (vx, vy, vc) (returns false for
-// unsupported lengths/candidates)
-bool batch_tiles(int n0, int M, int vx, int vy, int vc, bool f64, int *x_rows, int *c_rows, int *y_pencils);
 // number of candidates of batched pass `pass` (0 x forward, 1 y, 2 x inverse) for an n0 x 2M instance
 int batch_candidates(int n0, int M, int pass);
 

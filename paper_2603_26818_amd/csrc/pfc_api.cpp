@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstring>
 #include <map>
@@ -46,22 +47,23 @@ struct pfc_batch {
     pfc_dtype dtype = PFC_F32;
     int device = 0;
     std::vector<pfc_plan_desc> descs;  // caller's order
-    std::vector<int> order;            // device table order (largest first) -> caller's index
     struct Inst {
-        int n0, nx, M, x_rows, c_rows, W, tiles, x_items, c_items, f_rows, f_items;
+        int n0, nx, M;
         int vx = 0, vy = 0, vc = 0;  // candidate schedules (autotuner)
     };
     std::vector<Inst> inst;  // caller's order
     int lt_shift = 0;
-    int x_total = 0, y_total = 0, c_total = 0, f_total = 0;
-    size_t ctl_off = 0, inst_off = 0, tw_off = 0, partial_off = 0, ws_need = 0;
+    size_t inst_off = 0, tw_off = 0, partial_off = 0, ws_need = 0;
     std::vector<size_t> scratch_off;  // caller's order
     char *ws = nullptr;
     size_t ws_bytes = 0;
     std::vector<void *> psi, state;
-    int grid = 0;
-    hipStream_t cap = nullptr;
-    std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
+    // groups of instances (BatchGroup), split over the caller's stream ([0]) and one of the batch's own
+    // ([1]), which starts after the caller's earlier work and which the caller's stream then waits for
+    std::vector<pfc::BatchGroup> groups[2];
+    int64_t side_load = 0;  // points' worth of a step of groups[1]
+    hipStream_t side = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
 };
 
 namespace {
@@ -734,71 +736,32 @@ pfc_status do_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi_v, v
 }
 
 
-void drop_graphs(pfc_batch *b)
-{
-    for (auto &kv : b->graphs) {
-        (void)hipGraphExecDestroy(kv.second.second);
-        (void)hipGraphDestroy(kv.second.first);
-    }
-    b->graphs.clear();
-}
-
-// rows / pencils / items of every instance for its current candidate schedules
-pfc_status batch_layout(pfc_batch *b)
-{
-    for (int i = 0; i < b->count; ++i) {
-        pfc_batch::Inst &g = b->inst[i];
-        int wm = 0;
-        if (!pfc::batch_tiles(g.n0, g.M, g.vx, g.vy, g.vc, b->dtype == PFC_F64, &g.x_rows, &g.c_rows, &wm))
-            return fail(PFC_ERR_UNSUPPORTED, "instance %d: no batched schedule for %d x %d (candidates %d %d %d)", i,
-                        g.n0, g.nx, g.vx, g.vy, g.vc);
-        g.W = std::min(wm, g.M);
-        g.tiles = g.M / g.W;
-        g.x_items = (g.n0 + g.x_rows - 1) / g.x_rows;
-        g.c_items = (g.n0 + g.c_rows - 1) / g.c_rows;
-        g.f_rows = std::max(g.x_rows, g.c_rows);  // both powers of two: a multiple of each
-        if (g.f_rows % g.x_rows || g.f_rows % g.c_rows)
-            return fail(PFC_ERR_INTERNAL, "instance %d: rows per item %d and %d do not nest", i, g.x_rows, g.c_rows);
-        g.f_items = (g.n0 + g.f_rows - 1) / g.f_rows;
-    }
-    return PFC_OK;
-}
-
-// builds the device instance table (largest instances first) and uploads it (synchronous)
+// builds the device instance table, grouped by shape and schedules, and uploads it (synchronous)
 template <typename T>
 pfc_status batch_upload_table(pfc_batch *b)
 {
+    // largest shapes first, then by shape and schedules, so that every group is one run of the table
+    std::vector<int> order(b->count);
+    std::iota(order.begin(), order.end(), 0);
+    auto key = [&](int i) {
+        const pfc_batch::Inst &g = b->inst[i];
+        return std::array<int64_t, 5>{-(int64_t)g.n0 * g.nx, g.n0, g.vx, g.vy, g.vc};
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
     std::vector<pfc::BatchInst<T>> table(b->count);
-    int xb = 0, yb = 0, cb = 0, fb = 0;
+    std::vector<pfc::BatchGroup> groups;
     for (int j = 0; j < b->count; ++j) {
-        const int i = b->order[j];
+        const int i = order[j];
         const pfc_batch::Inst &g = b->inst[i];
         const pfc_plan_desc &d = b->descs[i];
+        if (j == 0 || key(i) != key(order[j - 1])) groups.push_back({g.n0, g.M, g.vx, g.vy, g.vc, j, 0});
+        ++groups.back().count;
         pfc::BatchInst<T> &t = table[j];
         t.psi = (T *)b->psi[i];
         t.state = (cx<T> *)b->state[i];
         t.scratch = (cx<T> *)(b->ws + b->scratch_off[i]);
         t.n0 = g.n0;
         t.M = g.M;
-        t.W = g.W;
-        t.tiles = g.tiles;
-        t.x_items = g.x_items;
-        t.c_items = g.c_items;
-        t.x_rows = g.x_rows;
-        t.c_rows = g.c_rows;
-        t.f_rows = g.f_rows;
-        t.f_items = g.f_items;
-        t.x_begin = xb;
-        t.y_begin = yb;
-        t.c_begin = cb;
-        t.f_begin = fb;
-        t.vx = g.vx;
-        t.vy = g.vy;
-        t.vc = g.vc;
-        xb += g.x_items;
-        yb += g.tiles;
-        cb += g.c_items;
-        fb += g.f_items;
         t.sc = (T)(1.0 / ((double)g.n0 * (double)g.M));
         t.mp.r = (T)d.r;
         t.mp.dt = (T)d.dt;
@@ -810,13 +773,19 @@ pfc_status batch_upload_table(pfc_batch *b)
         t.mp.nl = (d.flags & PFC_FLAG_LINEAR_ONLY) ? T(0) : T(1);
         t.mp.model = (int)d.model;
     }
-    b->x_total = xb;
-    b->y_total = yb;
-    b->c_total = cb;
-    b->f_total = fb;
     PFC_TRY(hipMemcpy(b->ws + b->inst_off, table.data(), table.size() * sizeof(table[0]), hipMemcpyHostToDevice),
             "instance table upload");
-    drop_graphs(b);  // the captured launches hold the item totals
+    // Largest group on the caller's stream; each next one goes where less has been given.  A step of a
+    // group costs its points plus the latency of its two launches, some 2^20 points' worth (7 us).
+    b->groups[0].clear();
+    b->groups[1].clear();
+    int64_t load[2] = {0, 0};
+    for (const pfc::BatchGroup &g : groups) {
+        const int k = load[1] < load[0] ? 1 : 0;
+        b->groups[k].push_back(g);
+        load[k] += (int64_t)g.count * g.n0 * g.M * 2 + (int64_t(1) << 20);
+    }
+    b->side_load = load[1];
     return PFC_OK;
 }
 
@@ -828,57 +797,47 @@ pfc_status batch_bind_impl(pfc_batch *b)
     const std::vector<cx<T>> tw = twiddle_table<T>(int64_t(1) << b->lt_shift);
     PFC_TRY(hipMemcpy(b->ws + b->tw_off, tw.data(), tw.size() * sizeof(tw[0]), hipMemcpyHostToDevice),
             "twiddle upload");
-    PFC_TRY(hipMemset(b->ws + b->ctl_off, 0, sizeof(pfc::BatchCtl)), "barrier state reset");
-    int per_cu = 0, cus = 0;
-    PFC_TRY(pfc::batch_blocks_per_cu<T>(&per_cu), "occupancy query");
-    PFC_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device), "CU count");
-    if (per_cu < 1) return fail(PFC_ERR_INTERNAL, "batched kernel does not fit on a CU");
-    b->grid = per_cu * cus;
     return PFC_OK;
 }
 
-template <typename T>
-pfc::BatchArgs<T> batch_args(const pfc_batch *b, int64_t nsteps)
-{
-    pfc::BatchArgs<T> a;
-    a.inst = (const pfc::BatchInst<T> *)(b->ws + b->inst_off);
-    a.ninst = b->count;
-    a.x_total = b->x_total;
-    a.y_total = b->y_total;
-    a.c_total = b->c_total;
-    a.f_total = b->f_total;
-    a.tw = (const cx<T> *)(b->ws + b->tw_off);
-    a.lt_shift = b->lt_shift;
-    a.ctl = (pfc::BatchCtl *)(b->ws + b->ctl_off);
-    a.max_polls = 1ull << 22;  // a few seconds of polling: far beyond any pass of a resident grid
-    a.nsteps = nsteps;
-    return a;
-}
-
+// nsteps steps of every instance.  The groups of the side stream run beside those of the caller's: both
+// are launched step by step, so neither queue waits for the host.  The fork and the join cost about 30 us,
+// so the side stream is used where it takes that much work off the caller's (12 instances each of 128^2 ..
+// 1024^2 FP32: 10 steps 1095 against 1413 us on one stream; 3 each of 32^2 .. 512^2: one step 54 us on one
+// stream against 75, two steps 101 against 102).
 template <typename T>
 pfc_status batch_step_impl(pfc_batch *b, int64_t nsteps, hipStream_t s)
 {
-    auto it = b->graphs.find(nsteps);
-    if (it == b->graphs.end()) {
-        if (!b->cap) PFC_TRY(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "capture stream");
-        hipGraph_t graph = nullptr;
-        hipGraphExec_t exec = nullptr;
-        PFC_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "graph capture begin");
-        hipError_t le = pfc::launch_batch<T>(batch_args<T>(b, nsteps), b->grid, b->cap);
-        hipError_t ee = hipStreamEndCapture(b->cap, &graph);
-        if (le != hipSuccess) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return hip_fail(le, "batched kernel launch (capture)");
-        }
-        if (ee != hipSuccess) return hip_fail(ee, "graph capture end");
-        hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-        if (ie != hipSuccess) {
-            (void)hipGraphDestroy(graph);
-            return hip_fail(ie, "graph instantiate");
-        }
-        it = b->graphs.emplace(nsteps, std::make_pair(graph, exec)).first;
+    const pfc::BatchInst<T> *table = (const pfc::BatchInst<T> *)(b->ws + b->inst_off);
+    const cx<T> *tw = (const cx<T> *)(b->ws + b->tw_off);
+    const bool two = nsteps * b->side_load >= (int64_t(1) << 22);
+    if (two) {
+        if (!b->side) PFC_TRY(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking), "batch stream");
+        if (!b->fork) PFC_TRY(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming), "batch event");
+        if (!b->join) PFC_TRY(hipEventCreateWithFlags(&b->join, hipEventDisableTiming), "batch event");
+        PFC_TRY(hipEventRecord(b->fork, s), "batch event record");
+        PFC_TRY(hipStreamWaitEvent(b->side, b->fork, 0), "batch stream wait");
     }
-    PFC_TRY(hipGraphLaunch(it->second.second, s), "graph launch");
+    hipError_t e = hipSuccess;
+    for (int64_t n = 0; n < nsteps && e == hipSuccess; ++n)
+        for (int pass = (n == 0 ? 0 : 1); pass < 3 && e == hipSuccess; ++pass)
+            for (int k = 0; k < 2; ++k)
+                for (const pfc::BatchGroup &g : b->groups[k]) {
+                    hipStream_t q = k == 0 || !two ? s : b->side;
+                    if (e != hipSuccess) break;
+                    if (pass == 1)
+                        e = pfc::launch_batch_y<T>(g, table, tw, b->lt_shift, q);
+                    else
+                        e = pfc::launch_batch_x<T>(
+                            g, pass == 0 ? pfc::BATCH_X_FWD : n + 1 < nsteps ? pfc::BATCH_X_FUSED : pfc::BATCH_X_INV, table,
+                            tw, b->lt_shift, q);
+                }
+    if (two) {  // joined after an error too: the caller's stream waits for whatever was launched
+        hipError_t je = hipEventRecord(b->join, b->side);
+        if (je == hipSuccess) je = hipStreamWaitEvent(s, b->join, 0);
+        if (e == hipSuccess) e = je;
+    }
+    if (e != hipSuccess) return hip_fail(e, "batched step launch");
     return PFC_OK;
 }
 
@@ -910,7 +869,7 @@ pfc_status batch_state_init_impl(pfc_batch *b, hipStream_t s)
 }
 
 // Coordinate descent over the candidate schedules: for each pass kind and each distinct length,
-// time every candidate by launching the persistent kernel (no graph) for `steps` steps.
+// time every candidate over `steps` steps.
 template <typename T>
 pfc_status batch_autotune_impl(pfc_batch *b, hipStream_t s, int steps, double *total_ms)
 {
@@ -922,17 +881,14 @@ pfc_status batch_autotune_impl(pfc_batch *b, hipStream_t s, int steps, double *t
         return hip_fail(ce, "hipEventCreate");
     }
     auto trial = [&](float *ms) -> pfc_status {
-        pfc_status st = batch_layout(b);
-        if (!st) st = batch_upload_table<T>(b);
+        pfc_status st = batch_upload_table<T>(b);
         if (st) return st;
         PFC_TRY(hipEventRecord(e0, s), "event record");
-        PFC_TRY(pfc::launch_batch<T>(batch_args<T>(b, steps), b->grid, s), "batched kernel launch");
+        st = batch_step_impl<T>(b, steps, s);
+        if (st) return st;
         PFC_TRY(hipEventRecord(e1, s), "event record");
         PFC_TRY(hipEventSynchronize(e1), "event synchronize");
         PFC_TRY(hipEventElapsedTime(ms, e0, e1), "event timing");
-        pfc::BatchCtl ctl;
-        PFC_TRY(hipMemcpy(&ctl, b->ws + b->ctl_off, sizeof ctl, hipMemcpyDeviceToHost), "barrier state read");
-        if (ctl.err) return fail(PFC_ERR_INTERNAL, "grid barrier timed out during autotuning");
         return PFC_OK;
     };
     pfc_status st = PFC_OK;
@@ -1336,24 +1292,10 @@ pfc_status pfc_batch_create(pfc_batch **out, const pfc_plan_desc *descs, int cou
         b->inst.push_back(g);
         Lt = std::max<int64_t>(Lt, std::max(g.n0, g.nx));
     }
-    {
-        pfc_status st = batch_layout(b);
-        if (st) {
-            delete b;
-            return st;
-        }
-    }
     while ((int64_t(1) << b->lt_shift) < Lt) ++b->lt_shift;
-    // largest instances first: their items are the longest, so they start first
-    b->order.resize(count);
-    std::iota(b->order.begin(), b->order.end(), 0);
-    std::stable_sort(b->order.begin(), b->order.end(), [&](int x, int y) {
-        return (int64_t)b->inst[x].n0 * b->inst[x].nx > (int64_t)b->inst[y].n0 * b->inst[y].nx;
-    });
     const size_t cs = b->dtype == PFC_F64 ? 16 : 8;
     const size_t inst_size = b->dtype == PFC_F64 ? sizeof(pfc::BatchInst<double>) : sizeof(pfc::BatchInst<float>);
-    b->ctl_off = 0;
-    b->inst_off = 256;
+    b->inst_off = 0;
     b->tw_off = b->inst_off + align256(inst_size * count);
     b->partial_off = b->tw_off + align256(twiddle_count(Lt) * cs);
     size_t off = b->partial_off + align256(pfc::kReduceBlocks * sizeof(double));
@@ -1368,7 +1310,15 @@ pfc_status pfc_batch_create(pfc_batch **out, const pfc_plan_desc *descs, int cou
 
 size_t pfc_batch_workspace_bytes(const pfc_batch *b) { return b ? b->ws_need : 0; }
 
-int pfc_batch_grid(const pfc_batch *b) { return b ? b->grid : 0; }
+int pfc_batch_grid(const pfc_batch *b)
+{
+    int64_t n = 0;
+    if (b)
+        for (const auto &list : b->groups)
+            for (const pfc::BatchGroup &g : list)
+                n += b->dtype == PFC_F64 ? pfc::batch_y_workgroups<double>(g) : pfc::batch_y_workgroups<float>(g);
+    return (int)n;
+}
 
 pfc_status pfc_batch_bind(pfc_batch *b, void *const *psi, void *const *state, void *workspace, size_t bytes)
 {
@@ -1388,7 +1338,6 @@ pfc_status pfc_batch_bind(pfc_batch *b, void *const *psi, void *const *state, vo
     }
     DeviceGuard dg(b->device);
     if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
-    drop_graphs(b);
     b->psi.assign(psi, psi + b->count);
     b->state.assign(state, state + b->count);
     b->ws = (char *)workspace;
@@ -1424,13 +1373,6 @@ pfc_status pfc_batch_check(pfc_batch *b, void *stream)
     DeviceGuard dg(b->device);
     if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
     PFC_TRY(hipStreamSynchronize((hipStream_t)stream), "stream synchronize");
-    pfc::BatchCtl ctl;
-    PFC_TRY(hipMemcpy(&ctl, b->ws + b->ctl_off, sizeof ctl, hipMemcpyDeviceToHost), "barrier state read");
-    if (ctl.err) {
-        PFC_TRY(hipMemset(b->ws + b->ctl_off, 0, sizeof ctl), "barrier state reset");
-        return fail(PFC_ERR_INTERNAL, "a grid barrier of the batched kernel timed out (workgroups not all resident); "
-                    "results of that launch are incomplete");
-    }
     return PFC_OK;
 }
 
@@ -1457,16 +1399,10 @@ pfc_status pfc_batch_set_tuning(pfc_batch *b, const int *variants, int n)
                 return fail(PFC_ERR_INVALID_ARG, "instance %d pass %d: variant %d out of [0, %d)", i, k,
                             variants[3 * i + k], nc);
         }
-    std::vector<pfc_batch::Inst> saved = b->inst;
     for (int i = 0; i < b->count; ++i) {
         b->inst[i].vx = variants[3 * i];
         b->inst[i].vy = variants[3 * i + 1];
         b->inst[i].vc = variants[3 * i + 2];
-    }
-    pfc_status st = batch_layout(b);
-    if (st) {
-        b->inst = saved;
-        return st;
     }
     if (!b->ws) return PFC_OK;
     DeviceGuard dg(b->device);
@@ -1487,8 +1423,13 @@ pfc_status pfc_batch_autotune(pfc_batch *b, void *stream, int steps, double *ms_
 pfc_status pfc_batch_destroy(pfc_batch *b)
 {
     if (!b) return PFC_OK;
-    drop_graphs(b);
-    if (b->cap) (void)hipStreamDestroy(b->cap);
+    if (b->side) {
+        DeviceGuard dg(b->device);
+        (void)hipStreamSynchronize(b->side);
+        (void)hipStreamDestroy(b->side);
+        if (b->fork) (void)hipEventDestroy(b->fork);
+        if (b->join) (void)hipEventDestroy(b->join);
+    }
     delete b;
     return PFC_OK;
 }

@@ -122,48 +122,16 @@ struct HydroArgs {
     double a0;     // width of the Gaussian average
 };
 
-// ---- batched persistent form (one entry per instance, in device memory)
+// ---- batched form (one entry per instance, in device memory)
 template <typename T>
 struct BatchInst {
     T *psi;
     cx<T> *state;
     cx<T> *scratch;
-    int n0;          // y length (last-axis FFT length)
-    int M;           // x length / 2
-    int W;           // active pencils per y item
-    int tiles;       // y items (M / W)
-    int x_items;     // x r2c items
-    int c_items;     // x c2r items
-    int x_rows, c_rows;  // rows per x r2c / x c2r item
-    int f_rows, f_items;  // fused x c2r + x r2c items (between two steps): rows per item, items
-    int x_begin, y_begin, c_begin, f_begin;  // first global item of this instance in each pass
-    int vx, vy, vc;                 // candidate schedule of the x forward, y and x inverse passes
-    T sc;            // 1 / (n0 M)
+    int n0;  // y length (last-axis FFT length)
+    int M;   // x length / 2
+    T sc;    // 1 / (n0 M)
     ModelParams<T> mp;
-};
-
-// Grid-barrier state of the batched kernel.  The arrival counter and the generation the waiters
-// poll sit on separate 128-byte lines: on one line, the polling and the arrivals contend for it
-// (measured on MI355X, 512 workgroups: 35 us per barrier on one line, 13 us on two).
-struct BatchCtl {
-    unsigned count;
-    unsigned pad0[31];
-    unsigned gen;
-    int err;
-    int pad1[30];
-};
-static_assert(sizeof(BatchCtl) == 256, "the instance table follows at byte 256");
-
-template <typename T>
-struct BatchArgs {
-    const BatchInst<T> *inst;  // sorted largest first
-    int ninst;
-    int x_total, y_total, c_total, f_total;
-    const cx<T> *tw;
-    int lt_shift;
-    BatchCtl *ctl;
-    unsigned long long max_polls;
-    int64_t nsteps;
 };
 
 }  // namespace pfc
