@@ -220,6 +220,18 @@ pfc_status pfc_plan_set_tuning(pfc_plan *p, const int *variants, int npasses);
 pfc_status pfc_step_backward(pfc_plan *p, const void *psi_n, const void *psi_np1, const void *lambda_np1,
                              void *lambda_n, double *dLdr_accum_dev, void *stream);
 
+/* nsteps >= 0 steps as pfc_step, storing the field after each: psi (psi^0) is only read, traj (nsteps real
+ * fields back to back, 16-byte aligned, overlapping neither psi nor state) receives psi^1 .. psi^nsteps,
+ * state is updated in place.  The same bits as pfc_step.  Source: the step of Listing 1 (Eq. (4)). */
+pfc_status pfc_step_trajectory(pfc_plan *p, const void *psi, void *state, void *traj, int64_t nsteps, void *stream);
+
+/* pfc_step_backward along a trajectory, last step first: psi^0 = psi0 and psi^{n+1} = traj[n] (as
+ * pfc_step_trajectory stores them); lambda holds the adjoint of psi^nsteps and receives that of psi^0, and
+ * all steps' contributions are added to *dLdr_accum_dev.  lambda overlaps no field.  Source: the update of
+ * Listing 1 (Eq. (4)), transposed as in pfc_step_backward; the paper has no adjoint. */
+pfc_status pfc_rollout_backward(pfc_plan *p, const void *psi0, const void *traj, void *lambda, int64_t nsteps,
+                                double *dLdr_accum_dev, void *stream);
+
 /* Free energy, Eq. (3), on the grid: out_dev[0] = dV [ (1/(2N)) sum_k (r + L(q_k)) |psi_hat_k|^2
  * + sum_x psi^4/4 ] (sum over the full spectrum, dV = product of dx), out_dev[1] = mean of psi
  * from the k = 0 mode.  Accumulation in FP64 in both dtypes.  out_dev: 2 device doubles.

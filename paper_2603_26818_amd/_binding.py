@@ -98,6 +98,8 @@ _SIGS = {
     "pfc_step_timed": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64,
                                       ctypes.c_void_p, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int)]),
     "pfc_step_backward": (ctypes.c_int, [ctypes.c_void_p] * 7),
+    "pfc_step_trajectory": (ctypes.c_int, [ctypes.c_void_p] * 4 + [ctypes.c_int64, ctypes.c_void_p]),
+    "pfc_rollout_backward": (ctypes.c_int, [ctypes.c_void_p] * 4 + [ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]),
     "pfc_plan_autotune": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                          ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
     "pfc_plan_get_tuning": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
@@ -339,6 +341,31 @@ class Plan:
             self._tensor(lambda_n, self.shape, self.real_dtype, "lambda_n"),
             ctypes.c_void_p(dLdr.data_ptr()), _stream_ptr(self.device)), "pfc_step_backward")
         return lambda_n, dLdr
+
+    def step_trajectory(self, psi, state, nsteps, traj=None):
+        """pfc_step_trajectory: the fields after each of nsteps steps from psi (which is not changed), stacked
+        in traj; state is updated in place."""
+        shape = (int(nsteps),) + tuple(self.shape)
+        traj = _torch().empty(shape, dtype=self.real_dtype, device=self.device) if traj is None else traj
+        _check(self._lib.pfc_step_trajectory(self._h, self._tensor(psi, self.shape, self.real_dtype, "psi"),
+                                             self._tensor(state, self.state_shape, self.complex_dtype, "state"),
+                                             self._tensor(traj, shape, self.real_dtype, "traj"), int(nsteps),
+                                             _stream_ptr(self.device)), "pfc_step_trajectory")
+        return traj
+
+    def rollout_backward(self, psi0, traj, lam, dLdr):
+        """pfc_rollout_backward: lam (the adjoint of traj[-1]) becomes that of psi0, in place; dLdr (float64)
+        receives the steps' contributions."""
+        torch = _torch()
+        if dLdr.dtype != torch.float64 or dLdr.device != self.device or dLdr.numel() < 1:
+            raise ValueError("dLdr must be a float64 tensor with >= 1 element on the plan's device")
+        n = int(traj.shape[0])
+        _check(self._lib.pfc_rollout_backward(
+            self._h, self._tensor(psi0, self.shape, self.real_dtype, "psi0"),
+            self._tensor(traj, (n,) + tuple(self.shape), self.real_dtype, "traj"),
+            self._tensor(lam, self.shape, self.real_dtype, "lambda"), n, ctypes.c_void_p(dLdr.data_ptr()),
+            _stream_ptr(self.device)), "pfc_rollout_backward")
+        return lam, dLdr
 
     def hydro_state_init(self, psi, v, psi_state=None, v_state=None):
         """States of the density and of the ndim velocity components (v: [ndim, *shape])."""

@@ -227,7 +227,7 @@ bool x_fused_ok(const Geom &g)
 }
 
 template <typename T>
-hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStream_t s)
+hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw, hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.M, [&](auto Mc) -> hipError_t {
@@ -248,8 +248,13 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStre
                 // measured 1.3 % slower per 512^3 FP32 step, the same in FP64.  Padded LDS rows
                 // (power-of-two M): FP64 steps 438 against 431 steps/s at 512^3, 2768 against 2671
                 // at 256^3; FP32 even.
-                hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), decltype(latc)::value>), grid, block, 0, s, data, g.xrows,
-                                   tw + g.tw_x, g.lt_shift, sc, pack_of(g));
+                constexpr bool LAT = decltype(latc)::value;
+                if (real)
+                    hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT, true>), grid, block, 0, s,
+                                       data, real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
+                else
+                    hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT>), grid, block, 0, s, data,
+                                       real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
                 return hipGetLastError();
             }
             };
@@ -260,8 +265,39 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStre
 }
 
 template <typename T>
+hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T *psi_n, const T *psi_np1, T c3,
+                            double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
+{
+    if (!layout_ok(g)) return hipErrorInvalidValue;
+    return by_length(g.M, [&](auto Mc) -> hipError_t {
+        constexpr int M = decltype(Mc)::value;
+        if constexpr (M > 1024) {
+            return hipErrorInvalidValue;
+        } else {
+            auto run = [&](auto pic, auto pfc, auto latc) -> hipError_t {
+                using PLI = decltype(pic);
+                using PLF = decltype(pfc);
+                if constexpr (!XStepFused<PLI, PLF>::ok) {
+                    return hipErrorInvalidValue;
+                } else {
+                    *nblocks = cdiv(g.xrows, XFused<PLI, PLF, 64>::R);
+                    const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
+                    const AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial, add ? 1 : 0};
+                    hipLaunchKernelGGL((x_adj_r2c_kernel<T, PLI, PLF, is_pow2c(M), decltype(latc)::value>),
+                                       dim3((unsigned)*nblocks), dim3(64), 0, s, data, g.xrows, tw + g.tw_x, g.lt_shift, sc, ea,
+                                       pack_of(g));
+                    return hipGetLastError();
+                }
+            };
+            if (g.ndim == 2) return run(typename X2InvPlan<M>::type{}, typename X2FwdPlan<M>::type{}, std::true_type{});
+            return run(typename XInvPlan<M>::type{}, typename XFwdPlan<M>::type{}, std::false_type{});
+        }
+    });
+}
+
+template <typename T>
 hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu, const T *psi_n, const T *psi_np1,
-                                T *out, T c3, double *partial, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
+                                T *out, T c3, double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.M, [&](auto Mc) -> hipError_t {
@@ -276,7 +312,7 @@ hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu,
                 *nblocks = nb;
                 const dim3 grid((unsigned)nb), block(ROWS * PL::Tp);
                 const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-                AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial};
+                AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial, add ? 1 : 0};
                 hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_ADJOINT, false, false, false, decltype(latc)::value>), grid, block, 0, s, mu, out, g.xrows,
                                    tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
                 return hipGetLastError();
@@ -576,9 +612,11 @@ hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStrea
     template hipError_t launch_x_r2c<T>(const Geom &, const T *, cx<T> *, bool, const cx<T> *, hipStream_t, int);     \
     template hipError_t launch_x_c2r<T>(const Geom &, const cx<T> *, T *, const cx<T> *, hipStream_t, int);           \
     template hipError_t launch_x_c2r_adjoint<T>(const Geom &, const cx<T> *, const cx<T> *, const T *, const T *, T *, \
-                                                T, double *, int64_t *, const cx<T> *, hipStream_t);
+                                                T, double *, bool, int64_t *, const cx<T> *, hipStream_t);
 #define PFC_INSTANTIATE_XF(T)                                                                                         \
-    template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, const cx<T> *, hipStream_t);                       \
+    template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, T *, const cx<T> *, hipStream_t);                  \
+    template hipError_t launch_x_adj_r2c<T>(const Geom &, cx<T> *, const cx<T> *, const T *, const T *, T, double *,  \
+                                            bool, int64_t *, const cx<T> *, hipStream_t);                             \
     template bool x_fused_ok<T>(const Geom &);
 #define PFC_INSTANTIATE_Y(T)                                                                                          \
     template hipError_t launch_y_c2c<T>(const Geom &, cx<T> *, int, const cx<T> *, hipStream_t, int);                 \

@@ -265,7 +265,8 @@ __global__ __launch_bounds__(ROWS *PL::Tp) void x_r2c_kernel(const T *__restrict
 // EPI_PLAIN stores x.  EPI_ADJOINT transforms two spectra (mu from `in`, in the layout `pk`; nu
 // from `in2`, always in the plain layout of rows of M, so that nu's row r covers the same bytes as
 // the real row r) and stores
-//   out = mu - c3 * psi_n^2 * nu,   and writes the block's FP64 sum of nu * psi_np1 to partial[].
+//   out = mu - c3 * psi_n^2 * nu   (TO_LDS: to the rows' LDS slots, as EPI_PLAIN), adding the thread's FP64
+// share of the sum of nu * psi_np1 to *acc, whose workgroup sum goes to partial[bid] (adj_partial).
 // `in2` and `out` may be the same buffer: each block reads its rows completely before writing them.
 enum { EPI_PLAIN = 0, EPI_ADJOINT = 1 };
 
@@ -276,7 +277,17 @@ struct AdjEpi {
     const T *psi_np1;
     T c3;
     double *partial;
+    int add;  // partial[bid] += the sum, instead of =
 };
+
+// The workgroup's sum of acc to its own slot of the partials.
+template <typename T>
+__device__ __forceinline__ void adj_partial(const AdjEpi<T> &ea, double acc, int64_t bid)
+{
+    __shared__ double red[16];
+    const double s = block_sum(acc, red);
+    if (threadIdx.x == 0) ea.partial[bid] = ea.add ? ea.partial[bid] + s : s;
+}
 
 // Pre-combination of one row for the c2r: own elements X(k) from `src` (column k at src[pk.col(k)]);
 // the mirror X(M-k) either through LDS (PG = false) or straight from `src` (PG = true: a second,
@@ -346,9 +357,8 @@ template <typename T, class PL, int ROWS, int EPI, bool PAD = false, bool PG = f
 __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nrows, const cx<T> *__restrict__ tw,
                                             int lt_shift, T sc, const AdjEpi<T> &ea, int64_t bid, cx<T> *sh,
                                             const Pack &pk, const int tid = (int)threadIdx.x,
-                                            const XTw<T, PL> *pre = nullptr)
+                                            const XTw<T, PL> *pre = nullptr, double *acc = nullptr)
 {
-    static_assert(!TO_LDS || EPI == EPI_PLAIN, "staging only for the plain epilogue");
     constexpr int M = PL::L, Tp = PL::Tp, Rl = PL::last, Rmax = PL::Rmax;
     constexpr int LD = XPitch<T, M, PAD>::value;
     const int p = tid / Tp, t = tid - p * Tp;
@@ -389,7 +399,7 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
         fft_stages<T, PL, +1, TW_STAGE, 1, PRE>(w, t, lds, tw, lt_shift, 0, PRE ? &pre->st : nullptr);
         const cx<T> *pn = reinterpret_cast<const cx<T> *>(ea.psi_n) + r0 * M;
         const cx<T> *pn1 = reinterpret_cast<const cx<T> *>(ea.psi_np1) + r0 * M;
-        double acc = 0.0;
+        if constexpr (TO_LDS) __syncthreads();  // every thread of the row is past its last exchange read
         if (valid) {
 #pragma unroll
             for (int b = 0; b < PL::nb(Rl); ++b)
@@ -399,13 +409,14 @@ __device__ __forceinline__ void x_c2r_block(const cx<T> *in, T *out, int64_t nro
                     const int m = t + b * Tp + r * (M / Rl);
                     const cx<T> mu = scale(v[b * Rl + r], sc), nu = scale(w[b * Rl + r], sc);
                     const cx<T> a = pn[m], c = pn1[m];
-                    dst[m] = {mu.x - ea.c3 * a.x * a.x * nu.x, mu.y - ea.c3 * a.y * a.y * nu.y};
-                    acc += (double)nu.x * (double)c.x + (double)nu.y * (double)c.y;
+                    const cx<T> o = {mu.x - ea.c3 * a.x * a.x * nu.x, mu.y - ea.c3 * a.y * a.y * nu.y};
+                    if constexpr (TO_LDS)
+                        sh[p * LD + m] = o;
+                    else
+                        dst[m] = o;
+                    *acc += (double)nu.x * (double)c.x + (double)nu.y * (double)c.y;
                 }
         }
-        __shared__ double red[16];
-        const double s = block_sum(acc, red);
-        if (threadIdx.x == 0) ea.partial[bid] = s;
     }
 }
 
@@ -418,8 +429,10 @@ __global__ __launch_bounds__(ROWS *PL::Tp) void x_c2r_kernel(const cx<T> *in, T 
     constexpr bool PRE = LAT && preload_tw<T, PL>();
     XTw<T, PL> pre;
     if constexpr (PRE) load_xtw<T, PL, false>(pre, (int)threadIdx.x % PL::Tp, tw, lt_shift);
+    double acc = 0.0;
     x_c2r_block<T, PL, ROWS, EPI, PAD, PG, NT, false, PRE>(in, out, nrows, tw, lt_shift, sc, ea, blockIdx.x, sh, pk,
-                                                           (int)threadIdx.x, &pre);
+                                                           (int)threadIdx.x, &pre, &acc);
+    if constexpr (EPI == EPI_ADJOINT) adj_partial(ea, acc, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -477,12 +490,46 @@ __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int
 
 // The fused x pass of the single-plan step between two steps: one workgroup of NTH threads (one
 // wavefront in the step) takes XFused<PLI, PLF, NTH>::R rows of the packed spectrum, in place.
-template <typename T, class PLI, class PLF, int NTH, bool NT, bool PAD, bool LAT = false>
-__global__ __launch_bounds__(NTH) void x_c2r_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw,
+// STORE: the field in between is also stored, to `real`.
+template <typename T, class PLI, class PLF, int NTH, bool NT, bool PAD, bool LAT = false, bool STORE = false>
+__global__ __launch_bounds__(NTH) void x_c2r_r2c_kernel(cx<T> *data, T *real, int64_t nrows, const cx<T> *__restrict__ tw,
                                                         int lt_shift, T sc, Pack pk)
 {
     __shared__ cx<T> sh[XFused<PLI, PLF, NTH>::R * XPitch<T, PLI::L, PAD>::value];
-    x_c2r_r2c_block<T, PLI, PLF, NTH, NT, PAD, LAT>(data, data, nrows, tw, lt_shift, sc, blockIdx.x, sh, pk);
+    x_c2r_r2c_block<T, PLI, PLF, NTH, NT, PAD, LAT, STORE>(data, data, nrows, tw, lt_shift, sc, blockIdx.x, sh, pk,
+                                                           (int)threadIdx.x, real);
+}
+
+// The x pass between two adjoint steps: lambda_n of one (EPI_ADJOINT) and the x r2c of lambda_n that the
+// next one starts with, one wavefront per workgroup as above; lambda_n itself is not stored.  mu and the
+// output spectrum are `data`.
+template <typename T, class PLI, class PLF, bool PAD, bool LAT>
+__global__ __launch_bounds__(64) void x_adj_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift,
+                                                       T sc, AdjEpi<T> ea, Pack pk)
+{
+    using F = XFused<PLI, PLF, 64>;
+    constexpr int LD = XPitch<T, PLI::L, PAD>::value, M = PLI::L;
+    constexpr bool PRE = LAT && preload_tw<T, PLI>() && preload_tw<T, PLF>();
+    __shared__ cx<T> sh[F::R * LD];
+    XTw<T, PLI> prei;
+    XTw<T, PLF> pref;
+    if constexpr (PRE) {
+        load_xtw<T, PLI, false>(prei, (int)threadIdx.x % PLI::Tp, tw, lt_shift);
+        load_xtw<T, PLF, true>(pref, (int)threadIdx.x % PLF::Tp, tw, lt_shift);
+    }
+    const int64_t bid = blockIdx.x;
+    double acc = 0.0;
+#pragma unroll
+    for (int s = 0; s < F::R / F::RI; ++s)
+        x_c2r_block<T, PLI, F::RI, EPI_ADJOINT, PAD, false, false, true, PRE>(data, nullptr, nrows, tw, lt_shift, sc, ea,
+                                                                              bid * (F::R / F::RI) + s, sh + s * F::RI * LD,
+                                                                              pk, (int)threadIdx.x, &prei, &acc);
+    __syncthreads();  // all staged rows written
+#pragma unroll
+    for (int s = 0; s < F::R / F::RF; ++s)
+        x_r2c_block<T, PLF, F::RF, false, PAD, false, true, PRE>(nullptr, data, nrows, tw, lt_shift, bid * (F::R / F::RF) + s,
+                                                                 sh + s * F::RF * LD, pk, (int)threadIdx.x, &pref);
+    adj_partial(ea, acc, bid);
 }
 
 

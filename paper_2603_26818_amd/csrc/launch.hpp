@@ -61,10 +61,14 @@ hipError_t launch_x_r2c(const Geom &g, const T *in, cx<T> *out, bool cube, const
 template <typename T>
 hipError_t launch_x_c2r(const Geom &g, const cx<T> *in, T *out, const cx<T> *tw, hipStream_t s, int variant = 0);
 
-// fused x pass between two steps, in place on the packed spectrum: x c2r (1/N), cube, x r2c; on the
-// default x schedules, where x_fused_ok says the geometry has it
+// fused x pass between two steps, in place on the packed spectrum: x c2r (1/N; also stored to `real`
+// unless that is null), cube, x r2c; on the default x schedules, where x_fused_ok says the geometry has it
 template <typename T>
-hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, const cx<T> *tw, hipStream_t s);
+hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw, hipStream_t s);
+// the same between two adjoint steps: lambda_n as launch_x_c2r_adjoint, not stored, then its x r2c into data
+template <typename T>
+hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T *psi_n, const T *psi_np1, T c3,
+                            double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
 template <typename T>
 bool x_fused_ok(const Geom &g);
 // whether the last-axis passes can address blocks of 2^zs z planes (their element steps are
@@ -72,11 +76,11 @@ bool x_fused_ok(const Geom &g);
 template <typename T>
 bool z_blocks_ok(const Geom &g, int zs);
 
-// adjoint epilogue: out = mu - c3 psi_n^2 nu; partial[block] = sum nu psi_np1.  Returns the number
-// of partials through *nblocks.
+// adjoint epilogue: out = mu - c3 psi_n^2 nu; partial[block] = (add: +=) sum nu psi_np1.  Returns the
+// number of partials through *nblocks.
 template <typename T>
 hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu, const T *psi_n, const T *psi_np1,
-                                T *out, T c3, double *partial, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
+                                T *out, T c3, double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
 
 // y-axis (3D middle axis) complex FFT, in place; dir = -1 forward, +1 inverse.
 template <typename T>

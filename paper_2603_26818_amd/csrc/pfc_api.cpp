@@ -92,14 +92,6 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 size_t cx_size(const pfc_plan *p) { return p->d.dtype == PFC_F64 ? 16 : 8; }
 
-double corr_op(const pfc_plan_desc &d, double q)
-{
-    double a = (1.0 - q) * (1.0 - q);
-    if (d.model == PFC_ONE_MODE) return a;
-    double b = d.q1sq - q;
-    return a * (b * b + d.R1);
-}
-
 // The implicit denominator 1 + dt q (r + L(q)) must stay positive for every q in [0, qmax]
 // (qmax = |k|^2 at the corner of the grid).  Checked on a dense sampling of the interval.
 pfc_status check_denominator(const pfc_plan_desc &d)
@@ -110,10 +102,24 @@ pfc_status check_denominator(const pfc_plan_desc &d)
         qmax += k * k;
     }
     const int ns = 1 << 18;
+    const double dt = d.dt, r = d.r, q1 = d.q1sq, R1 = d.R1;
+    auto denominator = [=](double q, bool two) {
+        double a = (1.0 - q) * (1.0 - q);
+        if (two) a *= (q1 - q) * (q1 - q) + R1;
+        return 1.0 + dt * q * (r + a);
+    };
+    // first only whether one of them is not positive, in loops without a branch
+    auto any_bad = [&](auto two) {
+        int bad = 0;
+        for (int i = 0; i <= ns; ++i) bad |= !(denominator(qmax * (double)i / ns, decltype(two)::value) > 0.0);
+        return bad != 0;
+    };
+    const bool two = d.model != PFC_ONE_MODE;
+    if (!(two ? any_bad(std::true_type{}) : any_bad(std::false_type{}))) return PFC_OK;
     double worst = INFINITY, worst_q = 0.0;
     for (int i = 0; i <= ns; ++i) {
         double q = qmax * (double)i / ns;
-        double den = 1.0 + d.dt * q * (d.r + corr_op(d, q));
+        double den = denominator(q, two);
         if (!(den > worst)) {
             worst = den;
             worst_q = q;
@@ -436,19 +442,25 @@ pfc_status step_pass(const pfc_plan *p, const Bufs<T> &b, int pass, void *psi, v
 // LDS and is never stored), where the geometry has it and both x passes take their default schedules;
 // the first step's x r2c reads psi and the last step's x c2r writes it.  The results are those of
 // the separate passes, bit for bit.
+// With `traj`, psi is only read, and the field after every step is stored, to traj[0 .. nsteps).
 template <typename T>
-pfc_status step_with(const pfc_plan *p, const Bufs<T> &b, void *psi, void *state, int64_t nsteps, hipStream_t s)
+pfc_status step_with(const pfc_plan *p, const Bufs<T> &b, void *psi, void *state, int64_t nsteps, hipStream_t s,
+                     void *traj = nullptr)
 {
     const int np = step_passes(p);
+    const int64_t ntot = p->g.n0 * p->g.nrows * p->g.nx;
     const bool fuse = p->x_fused && p->var[0] == 0 && p->var[np - 1] == 0;
     for (int64_t n = 0; n < nsteps; ++n)
         for (int k = 0; k < np; ++k) {
             if (fuse && k == 0 && n > 0) continue;  // done by the fused pass that ended the step before
             if (fuse && k == np - 1 && n + 1 < nsteps) {
-                PFC_TRY(pfc::launch_x_c2r_r2c<T>(p->g, b.scratch, b.tw, s), "fused x pass launch");
+                PFC_TRY(pfc::launch_x_c2r_r2c<T>(p->g, b.scratch, traj ? (T *)traj + n * ntot : nullptr, b.tw, s),
+                        "fused x pass launch");
                 continue;
             }
-            pfc_status st = step_pass<T>(p, b, k, psi, state, s);
+            // the field a separate x pass reads or writes
+            void *f = !traj || (k == 0 && n == 0) ? psi : (T *)traj + (k == 0 ? n - 1 : n) * ntot;
+            pfc_status st = step_pass<T>(p, b, k, f, state, s);
             if (st) return st;
         }
     return PFC_OK;
@@ -458,6 +470,12 @@ template <typename T>
 pfc_status do_step(pfc_plan *p, void *psi, void *state, int64_t nsteps, hipStream_t s)
 {
     return step_with<T>(p, bufs<T>(p), psi, state, nsteps, s);
+}
+
+template <typename T>
+pfc_status do_step_trajectory(pfc_plan *p, const void *psi, void *state, void *traj, int64_t nsteps, hipStream_t s)
+{
+    return step_with<T>(p, bufs<T>(p), const_cast<void *>(psi), state, nsteps, s, traj);
 }
 
 template <typename T>
@@ -552,15 +570,17 @@ pfc_status do_autotune(pfc_plan *p, void *psi, void *state, hipStream_t s, int r
     return st;
 }
 
+// Adjoint steps nsteps - 1 .. 0 along fields psi^0 = psi0, psi^{n+1} = traj[n], from lam_in (the adjoint of
+// the last field) to lam_n (may be lam_in).  Between two of them the x passes are one where the geometry
+// has it, and the sums for dL/dr stay in their workgroups' slots until the end.
 template <typename T>
-pfc_status do_backward(pfc_plan *p, const void *psi_n, const void *psi_np1, const void *lam_np1, void *lam_n,
+pfc_status do_backward(pfc_plan *p, const void *psi0, const void *traj, const void *lam_in, void *lam_n, int64_t nsteps,
                        double *dLdr, hipStream_t s)
 {
     const Geom &g = p->g;
     const Bufs<T> b = bufs<T>(p);
     const pfc::ModelParams<T> mp = model_params<T>(p);
-    pfc_status st = fwd_xy<T>(p, (const T *)lam_np1, false, b.scratch, s);
-    if (st) return st;
+    const int64_t ntot = g.n0 * g.nrows * g.nx;
     // The output buffer holds the nu spectrum until the last pass.  nu is kept in the plain layout
     // (rows of M, no plane blocks), where its row r covers exactly the bytes of the real row r, so
     // the last pass can read each row of nu before it overwrites the same bytes with lambda_n.
@@ -568,19 +588,36 @@ pfc_status do_backward(pfc_plan *p, const void *psi_n, const void *psi_np1, cons
     Geom gn = g;
     gn.Mp = g.M;
     gn.zs = 0;
-    PFC_TRY(pfc::launch_last<T>(g, pfc::LAST_ADJOINT, b.scratch, b.scratch, nu, nullptr, mp, b.tw, s),
-            "last-axis adjoint launch");
-    if (g.ndim == 3) {
-        PFC_TRY(pfc::launch_y_c2c<T>(g, b.scratch, +1, b.tw, s), "y inverse launch");
-        PFC_TRY(pfc::launch_y_c2c<T>(gn, nu, +1, b.tw, s), "y inverse launch");
-    }
     const T c3 = (p->d.flags & PFC_FLAG_LINEAR_ONLY) ? T(0) : (T)(3.0 * p->d.dt);
-    int64_t nb = 0;
-    PFC_TRY(pfc::launch_x_c2r_adjoint<T>(g, b.scratch, nu, (const T *)psi_n, (const T *)psi_np1, (T *)lam_n, c3,
-                                          b.partial, &nb, b.tw, s),
-            "x_c2r adjoint launch");
-    if ((size_t)nb > p->n_partials) return fail(PFC_ERR_INTERNAL, "partials buffer too small");
-    PFC_TRY(pfc::launch_accumulate(b.partial, (int)nb, -p->d.dt, dLdr, s), "accumulate launch");
+    double *partial[2] = {b.partial, b.partial + g.xrows};  // fused and separate x passes
+    int64_t used[2] = {0, 0};
+    for (int64_t n = nsteps - 1; n >= 0; --n) {
+        if (n == nsteps - 1 || !p->x_fused) {
+            const T *lam = (const T *)(n == nsteps - 1 ? lam_in : lam_n);
+            PFC_TRY(pfc::launch_x_r2c<T>(g, lam, b.scratch, false, b.tw, s), "x_r2c launch");
+        }
+        if (g.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(g, b.scratch, -1, b.tw, s), "y forward launch");
+        PFC_TRY(pfc::launch_last<T>(g, pfc::LAST_ADJOINT, b.scratch, b.scratch, nu, nullptr, mp, b.tw, s),
+                "last-axis adjoint launch");
+        if (g.ndim == 3) {
+            PFC_TRY(pfc::launch_y_c2c<T>(g, b.scratch, +1, b.tw, s), "y inverse launch");
+            PFC_TRY(pfc::launch_y_c2c<T>(gn, nu, +1, b.tw, s), "y inverse launch");
+        }
+        const T *pn = n == 0 ? (const T *)psi0 : (const T *)traj + (n - 1) * ntot, *pn1 = (const T *)traj + n * ntot;
+        const int sep = (n == 0 || !p->x_fused) ? 1 : 0;
+        int64_t nb = 0;
+        if (sep)
+            PFC_TRY(pfc::launch_x_c2r_adjoint<T>(g, b.scratch, nu, pn, pn1, (T *)lam_n, c3, partial[1], used[1] > 0, &nb, b.tw, s),
+                    "x_c2r adjoint launch");
+        else
+            PFC_TRY(pfc::launch_x_adj_r2c<T>(g, b.scratch, nu, pn, pn1, c3, partial[0], used[0] > 0, &nb, b.tw, s),
+                    "adjoint x pass launch");
+        if (nb > (sep ? (int64_t)p->n_partials - g.xrows : g.xrows))
+            return fail(PFC_ERR_INTERNAL, "partials buffer too small");
+        used[sep] = nb;
+    }
+    for (int k = 0; k < 2; ++k)
+        if (used[k] > 0) PFC_TRY(pfc::launch_accumulate(partial[k], (int)used[k], -p->d.dt, dLdr, s), "accumulate launch");
     return PFC_OK;
 }
 
@@ -970,7 +1007,9 @@ pfc_status pfc_plan_create(pfc_plan **out, const pfc_plan_desc *d)
     g.lt_shift = 0;
     while ((int64_t(1) << g.lt_shift) < Lt) ++g.lt_shift;
     const size_t cs = cx_size(p);
-    p->n_partials = (size_t)std::max<int64_t>(2 * pfc::kReduceBlocks, g.xrows);
+    // do_backward keeps a slot per workgroup of its fused x pass (at most one per row) and, after those, of
+    // the separate one (the same in 2D, at least four rows each in 3D)
+    p->n_partials = (size_t)std::max<int64_t>(2 * pfc::kReduceBlocks, g.xrows + (d->ndim == 2 ? g.xrows : (g.xrows + 3) / 4));
     // Layout of the packed spectra (Pack in types.hpp), 3D only: rows longer than one 128-byte line
     // padded to whole lines, so that every column tile of the strided passes is line-aligned; and
     // blocks of Z consecutive z planes interleaved by line, so that the z pass reads Z lines in a
@@ -1060,6 +1099,7 @@ pfc_status pfc_plan_set_workspace(pfc_plan *p, void *dev_ptr, size_t bytes)
 pfc_status pfc_plan_set_params(pfc_plan *p, double r, double dt)
 {
     if (!p) return fail(PFC_ERR_INVALID_ARG, "plan is NULL");
+    if (r == p->d.r && dt == p->d.dt) return PFC_OK;  // what the plan has was validated
     pfc_plan_desc d = p->d;
     d.r = r;
     d.dt = dt;
@@ -1209,7 +1249,37 @@ pfc_status pfc_step_backward(pfc_plan *p, const void *psi_n, const void *psi_np1
         return fail(PFC_ERR_INVALID_ARG, "lambda_n overlaps psi_n or psi_np1");
     if (lambda_n != lambda_np1 && overlap(lambda_n, rb, lambda_np1, rb))
         return fail(PFC_ERR_INVALID_ARG, "lambda_n partially overlaps lambda_np1");
-    PFC_DISPATCH(p, do_backward, p, psi_n, psi_np1, lambda_np1, lambda_n, dLdr_accum_dev, (hipStream_t)stream);
+    PFC_DISPATCH(p, do_backward, p, psi_n, psi_np1, lambda_np1, lambda_n, 1, dLdr_accum_dev, (hipStream_t)stream);
+}
+
+pfc_status pfc_step_trajectory(pfc_plan *p, const void *psi, void *state, void *traj, int64_t nsteps, void *stream)
+{
+    PFC_CHECK(check_ready(p));
+    PFC_CHECK(check_ptr(psi, "psi"));
+    PFC_CHECK(check_ptr(state, "state"));
+    if (nsteps < 0) return fail(PFC_ERR_INVALID_ARG, "nsteps < 0");
+    if (nsteps == 0) return PFC_OK;
+    PFC_CHECK(check_ptr(traj, "traj"));
+    const size_t rb = real_bytes(p), tb = rb * (size_t)nsteps;
+    if (overlap(psi, rb, state, state_bytes(p)) || overlap(psi, rb, traj, tb) || overlap(state, state_bytes(p), traj, tb))
+        return fail(PFC_ERR_INVALID_ARG, "psi, state and traj overlap");
+    PFC_DISPATCH(p, do_step_trajectory, p, psi, state, traj, nsteps, (hipStream_t)stream);
+}
+
+pfc_status pfc_rollout_backward(pfc_plan *p, const void *psi0, const void *traj, void *lambda, int64_t nsteps,
+                                double *dLdr_accum_dev, void *stream)
+{
+    PFC_CHECK(check_ready(p));
+    if (nsteps < 0) return fail(PFC_ERR_INVALID_ARG, "nsteps < 0");
+    if (nsteps == 0) return PFC_OK;
+    PFC_CHECK(check_ptr(psi0, "psi0"));
+    PFC_CHECK(check_ptr(traj, "traj"));
+    PFC_CHECK(check_ptr(lambda, "lambda"));
+    if (!dLdr_accum_dev) return fail(PFC_ERR_INVALID_ARG, "dLdr_accum_dev is NULL");
+    const size_t rb = real_bytes(p);
+    if (overlap(lambda, rb, psi0, rb) || overlap(lambda, rb, traj, rb * (size_t)nsteps))
+        return fail(PFC_ERR_INVALID_ARG, "lambda overlaps psi0 or traj");
+    PFC_DISPATCH(p, do_backward, p, psi0, traj, lambda, lambda, nsteps, dLdr_accum_dev, (hipStream_t)stream);
 }
 
 size_t pfc_hydro_work_bytes(const pfc_plan *p) { return p ? hydro_work_bytes(p) : 0; }

@@ -2,10 +2,10 @@
 
 Forward: ``nsteps`` semi-implicit steps (pfc_step) from psi0, keeping (psi, state) every
 ``checkpoint_every`` steps.  Backward: for each segment, newest first, replay the segment from its
-checkpoint keeping every psi^n (the step is deterministic, so the replay reproduces the forward
-bit for bit), then apply the transpose of each step's Jacobian (pfc_step_backward) from the last
-step of the segment to the first.  pfc_step_backward also accumulates dL/dr in an FP64 device
-scalar.  All arithmetic runs in the library's kernels; this module only orders the calls.
+checkpoint keeping every psi^n (pfc_step_trajectory; the step is deterministic, so the replay
+reproduces the forward bit for bit), then apply the transpose of each step's Jacobian from the last
+step of the segment to the first (pfc_rollout_backward, which also accumulates dL/dr in an FP64
+device scalar).  All arithmetic runs in the library's kernels; this module only orders the calls.
 """
 from __future__ import annotations
 
@@ -48,14 +48,8 @@ class PFCRollout(torch.autograd.Function):
         lam = grad_out.detach().to(plan.real_dtype).contiguous().clone()
         dLdr = torch.zeros(1, dtype=torch.float64, device=plan.device)
         for psi_c, state_c, seg in reversed(ctx.ckpts):
-            traj = [psi_c]
-            psi = psi_c.clone()
-            state = state_c.clone()
-            for _ in range(seg):
-                plan.step(psi, state, 1)
-                traj.append(psi.clone())
-            for n in range(seg - 1, -1, -1):
-                plan.step_backward(traj[n], traj[n + 1], lam, lambda_n=lam, dLdr=dLdr)
+            traj = plan.step_trajectory(psi_c, state_c.clone(), seg)
+            plan.rollout_backward(psi_c, traj, lam, dLdr)
             del traj
         ctx.ckpts = None
         grad_r = dLdr.reshape(()).cpu() if ctx.needs_input_grad[1] else None
