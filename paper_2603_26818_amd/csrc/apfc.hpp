@@ -140,27 +140,120 @@ __global__ __launch_bounds__(ROWS *PL::Tp) void apfc_row_kernel(const cx<T> *in,
     }
 }
 
+// The x passes and the nonlinearity between them in one kernel: a workgroup takes ROWS rows of every
+// field, one field per TF = ROWS Tp threads (whole wavefronts).  FIRST: in holds the amplitudes; else
+// spectra along x, which it transforms back (times scale).  The amplitudes meet in LDS, every thread forms
+// N_f of its field at the points its forward transform starts from, and the rows of N_f are transformed
+// into the same LDS slots and stored.  in and out may be the same: rows are read before they are written.
+// 2 field passes where x inverse, nonlinearity and x forward apart move 6 (281 + 361 + 277 us at 256^3 x 6
+// FP32); bound by the LDS reads of the products, about 36 values per point and field: 715 us, and 470 us
+// for the first step's.  An earlier form, one 64-thread workgroup for all fields of a row, was slower than
+// the separate passes, with two wavefronts per CU.
+template <class PL>
+struct ApfcXRows {
+    static constexpr int value = 64 / PL::Tp < 1 ? 1 : 64 / PL::Tp;
+    static constexpr int TF = value * PL::Tp;
+};
+constexpr int kApfcXThreads = 512;  // at most: kApfcXThreads / TF fields
+template <typename T, class PL, bool FIRST>
+__global__ __launch_bounds__(kApfcXThreads) void apfc_x_kernel(const cx<T> *in, cx<T> *out, int64_t nrows, int64_t P, int nf,
+                                                               const ApfcTerm *__restrict__ terms,
+                                                               const int *__restrict__ off, T c3, T scale,
+                                                               const cx<T> *__restrict__ tw, int lt_shift)
+{
+    constexpr int L = PL::L, Tp = PL::Tp, R0 = PL::first, Rl = PL::last, Rmax = PL::Rmax;
+    constexpr int ROWS = ApfcXRows<PL>::value, TF = ApfcXRows<PL>::TF, LD = XPitch<T, L, true>::value;
+    extern __shared__ __align__(16) unsigned char apfc_lds[];
+    const int tid = threadIdx.x, f = __builtin_amdgcn_readfirstlane(tid / TF), q = tid - f * TF, p = q / Tp, t = q - p * Tp;
+    const int64_t row = (int64_t)blockIdx.x * ROWS + p;
+    const bool valid = row < nrows;
+    const int64_t base = (int64_t)f * P + (valid ? row : 0) * L;
+    cx<T> *const row0 = reinterpret_cast<cx<T> *>(apfc_lds) + p * LD;  // field 0's row; field g's ROWS LD g further
+    auto slot = [&](int g, int e) -> cx<T> & { return row0[g * (ROWS * LD) + xidx<T, L, true>(e)]; };
+    auto lds = [&](int e) -> cx<T> & { return slot(f, e); };
+    cx<T> v[Rmax];
+#pragma unroll
+    for (int b = 0; b < PL::nb(R0); ++b)
+#pragma unroll
+        for (int r = 0; r < R0; ++r) v[b * R0 + r] = valid ? in[base + t + b * Tp + r * (L / R0)] : cx<T>{T(0), T(0)};
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int b = 0; b < PL::nb(R0); ++b)
+#pragma unroll
+            for (int r = 0; r < R0; ++r) lds(t + b * Tp + r * (L / R0)) = v[b * R0 + r];
+    } else {
+        fft_stages<T, PL, +1>(v, t, lds, tw, lt_shift);
+        __syncthreads();  // every thread of the row is past its last exchange read
+#pragma unroll
+        for (int b = 0; b < PL::nb(Rl); ++b)
+#pragma unroll
+            for (int r = 0; r < Rl; ++r) {
+                const cx<T> z = v[b * Rl + r];
+                lds(t + b * Tp + r * (L / Rl)) = cx<T>{z.x * scale, z.y * scale};
+            }
+    }
+    __syncthreads();
+    // N_f, as apfc_nonlin_kernel
+    auto elem = [&](int i) { return t + (i / R0) * Tp + (i % R0) * (L / R0); };
+    T A2[Rmax] = {};
+    for (int g = 0; g < nf; ++g)
+#pragma unroll
+        for (int i = 0; i < Rmax; ++i) {
+            const cx<T> z = slot(g, elem(i));
+            A2[i] += z.x * z.x + z.y * z.y;
+        }
+#pragma unroll
+    for (int i = 0; i < Rmax; ++i) {
+        const cx<T> zj = slot(f, elem(i));
+        const T g = c3 * (T(2) * A2[i] - (zj.x * zj.x + zj.y * zj.y));
+        v[i] = {g * zj.x, g * zj.y};
+    }
+    const int m1 = off[f + 1];
+    for (int m = off[f]; m < m1; ++m) {
+        const ApfcTerm tm = terms[m];
+        const T c = apfc_coef<T>(tm);
+        auto pick = [&](int s, int e) -> cx<T> {
+            const cx<T> z = slot((s > 0 ? s : -s) - 1, e);
+            return s > 0 ? z : cx<T>{z.x, -z.y};
+        };
+#pragma unroll
+        for (int i = 0; i < Rmax; ++i) {
+            cx<T> z = cmul(pick(tm.a, elem(i)), pick(tm.b, elem(i)));
+            if (tm.c != 0) z = cmul(z, pick(tm.c, elem(i)));
+            v[i] = {v[i].x + c * z.x, v[i].y + c * z.y};
+        }
+    }
+    // (the transform's first LDS write follows a barrier: every amplitude has been read)
+    fft_stages<T, PL, -1>(v, t, lds, tw, lt_shift);
+    if (valid) {
+#pragma unroll
+        for (int b = 0; b < PL::nb(Rl); ++b)
+#pragma unroll
+            for (int r = 0; r < Rl; ++r) out[base + t + b * Tp + r * (L / Rl)] = v[b * Rl + r];
+    }
+}
+
 // signed index of Fourier mode i on an axis of length n in numpy's fftfreq order (Nyquist negative)
 __device__ __forceinline__ int fft_freq(int64_t i, int64_t n) { return (int)(2 * i < n ? i : i - n); }
 
 // Fused last-axis pass of the amplitude step (arguments in apfc_launch.hpp): completes the forward
 // FFT of FFT(N_f) along this axis, updates the state in place and writes the inverse FFT along this
 // axis of the new state to dst.
-template <typename T, class PL, int WMAX, bool PF, int G>
+template <typename T, class PL, int WMAX, bool PF, int G, bool LP = false>
 __global__ __launch_bounds__(WMAX *PL::Tp) void apfc_last_step_kernel(ApfcStepArgs<T> a)
 {
     static_assert(WMAX % G == 0, "groups of whole pencils");
     constexpr int L = PL::L, Tp = PL::Tp, Rmax = PL::Rmax, R0 = PL::first, Rl = PL::last, GW = WMAX / G;
     using PR = typename PL::Reverse;
-    __shared__ cx<T> sh[L * WMAX / G];
+    __shared__ cx<T> sh[pencil_slot<LP>(L) * WMAX / G];
     const int tid = threadIdx.x, p = tid % WMAX, t = tid / WMAX, grp = p / GW;
-    const int64_t bid = blockIdx.x;
+    const int64_t bid = LP ? xcd_tile_order(blockIdx.x, gridDim.x, a.xg) : blockIdx.x;
     const int f = (int)(bid / a.tiles);
     const int64_t col = (bid - (int64_t)f * a.tiles) * a.W + p;
     const bool valid = p < a.W && col < a.ncols;
     const int64_t base = (int64_t)f * a.fstride + (valid ? col : 0);
     auto at = [&](cx<T> *g, int e) -> cx<T> * { return g + base + (int64_t)e * a.ncols; };
-    auto lds = [&](int e) -> cx<T> & { return sh[e * GW + p % GW]; };
+    auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * GW + p % GW]; };
 
     cx<T> spre[PF ? Rmax : 1];
     if constexpr (PF) {

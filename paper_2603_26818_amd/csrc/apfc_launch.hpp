@@ -27,8 +27,8 @@ struct ApfcStepArgs {
     const cx<T> *src;  // FFT(N_f) along every other axis
     cx<T> *dst;        // inverse FFT along this axis of the new state (may be src)
     cx<T> *state;      // spectra of the amplitudes, updated in place
-    int64_t ncols, nx, n1, fstride, tiles;  // tiles (column tiles per field) and W: set by the launcher
-    int W;
+    int64_t ncols, nx, n1, fstride, tiles;  // tiles (column tiles per field), W, xg: set by the launcher
+    int W, xg;  // (xg: workgroups per line of narrow tiles)
     T fk[3];  // 2 pi / (n dx) per axis (axis 0, axis 1 (3D), x)
     T dt, dB, Bx;
     T kv[kApfcMaxFields][3];  // k_f along (axis 0, axis 1, x); axis 1 is 0 in 2D
@@ -44,10 +44,19 @@ template <typename T>
 hipError_t launch_apfc_nonlin(const cx<T> *eta, cx<T> *out, int64_t P, int nf, const ApfcTerm *terms, const int *off,
                               double c3, hipStream_t s);
 
-// FFT (dir -1 forward, +1 inverse) of nrows contiguous rows of length L, times scale.
+// FFT (dir -1 forward, +1 inverse) of nrows contiguous rows of length L, times scale; lat: on the schedule of
+// launch_apfc_x (L a power of two).
 template <typename T>
 hipError_t launch_apfc_rows(int64_t L, const cx<T> *in, cx<T> *out, int64_t nrows, int dir, double scale, bool nt,
-                            const cx<T> *tw, int lt_shift, hipStream_t s);
+                            bool lat, const cx<T> *tw, int lt_shift, hipStream_t s);
+
+// out_f = x FFT of N_f for nf fields of nrows rows of length L (P points each): first, of the amplitudes `in`;
+// else of the inverse x FFT of `in`, times scale.  Where apfc_x_ok says so.
+template <typename T>
+hipError_t launch_apfc_x(int64_t L, const cx<T> *in, cx<T> *out, int64_t nrows, int64_t P, int nf, const ApfcTerm *terms,
+                         const int *off, double c3, bool first, double scale, const cx<T> *tw, int lt_shift, hipStream_t s);
+template <typename T>
+bool apfc_x_ok(int64_t L, int nf);
 
 // Fused last-axis pass (length L) over nf fields.
 template <typename T>

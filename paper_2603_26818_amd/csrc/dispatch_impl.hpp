@@ -236,27 +236,27 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw
             return hipErrorInvalidValue;
         } else {
             auto run = [&](auto pic, auto pfc, auto latc) -> hipError_t {
-            using PLI = decltype(pic);
-            using PLF = decltype(pfc);
-            if constexpr (!XStepFused<PLI, PLF>::ok) {
-                return hipErrorInvalidValue;
-            } else {
-                constexpr int R = XFused<PLI, PLF, 64>::R;
-                const dim3 grid((unsigned)cdiv(g.xrows, R)), block(64);
-                const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-                // ordinary loads and stores: non-temporal hints (as the separate x passes take them)
-                // measured 1.3 % slower per 512^3 FP32 step, the same in FP64.  Padded LDS rows
-                // (power-of-two M): FP64 steps 438 against 431 steps/s at 512^3, 2768 against 2671
-                // at 256^3; FP32 even.
-                constexpr bool LAT = decltype(latc)::value;
-                if (real)
-                    hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT, true>), grid, block, 0, s,
-                                       data, real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
-                else
-                    hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT>), grid, block, 0, s, data,
-                                       real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
-                return hipGetLastError();
-            }
+                using PLI = decltype(pic);
+                using PLF = decltype(pfc);
+                if constexpr (!XStepFused<PLI, PLF>::ok) {
+                    return hipErrorInvalidValue;
+                } else {
+                    constexpr int R = XFused<PLI, PLF, 64>::R;
+                    const dim3 grid((unsigned)cdiv(g.xrows, R)), block(64);
+                    const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
+                    // ordinary loads and stores: non-temporal hints (as the separate x passes take them)
+                    // measured 1.3 % slower per 512^3 FP32 step, the same in FP64.  Padded LDS rows
+                    // (power-of-two M): FP64 steps 438 against 431 steps/s at 512^3, 2768 against 2671
+                    // at 256^3; FP32 even.
+                    constexpr bool LAT = decltype(latc)::value;
+                    if (real)
+                        hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT, true>), grid, block, 0, s,
+                                           data, real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
+                    else
+                        hipLaunchKernelGGL((x_c2r_r2c_kernel<T, PLI, PLF, 64, false, is_pow2c(M), LAT>), grid, block, 0, s, data,
+                                           real, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
+                    return hipGetLastError();
+                }
             };
             if (g.ndim == 2) return run(typename X2InvPlan<M>::type{}, typename X2FwdPlan<M>::type{}, std::true_type{});
             return run(typename XInvPlan<M>::type{}, typename XFwdPlan<M>::type{}, std::false_type{});

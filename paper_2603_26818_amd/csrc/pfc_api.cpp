@@ -1719,7 +1719,7 @@ pfc_status do_apfc_fft(pfc_apfc *p, const void *in_v, void *out_v, int dir, hipS
     const int64_t rows = (int64_t)N * p->n0 * p->n1;
     const pfc::Geom gy = apfc_y_geom(p), gl = apfc_last_geom(p);
     if (dir < 0) {
-        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, in, out, rows, -1, 1.0, p->nt, tw + p->tw_x, p->lt_shift, s),
+        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, in, out, rows, -1, 1.0, p->nt, false, tw + p->tw_x, p->lt_shift, s),
                 "x forward launch");
         if (p->d.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(gy, out, -1, tw, s), "y forward launch");
         for (int f = 0; f < N; ++f)
@@ -1728,7 +1728,7 @@ pfc_status do_apfc_fft(pfc_apfc *p, const void *in_v, void *out_v, int dir, hipS
         for (int f = 0; f < N; ++f)
             PFC_TRY(pfc::launch_last_c2c<T>(gl, in + f * p->P, out + f * p->P, +1, tw, s), "last-axis inverse launch");
         if (p->d.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(gy, out, +1, tw, s), "y inverse launch");
-        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, out, out, rows, +1, 1.0 / (double)p->P, p->nt, tw + p->tw_x,
+        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, out, out, rows, +1, 1.0 / (double)p->P, p->nt, false, tw + p->tw_x,
                                          p->lt_shift, s),
                 "x inverse launch");
     }
@@ -1778,17 +1778,28 @@ pfc_status do_apfc_step(pfc_apfc *p, void *eta_v, void *eta_hat_v, int64_t nstep
     }
     a.tw = tw + p->tw_last;
     a.lt_shift = p->lt_shift;
+    // the x passes and the nonlinearity between them in one kernel where the geometry has it
+    const bool fused = pfc::apfc_x_ok<T>(p->nx, N);
+    const double inv = 1.0 / (double)p->P;
+    const pfc::ApfcTerm *terms = reinterpret_cast<const pfc::ApfcTerm *>(p->ws + p->terms_off);
+    const int *off = reinterpret_cast<const int *>(p->ws + p->off_off);
     for (int64_t st = 0; st < nsteps; ++st) {
-        pfc_status e = do_apfc_nonlinear<T>(p, eta, scr, s);
-        if (e) return e;
-        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, scr, scr, rows, -1, 1.0, p->nt, tw + p->tw_x, p->lt_shift, s),
-                "x forward launch");
+        if (fused) {
+            PFC_TRY(pfc::launch_apfc_x<T>(p->nx, st == 0 ? eta : scr, scr, p->n0 * p->n1, p->P, N, terms, off, 3.0 * d.v,
+                                          st == 0, inv, tw + p->tw_x, p->lt_shift, s),
+                    "x pass launch");
+        } else {
+            pfc_status e = do_apfc_nonlinear<T>(p, eta, scr, s);
+            if (e) return e;
+            PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, scr, scr, rows, -1, 1.0, p->nt, false, tw + p->tw_x, p->lt_shift, s),
+                    "x forward launch");
+        }
         if (d.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(gy, scr, -1, tw, s), "y forward launch");
         PFC_TRY(pfc::launch_apfc_last_step<T>(p->n0, N, a, s), "last-axis step launch");
         if (d.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(gy, scr, +1, tw, s), "y inverse launch");
-        PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, scr, eta, rows, +1, 1.0 / (double)p->P, p->nt, tw + p->tw_x,
-                                         p->lt_shift, s),
-                "x inverse launch");
+        if (!fused || st + 1 == nsteps)
+            PFC_TRY(pfc::launch_apfc_rows<T>(p->nx, scr, eta, rows, +1, inv, p->nt, fused, tw + p->tw_x, p->lt_shift, s),
+                    "x inverse launch");
     }
     return PFC_OK;
 }
