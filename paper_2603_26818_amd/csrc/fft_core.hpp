@@ -511,6 +511,11 @@ template <> struct Last2Cands<128> { using type = PlanList<Radices<4, 4, 8>, Rad
 template <> struct Last2Cands<256> { using type = PlanList<Radices<4, 8, 8>, Radices<4, 8, 8>, Radices<16, 16>>; };
 template <> struct Last2Cands<512> { using type = PlanList<Radices<8, 8, 8>, Radices<16, 16, 2>, Radices<2, 16, 16>>; };
 
+// 700, 750 and 1400 in 2D: the 3D radices over more threads, at most 10, 15 and 14 elements each
+template <> struct Last2Cands<700> { using type = PlanList<Radices<7, 10, 10, 100>, Radices<7, 10, 10, 50>>; };
+template <> struct Last2Cands<750> { using type = PlanList<Radices<15, 10, 5, 75>, Radices<15, 10, 5, 50>>; };
+template <> struct Last2Cands<1400> { using type = PlanList<Radices<14, 10, 10, 140>, Radices<14, 10, 10, 50>>; };
+
 // The radix schedule of a candidate (a Tiled candidate's own; the default candidate's schedule is
 // what the other kernels of a length take, with the length's default tile)
 template <class C, class = void>
