@@ -158,6 +158,8 @@ hipError_t launch_x_r2c(const Geom &g, const T *in, cx<T> *out, bool cube, const
             };
             using C2 = typename X2FwdCands<M>::type;
             using C3 = typename XFwdCands<M>::type;
+            if constexpr (sizeof(T) == 4)
+                if (!cube && g.init) return run(typename InitXPlan<M>::type{}, std::false_type{});
             if (!cube)
                 return with_cands<PlanList<typename ListAt<0, C2>::type>, PlanList<typename ListAt<0, C3>::type>>(
                     g, 0, [&](auto plc) { return run(plc, std::false_type{}); });
@@ -334,7 +336,7 @@ hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hi
         if constexpr (L < 4) {
             return hipErrorInvalidValue;
         } else {
-            return with_plan<typename AxisCands<L>::type>(variant, [&](auto plc) -> hipError_t {
+            auto run = [&](auto plc) -> hipError_t {
                 using TO = TileOf<T, decltype(plc)>;
                 using TL = typename TO::tile;
                 using PL = SpreadIf<typename TO::plan, TL::E>;
@@ -375,7 +377,11 @@ hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hi
                                            data, W, g.M, am, tiles, tw + g.tw_y, g.lt_shift, xg);
                     return hipGetLastError();
                 });
-            });
+            };
+            // the state set-up: a mixed length's own schedule in the tile of its default candidate
+            if constexpr (sizeof(T) == 4 && !is_pow2c(L))
+                if (g.init && dir < 0) return run(InitTile<typename ListAt<0, typename AxisCands<L>::type>::type, typename InitAxisPlan<L>::type>{});
+            return with_plan<typename AxisCands<L>::type>(variant, run);
         }
     });
 }
@@ -417,14 +423,23 @@ hipError_t launch_last_c2c(const Geom &g, const cx<T> *src, cx<T> *dst, int dir,
                 return hipGetLastError();
             };
             using PL = typename AxisPlan<L>::type;
+            auto forward = [&](auto plc) -> hipError_t {
+                using PF = decltype(plc);
+                if (!z_steps_ok<PF>(g.zs)) return hipErrorInvalidValue;
+                hipLaunchKernelGGL((axis_c2c_kernel<T, PF, WM, -1>), dim3((unsigned)tiles), dim3(WM * PF::Tp), 0, s, src, dst,
+                                   W, ncols, am, tiles, tw + g.tw_last, g.lt_shift, 1);
+                return hipGetLastError();
+            };
+            if constexpr (sizeof(T) == 4)
+                if (g.init && dir < 0) {
+                    using PI = typename InitAxisPlan<L>::type;
+                    return tiles < kFillTiles1 ? narrow(PI{}) : forward(PI{});
+                }
             if (tiles < kFillTiles1) return g.ndim == 2 ? narrow(typename Last2Plan<L>::type{}) : narrow(PL{});
+            if (dir < 0) return forward(PL{});
             if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
             const dim3 grid((unsigned)tiles), block(WM * PL::Tp);
-            if (dir < 0)
-                hipLaunchKernelGGL((axis_c2c_kernel<T, PL, WM, -1>), grid, block, 0, s, src, dst, W, ncols, am, tiles,
-                                   tw + g.tw_last, g.lt_shift, 1);
-            else
-                hipLaunchKernelGGL((axis_c2c_kernel<T, PL, WM, +1>), grid, block, 0, s, src, dst, W, ncols, am, tiles,
+            hipLaunchKernelGGL((axis_c2c_kernel<T, PL, WM, +1>), grid, block, 0, s, src, dst, W, ncols, am, tiles,
                                    tw + g.tw_last, g.lt_shift, 1);
             return hipGetLastError();
         }

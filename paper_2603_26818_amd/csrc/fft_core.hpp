@@ -190,13 +190,14 @@ __device__ __forceinline__ cx<T> rotg(cx<T> a)
 // (k mod p, k mod q), under which the DFT is a DFT_p of DFT_q's without twiddles: 178 additions and
 // multiplications at R = 15 and 92 at R = 10, where decimation in time takes 280 and 124.  Prime powers
 // decimate in time over the prime p: X[k + q s] = sum_r W_p^{r s} W_R^{r k} DFT_q(v[r], v[r + p], ...)[k];
-// a prime R is summed directly.
-template <typename T, int R, int DIR>
+// a prime R is summed directly.  DIT: every composite R decimates in time, over its smallest prime factor
+// (the state set-up's transforms, see Dit).
+template <typename T, int R, int DIR, bool DIT = false>
 __device__ __forceinline__ void dft(cx<T> *v)
 {
     if constexpr (!is_pow2c(R)) {
         constexpr int p = smallest_factor(R), q = R / p, pp = prime_part(R);
-        if constexpr (pp < R) {
+        if constexpr (pp < R && !DIT) {
             constexpr int qq = R / pp;
             cx<T> e[pp][qq];
 #pragma unroll
@@ -251,7 +252,7 @@ __device__ __forceinline__ void dft(cx<T> *v)
             for (int r = 0; r < p; ++r) {
 #pragma unroll
                 for (int j = 0; j < q; ++j) e[r][j] = v[r + p * j];
-                dft<T, q, DIR>(e[r]);
+                dft<T, q, DIR, DIT>(e[r]);
             }
             static_for<0, q>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
@@ -317,6 +318,19 @@ struct Radices {
     using Reverse = std::conditional_t<nst == 1, Radices<A, 1, 1, TP>,
                                        std::conditional_t<nst == 2, Radices<B, A, 1, TP>, Radices<C, B, A, TP>>>;
 };
+
+// The schedule PL with composite radices decimated in time.  FP32 energies hold FP64 sums over a spectrum
+// that FP32 transforms set up, and the biases of its rounded constants show in them at some 1e-8; the
+// transforms of the state set-up therefore keep their arithmetic where a step's passes change theirs.
+template <class PL>
+struct Dit : PL {
+    static constexpr bool dit = true;
+    using Reverse = Dit<typename PL::Reverse>;
+};
+template <class PL, class = void>
+struct IsDit : std::false_type {};
+template <class PL>
+struct IsDit<PL, std::void_t<decltype(PL::dit)>> : std::true_type {};
 
 // Offset of stage s in a table of per-stage blocks (prefix(s) * radix(s) entries each).
 template <class P>
@@ -385,13 +399,30 @@ template <int L>
 struct MixPlan {
     using type = typename DefaultPlan<L>::type;
 };
+// radices of the state set-up's transforms, over any number of threads
+template <int L> struct InitMix { using type = typename DefaultPlan<L>::type; };
+template <> struct InitMix<30> { using type = Radices<10, 3, 1, 5>; };
+template <> struct InitMix<150> { using type = Radices<10, 15, 1, 15>; };
 template <int L>
 struct MixTable {
     using F = typename MixPlan<L>::type;
     using Rv = typename F::Reverse;
+    using In = typename InitMix<L>::type;
     static constexpr int split = stage_blocks_off<F>(F::nst) + stage_blocks_off<Rv>(Rv::nst);
-    static constexpr int size = split + L;  // entries, with the x-pass split twiddles
+    static constexpr int init = split + L;  // after the x-pass split twiddles: InitMix's blocks, where they differ
+    static constexpr int size = init + (same_stages<In, F>() ? 0 : stage_blocks_off<In>(In::nst));  // entries
 };
+// first entry of schedule PL's stage blocks in its length's table
+template <class PL>
+__host__ __device__ constexpr int mix_base()
+{
+    using MT = MixTable<PL::L>;
+    static_assert(same_stages<PL, typename MT::F>() || same_stages<PL, typename MT::Rv>() || same_stages<PL, typename MT::In>(),
+                  "a schedule of a length that is not a power of two takes the stages of its table");
+    return same_stages<PL, typename MT::F>() ? 0
+         : same_stages<PL, typename MT::Rv>() ? stage_blocks_off<typename MT::F>(MT::F::nst)
+                                              : MT::init;
+}
 
 // Candidate schedules per pass kind and length.  Candidate 0 is the default (measured best on
 // MI355X at 512^3 FP32 where the lengths occur there); the autotuner may pick another per plan.
@@ -534,6 +565,17 @@ template <int M> struct X2FwdPlan { using type = typename PlanOf<typename ListAt
 template <int M> struct X2InvPlan { using type = typename PlanOf<typename ListAt<0, typename X2InvCands<M>::type>::type>::type; };
 template <int L> struct Last2Plan { using type = typename PlanOf<typename ListAt<0, typename Last2Cands<L>::type>::type>::type; };
 
+// Schedules of the state set-up's transforms in FP32 (Dit): x rows, and the strided axes
+template <int M> struct InitXPlan {
+    using type = std::conditional_t<is_pow2c(M), typename XFwdPlan<M>::type,
+                                    Dit<std::conditional_t<(M == 30 || M == 150), typename InitMix<M>::type, typename XFwdPlan<M>::type>>>;
+};
+template <> struct InitXPlan<128> { using type = Radices<8, 16>; };
+template <int L> struct InitAxisPlan {
+    using type = std::conditional_t<is_pow2c(L), typename AxisPlan<L>::type,
+                                    Dit<std::conditional_t<(L == 30 || L == 150), typename InitMix<L>::type, typename AxisPlan<L>::type>>>;
+};
+
 // Calls f(PL{}) with the schedule number v of List (v out of range: candidate 0).
 template <class List, int I = 0, class F>
 __host__ __device__ __forceinline__ auto with_plan(int v, F &&f)
@@ -570,11 +612,7 @@ __device__ __forceinline__ void apply_twiddles(cx<T> *v, int jj, const cx<T> *__
 {
     constexpr int R = PL::radix(s), Ns = PL::prefix(s);
     if constexpr (TWM == TW_MIX) {
-        using F = typename MixPlan<PL::L>::type;
-        static_assert(same_stages<PL, F>() || same_stages<PL, typename F::Reverse>(),
-                      "a schedule of a length that is not a power of two takes the stages of its table");
-        constexpr int base = same_stages<PL, F>() ? 0 : stage_blocks_off<F>(F::nst);
-        const cx<T> *st = tw + base + stage_blocks_off<PL>(s) + (unsigned)(jj * R);
+        const cx<T> *st = tw + mix_base<PL>() + stage_blocks_off<PL>(s) + (unsigned)(jj * R);
 #pragma unroll
         for (int r = 1; r < R; ++r) v[r] = cmul(v[r], DIR > 0 ? conj(st[r]) : st[r]);
     } else if constexpr (TWM == TW_STAGE) {
@@ -633,9 +671,7 @@ __device__ __forceinline__ void load_stage_tw(StageTw<T, PL> &o, int t, const cx
             } else {
                 const cx<T> *st;
                 if constexpr (TW == TW_MIX) {
-                    using F = typename MixPlan<PL::L>::type;
-                    static_assert(same_stages<PL, F>() || same_stages<PL, typename F::Reverse>(), "stages of the table");
-                    st = tw + (same_stages<PL, F>() ? 0 : stage_blocks_off<F>(F::nst)) + stage_blocks_off<PL>(s) + jj * R;
+                    st = tw + mix_base<PL>() + stage_blocks_off<PL>(s) + jj * R;
                 } else {
                     st = tw + (1u << lt_shift) + stage_tw_offset(Ns * R, R) + (unsigned)(jj * R);
                 }
@@ -670,7 +706,7 @@ __device__ __forceinline__ void fft_stages(cx<T> *v, int t, Lds &&lds, const cx<
         constexpr int B = PL::nb(R);
         constexpr int Ns = PL::prefix(s);
 #pragma unroll
-        for (int b = 0; b < B; ++b) dft<T, R, DIR>(&v[b * R]);  // (absent butterflies: unused values)
+        for (int b = 0; b < B; ++b) dft<T, R, DIR, IsDit<PL>::value>(&v[b * R]);  // (absent butterflies: unused values)
         if constexpr (s + 1 < PL::nst) {
             // exchange, then the next stage's inputs and twiddles
             constexpr int R2 = PL::radix(s + 1);

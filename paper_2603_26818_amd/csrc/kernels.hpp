@@ -612,6 +612,18 @@ struct TileOf<T, C, std::void_t<typename C::plan>> {
     using plan = typename C::plan;
 };
 
+// Schedule PL in the tile of candidate C, as a candidate.
+template <class C, class PL, class = void>
+struct InitTiled : PL {};
+template <class C, class PL>
+struct InitTiled<C, PL, std::void_t<typename C::plan>> {
+    using plan = PL;
+    static constexpr int L = PL::L, seg_bytes = C::seg_bytes, elems = C::elems, groups = C::groups;
+    static constexpr bool prefetch = C::prefetch;
+};
+template <class C, class PL>
+using InitTile = std::conditional_t<std::is_same_v<typename PlanOf<C>::type, C>, PL, InitTiled<C, PL>>;
+
 // ------------------------------------------------------------------------------------------------
 // Workgroup order for column tiles narrower than a 128-byte line.  Consecutive workgroups are
 // dispatched to the 8 XCDs in turn, so workgroups b, b + 8, ..., b + 8 (G - 1) share one XCD and

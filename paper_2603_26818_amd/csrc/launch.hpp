@@ -26,6 +26,7 @@ struct Geom {
     int64_t Mp = 0;
     int zs = 0, cs = 0;
     int xnat = 0;  // x passes in natural row order
+    bool init = false;  // forward transforms of the state set-up (InitXPlan, InitAxisPlan in FP32)
 };
 
 // The Pack of a geometry.

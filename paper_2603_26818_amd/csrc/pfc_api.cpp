@@ -232,6 +232,7 @@ void fill_mix_table(cx<T> *out)
     blocks(typename MT::F{}, 0);
     blocks(typename MT::Rv{}, pfc::stage_blocks_off<typename MT::F>(MT::F::nst));
     for (int k = 0; k < L; ++k) out[MT::split + k] = unit_root<T>(k, 2 * (int64_t)L);
+    if (MT::size > MT::init) blocks(typename MT::In{}, MT::init);
 }
 // calls f(std::integral_constant<int, L>) for a supported non-power-of-two length
 template <class F>
@@ -403,9 +404,11 @@ template <typename T>
 pfc_status do_state_init(pfc_plan *p, const void *psi0, void *state, hipStream_t s)
 {
     const Bufs<T> b = bufs<T>(p);
-    pfc_status st = fwd_xy<T>(p, (const T *)psi0, false, b.scratch, s);
-    if (st) return st;
-    PFC_TRY(pfc::launch_last_fwd<T>(p->g, b.scratch, (cx<T> *)state, b.tw, s), "last-axis launch");
+    Geom g = p->g;
+    g.init = true;
+    PFC_TRY(pfc::launch_x_r2c<T>(g, (const T *)psi0, b.scratch, false, b.tw, s), "x_r2c launch");
+    if (g.ndim == 3) PFC_TRY(pfc::launch_y_c2c<T>(g, b.scratch, -1, b.tw, s), "y forward launch");
+    PFC_TRY(pfc::launch_last_fwd<T>(g, b.scratch, (cx<T> *)state, b.tw, s), "last-axis launch");
     const int64_t ntot = p->g.n0 * p->g.nrows * p->g.nx;
     PFC_TRY(pfc::launch_set_mass<T>((const T *)psi0, ntot, b.partial, (cx<T> *)state, s), "mass launch");
     return PFC_OK;
@@ -895,6 +898,7 @@ pfc_status batch_state_init_impl(pfc_batch *b, hipStream_t s)
         g.xrows = in.n0;
         g.lt_shift = b->lt_shift;
         g.nt = false;
+        g.init = true;
         g.tw_x = g.tw_y = g.tw_last = 0;
         cx<T> *scratch = (cx<T> *)(b->ws + b->scratch_off[i]);
         PFC_TRY(pfc::launch_x_r2c<T>(g, (const T *)b->psi[i], scratch, false, tw, s), "x_r2c launch");
