@@ -69,7 +69,7 @@ def bench_batched(nsteps):
     b = pfc.Batch(insts).bind(psis)
     b.state_init()
     variants, tuned_ms = b.autotune(steps=5)  # radix schedules (and item shapes) per pass and length
-    b.step(nsteps)  # captures the graph for this nsteps and warms up
+    b.step(nsteps)  # warm-up
     b.check()
     stream = torch.cuda.current_stream()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -94,7 +94,7 @@ def bench_batched(nsteps):
     ms_sep = e0.elapsed_time(e1) / ref_steps
     return {"workload": "48 2D runs {128^2,256^2,512^2,1024^2}x12, one-/two-mode, FP32, dt=0.25", "steps": nsteps,
             "ms": round(ms, 3), "batch_steps_per_s": round(1000.0 * nsteps / ms, 1),
-            "points_per_step": pts, "alg_gbps": round(32.0 * pts * nsteps / ms / 1e6, 1),
+            "points_per_step": pts, "alg_gbps": round((24.0 + 8.0 / nsteps) * pts * nsteps / ms / 1e6, 1),
             "grid_workgroups": b.grid, "autotuned_variants_by_size": {
                 f"{d['shape'][0]}^2": v for d, v in zip(insts, variants)},
             "separate_launches_ms_per_step": round(ms_sep, 4),
@@ -103,9 +103,9 @@ def bench_batched(nsteps):
 
 def bench_hydro(nsteps, n=512, seed=9):
     """Hydrodynamic PFC (density + 3 velocity components) at n^3 FP32, rho0 = gamma = a0 = 1,
-    r = -0.30, dt = 0.25: ms per step and algorithmic GB/s on the 480 B/point pass model (120 reads
-    or writes of 4 B per point, a packed spectrum or a real field: 16 transforms, the 6 derivatives
-    applied inside the last-axis inverse passes, 5 pointwise updates)."""
+    r = -0.30, dt = 0.25: ms per step and algorithmic GB/s on the pass model of the merged passes, 75
+    reads or writes of 4 B per point (a packed spectrum or a real field) per step and 4 more per call
+    (the first step transforms psi^3 itself)."""
     import torch
 
     import paper_2603_26818_amd as pfc
@@ -130,7 +130,7 @@ def bench_hydro(nsteps, n=512, seed=9):
     finite = bool(torch.isfinite(psi).all().item()) and bool(torch.isfinite(v).all().item())
     del psi, v, S, V, work, plan
     torch.cuda.empty_cache()
-    alg = 480.0 * n**3
+    alg = 4.0 * (75.0 + 4.0 / nsteps) * n**3
     return {"workload": f"3D hydrodynamic PFC {n}^3 FP32 (psi + 3 velocity components), rho0=gamma=a0=1, r=-0.30, "
                         f"dt=0.25, seed {seed}", "steps": nsteps, "ms_per_step": round(ms, 3),
             "steps_per_s": round(1000.0 / ms, 2), "alg_gbps": round(alg / ms / 1e6, 1),
@@ -140,9 +140,9 @@ def bench_hydro(nsteps, n=512, seed=9):
 def bench_amplitude(nsteps, shape=(256, 256, 256), lattice="bcc", seed=7):
     """Complex-amplitude form: the amplitudes of a lattice (6 bcc amplitudes on 256^3, or 3
     triangular ones on 2048^2), FP32 (dB = -0.15, Bx = 1, t = 0.3, v = 1, dt = 0.5, dx = pi/2),
-    amplitudes 0.1 + U(-0.05, 0.05) (1 + i).  Algorithmic bytes per step: 14 (3D) or 10 (2D) reads or
-    writes of the complex fields (nonlinearity, x forward, y forward in 3D, the fused last axis
-    twice each way, y inverse in 3D, x inverse)."""
+    amplitudes 0.1 + U(-0.05, 0.05) (1 + i).  Algorithmic reads or writes of the complex fields: 4 per
+    step for the fused last axis, 4 more for y in 3D, and for x and the nonlinearity 2 per step and 2
+    per call where they are one pass (rows of at most 1024 points), else 6 per step."""
     import torch
 
     import paper_2603_26818_amd as pfc
@@ -167,7 +167,8 @@ def bench_amplitude(nsteps, shape=(256, 256, 256), lattice="bcc", seed=7):
     finite = bool(torch.isfinite(torch.view_as_real(eta)).all().item())
     del eta, S, obj
     torch.cuda.empty_cache()
-    alg = (14.0 if len(shape) == 3 else 10.0) * len(k) * npts * 8
+    x_units = 2.0 + 2.0 / nsteps if shape[-1] <= 1024 else 6.0
+    alg = ((8.0 if len(shape) == 3 else 4.0) + x_units) * len(k) * npts * 8
     dims = "x".join(str(v) for v in shape)
     return {"workload": f"complex-amplitude PFC, {len(k)} {lattice} amplitudes on {dims}, FP32, dB=-0.15 Bx=1 "
                         f"t=0.3 v=1, dt=0.5, seed {seed}", "steps": nsteps, "ms_per_step": round(ms, 3),
