@@ -49,8 +49,8 @@ __global__ __launch_bounds__(XInvRows<PL>::value *PL::Tp) void batch_x_inv_kerne
 }
 
 template <typename T, class PLI, class PLF>
-__global__ __launch_bounds__(64) void batch_x_fused_kernel(const BatchInst<T> *inst, const cx<T> *__restrict__ tw,
-                                                           int lt_shift)
+__global__ __launch_bounds__((XFused<PLI, PLF, 64>::threads)) void
+batch_x_fused_kernel(const BatchInst<T> *inst, const cx<T> *__restrict__ tw, int lt_shift)
 {
     __shared__ cx<T> sh[XFused<PLI, PLF, 64>::R * XPitch<T, PLI::L, true>::value];
     const BatchInst<T> &in = inst[blockIdx.y];
@@ -178,7 +178,8 @@ hipError_t launch_batch_x(const BatchGroup &g, int pass, const BatchInst<T> *tab
                     using PLF = decltype(pf);
                     using XF = XFused<PLI, PLF, 64>;
                     static_assert(XF::ok, "both schedules fill one wavefront");
-                    hipLaunchKernelGGL((batch_x_fused_kernel<T, PLI, PLF>), grid(XF::R), dim3(64), 0, s, inst, tw, lt_shift);
+                    hipLaunchKernelGGL((batch_x_fused_kernel<T, PLI, PLF>), grid(XF::R), dim3(XF::threads), 0, s, inst, tw,
+                                       lt_shift);
                     return hipGetLastError();
                 });
             });

@@ -243,8 +243,8 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw
                 if constexpr (!XStepFused<PLI, PLF>::ok) {
                     return hipErrorInvalidValue;
                 } else {
-                    constexpr int R = XFused<PLI, PLF, 64>::R;
-                    const dim3 grid((unsigned)cdiv(g.xrows, R)), block(64);
+                    using F = XFused<PLI, PLF, 64>;
+                    const dim3 grid((unsigned)cdiv(g.xrows, F::R)), block(F::threads);
                     const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
                     // ordinary loads and stores: non-temporal hints (as the separate x passes take them)
                     // measured 1.3 % slower per 512^3 FP32 step, the same in FP64.  Padded LDS rows
@@ -286,8 +286,8 @@ hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T
                     const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
                     const AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial, add ? 1 : 0};
                     hipLaunchKernelGGL((x_adj_r2c_kernel<T, PLI, PLF, is_pow2c(M), decltype(latc)::value>),
-                                       dim3((unsigned)*nblocks), dim3(64), 0, s, data, g.xrows, tw + g.tw_x, g.lt_shift, sc, ea,
-                                       pack_of(g));
+                                       dim3((unsigned)*nblocks), dim3(XFused<PLI, PLF, 64>::threads), 0, s, data, g.xrows,
+                                       tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
                     return hipGetLastError();
                 }
             };

@@ -306,11 +306,12 @@ __device__ __forceinline__ void hydro_stage(const cx<T> *v, int t, cx<T> *rowlds
 }
 
 // x passes of one wavefront per workgroup (XFused<PLI, PLF, 64>::R rows in padded LDS rows, as the fused
-// pass of the plain step); a workgroup reads its rows before it writes them.
+// pass of the plain step); a workgroup reads its rows before it writes them.  It is XFused::threads threads:
+// 64 but for rows of 750 points, whose 25 threads each leave 14 lanes of the wavefront without a row.
 // out = x r2c of sum_j w[j] field_j over NC components.
 template <typename T, class PLI, class PLF, int NC>
-__global__ __launch_bounds__(64) void hydro_adv_x_kernel(HydroFlow<T> f, int64_t nrows, const cx<T> *__restrict__ tw,
-                                                         int lt_shift, T sc, Pack pk)
+__global__ __launch_bounds__((XFused<PLI, PLF, 64>::threads)) void
+hydro_adv_x_kernel(HydroFlow<T> f, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift, T sc, Pack pk)
 {
     using F = XFused<PLI, PLF, 64>;
     static_assert(F::ok && PLI::L == PLF::L, "schedules must share the workgroup");
@@ -343,9 +344,9 @@ __global__ __launch_bounds__(64) void hydro_adv_x_kernel(HydroFlow<T> f, int64_t
 
 // spec = x r2c of wt * (x c2r of spec; DX: of i k_x spec), in place
 template <typename T, class PLI, class PLF, bool DX>
-__global__ __launch_bounds__(64) void hydro_force_x_kernel(cx<T> *spec, const T *wt, int64_t nrows,
-                                                           const cx<T> *__restrict__ tw, int lt_shift, T sc, Pack pk,
-                                                           double fkx)
+__global__ __launch_bounds__((XFused<PLI, PLF, 64>::threads)) void
+hydro_force_x_kernel(cx<T> *spec, const T *wt, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift, T sc,
+                     Pack pk, double fkx)
 {
     using F = XFused<PLI, PLF, 64>;
     static_assert(F::ok && PLI::L == PLF::L, "schedules must share the workgroup");
@@ -371,8 +372,9 @@ __global__ __launch_bounds__(64) void hydro_force_x_kernel(cx<T> *spec, const T 
 
 // real = x c2r of in, out = x r2c of real^3
 template <typename T, class PLI, class PLF>
-__global__ __launch_bounds__(64) void hydro_psi_x_kernel(const cx<T> *in, T *real, cx<T> *out, int64_t nrows,
-                                                         const cx<T> *__restrict__ tw, int lt_shift, T sc, Pack pk)
+__global__ __launch_bounds__((XFused<PLI, PLF, 64>::threads)) void
+hydro_psi_x_kernel(const cx<T> *in, T *real, cx<T> *out, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift,
+                   T sc, Pack pk)
 {
     constexpr bool PAD = is_pow2c(PLI::L);
     __shared__ cx<T> sh[XFused<PLI, PLF, 64>::R * XPitch<T, PLI::L, PAD>::value];
@@ -502,7 +504,7 @@ hipError_t launch_hydro_x(const Geom &g, const HydroFlow<T> &fl, const cx<T> *tw
         return with_x_plans<true>(g, [&](auto pic, auto pfc) -> hipError_t {
             using PLI = decltype(pic);
             using PLF = decltype(pfc);
-            const dim3 grid((unsigned)cdiv(g.xrows, XFused<PLI, PLF, 64>::R)), block(64);
+            const dim3 grid((unsigned)cdiv(g.xrows, XFused<PLI, PLF, 64>::R)), block(XFused<PLI, PLF, 64>::threads);
             if (g.ndim == 3)
                 hipLaunchKernelGGL((hydro_adv_x_kernel<T, PLI, PLF, 3>), grid, block, 0, s, fl, g.xrows, twx, g.lt_shift, sc, pk);
             else
@@ -514,7 +516,7 @@ hipError_t launch_hydro_x(const Geom &g, const HydroFlow<T> &fl, const cx<T> *tw
     return with_x_plans<false>(g, [&](auto pic, auto pfc) -> hipError_t {
         using PLI = decltype(pic);
         using PLF = decltype(pfc);
-        const dim3 grid((unsigned)cdiv(g.xrows, XFused<PLI, PLF, 64>::R)), block(64);
+        const dim3 grid((unsigned)cdiv(g.xrows, XFused<PLI, PLF, 64>::R)), block(XFused<PLI, PLF, 64>::threads);
         for (int j = 0; j < g.ndim; ++j) {
             if (j + 1 < g.ndim)
                 hipLaunchKernelGGL((hydro_force_x_kernel<T, PLI, PLF, false>), grid, block, 0, s, fl.spec[j], fl.w[0], g.xrows,
@@ -537,8 +539,9 @@ hipError_t launch_hydro_psi_x(const Geom &g, const cx<T> *in, T *real, cx<T> *ou
         using PLI = decltype(pic);
         using PLF = decltype(pfc);
         const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
-        hipLaunchKernelGGL((hydro_psi_x_kernel<T, PLI, PLF>), dim3((unsigned)cdiv(g.xrows, XFused<PLI, PLF, 64>::R)), dim3(64),
-                           0, s, in, real, out, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
+        using F = XFused<PLI, PLF, 64>;
+        hipLaunchKernelGGL((hydro_psi_x_kernel<T, PLI, PLF>), dim3((unsigned)cdiv(g.xrows, F::R)), dim3(F::threads), 0, s, in,
+                           real, out, g.xrows, tw + g.tw_x, g.lt_shift, sc, pack_of(g));
         return hipGetLastError();
     });
 }

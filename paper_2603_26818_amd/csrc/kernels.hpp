@@ -457,8 +457,10 @@ struct XFused {
     static constexpr bool ok = RI * PLI::Tp == RF * PLF::Tp && R % RI == 0 && R % RF == 0;
 };
 // One block of R rows (block index `bid`) of packed spectra in the layout `pk`; `sh` holds
-// R XPitch<T, M, PAD> LDS slots; NTH threads.  In place (in == out) is safe: the block reads all its
-// rows before it writes.  STORE: the field in between is also stored, to `real`.
+// R XPitch<T, M, PAD> LDS slots; exactly XFused<PLI, PLF, NTH>::threads threads (fewer than NTH where the
+// threads per row do not divide it: a thread past them would take a row of the next workgroup).  In place
+// (in == out) is safe: the block reads all its rows before it writes.  STORE: the field in between is also
+// stored, to `real`.
 template <typename T, class PLI, class PLF, int NTH, bool NT = false, bool PAD = false, bool LAT = false, bool STORE = false>
 __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int64_t nrows,
                                                 const cx<T> *__restrict__ tw, int lt_shift, T sc, int64_t bid,
@@ -488,12 +490,12 @@ __device__ __forceinline__ void x_c2r_r2c_block(const cx<T> *in, cx<T> *out, int
                                                              sh + s * F::RF * LD, pk, tid, &pref);
 }
 
-// The fused x pass of the single-plan step between two steps: one workgroup of NTH threads (one
-// wavefront in the step) takes XFused<PLI, PLF, NTH>::R rows of the packed spectrum, in place.
+// The fused x pass of the single-plan step between two steps: one workgroup of XFused::threads threads
+// (one wavefront in the step) takes XFused<PLI, PLF, NTH>::R rows of the packed spectrum, in place.
 // STORE: the field in between is also stored, to `real`.
 template <typename T, class PLI, class PLF, int NTH, bool NT, bool PAD, bool LAT = false, bool STORE = false>
-__global__ __launch_bounds__(NTH) void x_c2r_r2c_kernel(cx<T> *data, T *real, int64_t nrows, const cx<T> *__restrict__ tw,
-                                                        int lt_shift, T sc, Pack pk)
+__global__ __launch_bounds__((XFused<PLI, PLF, NTH>::threads)) void
+x_c2r_r2c_kernel(cx<T> *data, T *real, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift, T sc, Pack pk)
 {
     __shared__ cx<T> sh[XFused<PLI, PLF, NTH>::R * XPitch<T, PLI::L, PAD>::value];
     x_c2r_r2c_block<T, PLI, PLF, NTH, NT, PAD, LAT, STORE>(data, data, nrows, tw, lt_shift, sc, blockIdx.x, sh, pk,
@@ -504,11 +506,11 @@ __global__ __launch_bounds__(NTH) void x_c2r_r2c_kernel(cx<T> *data, T *real, in
 // next one starts with, one wavefront per workgroup as above; lambda_n itself is not stored.  mu and the
 // output spectrum are `data`.
 template <typename T, class PLI, class PLF, bool PAD, bool LAT>
-__global__ __launch_bounds__(64) void x_adj_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift,
-                                                       T sc, AdjEpi<T> ea, Pack pk)
+__global__ __launch_bounds__((XFused<PLI, PLF, 64>::threads)) void
+x_adj_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw, int lt_shift, T sc, AdjEpi<T> ea, Pack pk)
 {
     using F = XFused<PLI, PLF, 64>;
-    constexpr int LD = XPitch<T, PLI::L, PAD>::value, M = PLI::L;
+    constexpr int LD = XPitch<T, PLI::L, PAD>::value;
     constexpr bool PRE = LAT && preload_tw<T, PLI>() && preload_tw<T, PLF>();
     __shared__ cx<T> sh[F::R * LD];
     XTw<T, PLI> prei;
