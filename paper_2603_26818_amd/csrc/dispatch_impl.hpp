@@ -107,7 +107,7 @@ static inline int even_width(int w) { return w > 1 ? (w & ~1) : w; }
 
 // Workgroups per 128-byte line for column tiles of W complex values (1 for whole-line tiles).
 template <typename T>
-static int line_group(int W)
+__host__ __device__ constexpr int line_group(int W)
 {
     const int bytes = W * (int)sizeof(cx<T>);
     return bytes >= 128 ? 1 : 128 / bytes;

@@ -146,13 +146,21 @@ hipError_t launch_accumulate(const double *partial, int np, double coef, double 
 struct BatchGroup {
     int n0, M, vx, vy, vc, first, count;
 };
+// Small groups of one class of y lengths share their launches: at most 4 y lengths with 6 of x.  The class of
+// a group, 0 where it has launches of its own.
+constexpr int kBatchUnitGroups = 24;
+template <typename T>
+int batch_y_class(const BatchGroup &g);
 enum { BATCH_X_FWD = 0, BATCH_X_INV = 1, BATCH_X_FUSED = 2 };  // x r2c with the cube, x c2r, both between steps
+// one pass of the unit g[0 .. ng): a group, or groups of one class
 template <typename T>
-hipError_t launch_batch_x(const BatchGroup &g, int pass, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
+hipError_t launch_batch_x(const BatchGroup *g, int ng, int pass, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
                           hipStream_t s);
-// y forward, update, y inverse; the workgroups of that launch
+// y forward, update, y inverse
 template <typename T>
-hipError_t launch_batch_y(const BatchGroup &g, const BatchInst<T> *table, const cx<T> *tw, int lt_shift, hipStream_t s);
+hipError_t launch_batch_y(const BatchGroup *g, int ng, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
+                          hipStream_t s);
+// workgroups of a group's y pass
 template <typename T>
 int64_t batch_y_workgroups(const BatchGroup &g);
 constexpr int kBatchMaxInstHost = 256;

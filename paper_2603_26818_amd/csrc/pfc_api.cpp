@@ -58,10 +58,11 @@ struct pfc_batch {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     std::vector<void *> psi, state;
-    // groups of instances (BatchGroup), split over the caller's stream ([0]) and one of the batch's own
-    // ([1]), which starts after the caller's earlier work and which the caller's stream then waits for
-    std::vector<pfc::BatchGroup> groups[2];
-    int64_t side_load = 0;  // points' worth of a step of groups[1]
+    // units (groups of instances that share their launches), split over the caller's stream ([0]) and one
+    // of the batch's own ([1]), which starts after the caller's earlier work and which the caller's stream
+    // then waits for
+    std::vector<std::vector<pfc::BatchGroup>> units[2];
+    int64_t side_load = 0;  // points' worth of a step of units[1]
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };
@@ -815,15 +816,29 @@ pfc_status batch_upload_table(pfc_batch *b)
     }
     PFC_TRY(hipMemcpy(b->ws + b->inst_off, table.data(), table.size() * sizeof(table[0]), hipMemcpyHostToDevice),
             "instance table upload");
-    // Largest group on the caller's stream; each next one goes where less has been given.  A step of a
-    // group costs its points plus the latency of its two launches, some 2^20 points' worth (7 us).
-    b->groups[0].clear();
-    b->groups[1].clear();
-    int64_t load[2] = {0, 0};
+    // units: every group by itself, but small groups of one class of y lengths together
+    std::vector<std::vector<pfc::BatchGroup>> units;
+    std::map<int, size_t> unit_of;
     for (const pfc::BatchGroup &g : groups) {
+        const int c = pfc::batch_y_class<T>(g);
+        auto it = c ? unit_of.find(c) : unit_of.end();
+        if (it != unit_of.end()) {
+            units[it->second].push_back(g);
+        } else {
+            if (c) unit_of[c] = units.size();
+            units.push_back({g});
+        }
+    }
+    // Largest unit on the caller's stream; each next one goes where less has been given.  A step of a
+    // unit costs its points plus the latency of its two launches, some 2^20 points' worth (7 us).
+    b->units[0].clear();
+    b->units[1].clear();
+    int64_t load[2] = {0, 0};
+    for (const auto &u : units) {
         const int k = load[1] < load[0] ? 1 : 0;
-        b->groups[k].push_back(g);
-        load[k] += (int64_t)g.count * g.n0 * g.M * 2 + (int64_t(1) << 20);
+        b->units[k].push_back(u);
+        for (const pfc::BatchGroup &g : u) load[k] += (int64_t)g.count * g.n0 * g.M * 2;
+        load[k] += int64_t(1) << 20;
     }
     b->side_load = load[1];
     return PFC_OK;
@@ -840,7 +855,7 @@ pfc_status batch_bind_impl(pfc_batch *b)
     return PFC_OK;
 }
 
-// nsteps steps of every instance.  The groups of the side stream run beside those of the caller's: both
+// nsteps steps of every instance.  The units of the side stream run beside those of the caller's: both
 // are launched step by step, so neither queue waits for the host.  The fork and the join cost about 30 us,
 // so the side stream is used where it takes that much work off the caller's (12 instances each of 128^2 ..
 // 1024^2 FP32: 10 steps 1095 against 1413 us on one stream; 3 each of 32^2 .. 512^2: one step 54 us on one
@@ -862,15 +877,17 @@ pfc_status batch_step_impl(pfc_batch *b, int64_t nsteps, hipStream_t s)
     for (int64_t n = 0; n < nsteps && e == hipSuccess; ++n)
         for (int pass = (n == 0 ? 0 : 1); pass < 3 && e == hipSuccess; ++pass)
             for (int k = 0; k < 2; ++k)
-                for (const pfc::BatchGroup &g : b->groups[k]) {
+                for (const auto &u : b->units[k]) {
                     hipStream_t q = k == 0 || !two ? s : b->side;
                     if (e != hipSuccess) break;
+                    const int ng = (int)u.size();
                     if (pass == 1)
-                        e = pfc::launch_batch_y<T>(g, table, tw, b->lt_shift, q);
+                        e = pfc::launch_batch_y<T>(u.data(), ng, table, tw, b->lt_shift, q);
                     else
                         e = pfc::launch_batch_x<T>(
-                            g, pass == 0 ? pfc::BATCH_X_FWD : n + 1 < nsteps ? pfc::BATCH_X_FUSED : pfc::BATCH_X_INV, table,
-                            tw, b->lt_shift, q);
+                            u.data(), ng,
+                            pass == 0 ? pfc::BATCH_X_FWD : n + 1 < nsteps ? pfc::BATCH_X_FUSED : pfc::BATCH_X_INV, table, tw,
+                            b->lt_shift, q);
                 }
     if (two) {  // joined after an error too: the caller's stream waits for whatever was launched
         hipError_t je = hipEventRecord(b->join, b->side);
@@ -1388,9 +1405,10 @@ int pfc_batch_grid(const pfc_batch *b)
 {
     int64_t n = 0;
     if (b)
-        for (const auto &list : b->groups)
-            for (const pfc::BatchGroup &g : list)
-                n += b->dtype == PFC_F64 ? pfc::batch_y_workgroups<double>(g) : pfc::batch_y_workgroups<float>(g);
+        for (const auto &list : b->units)
+            for (const auto &u : list)
+                for (const pfc::BatchGroup &g : u)
+                    n += b->dtype == PFC_F64 ? pfc::batch_y_workgroups<double>(g) : pfc::batch_y_workgroups<float>(g);
     return (int)n;
 }
 
