@@ -852,6 +852,12 @@ pfc_status batch_bind_impl(pfc_batch *b)
     const std::vector<cx<T>> tw = twiddle_table<T>(int64_t(1) << b->lt_shift);
     PFC_TRY(hipMemcpy(b->ws + b->tw_off, tw.data(), tw.size() * sizeof(tw[0]), hipMemcpyHostToDevice),
             "twiddle upload");
+    // created here, not by the first step that takes them: that one may be under capture
+    if (b->count > 1) {
+        if (!b->side) PFC_TRY(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking), "batch stream");
+        if (!b->fork) PFC_TRY(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming), "batch event");
+        if (!b->join) PFC_TRY(hipEventCreateWithFlags(&b->join, hipEventDisableTiming), "batch event");
+    }
     return PFC_OK;
 }
 
@@ -867,9 +873,6 @@ pfc_status batch_step_impl(pfc_batch *b, int64_t nsteps, hipStream_t s)
     const cx<T> *tw = (const cx<T> *)(b->ws + b->tw_off);
     const bool two = nsteps * b->side_load >= (int64_t(1) << 22);
     if (two) {
-        if (!b->side) PFC_TRY(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking), "batch stream");
-        if (!b->fork) PFC_TRY(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming), "batch event");
-        if (!b->join) PFC_TRY(hipEventCreateWithFlags(&b->join, hipEventDisableTiming), "batch event");
         PFC_TRY(hipEventRecord(b->fork, s), "batch event record");
         PFC_TRY(hipStreamWaitEvent(b->side, b->fork, 0), "batch stream wait");
     }

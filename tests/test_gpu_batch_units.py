@@ -1,7 +1,7 @@
 """Batches of many shapes, whose small groups share their launches by class of y lengths: every shape the
 batched form takes, several instances of some, groups on launches of their own among them (large ones, tuned
 ones).  Every instance equals its own plan bit for bit, and the number of launches does not grow with the
-number of shapes."""
+number of shapes.  A step captured as the first call of a batch."""
 import ctypes
 import itertools
 
@@ -76,3 +76,24 @@ def test_launches_of_many_shapes(dtype):
     # three passes of at most a class each for y up to 256, 512 and 1024, and of a few groups that fill the
     # chip by themselves; one launch per shape and pass would be 108
     assert n.value <= 18
+
+
+def test_first_step_under_capture():
+    import torch
+
+    shapes = [(1024, 1024), (512, 512), (512, 512), (64, 64), (32, 256)]  # 6 steps take the second stream
+    _, b, psi0, _, _ = _setup(shapes, {}, "f32")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        b.step(6)
+    got = []
+    for rep in range(3):
+        for x, y in zip(b.psi, psi0):
+            x.copy_(y)
+        b.state_init()
+        g.replay() if rep < 2 else b.step(6)  # the eager call last
+        torch.cuda.synchronize()
+        got.append([x.clone() for x in b.psi + b.state])
+    for rep in range(2):
+        assert all(torch.equal(x, y) for x, y in zip(got[rep], got[2])), f"replay {rep} differs from the eager call"
