@@ -268,7 +268,7 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw
 
 template <typename T>
 hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T *psi_n, const T *psi_np1, T c3,
-                            double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
+                            double *partial, int64_t slots, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.M, [&](auto Mc) -> hipError_t {
@@ -283,6 +283,7 @@ hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T
                     return hipErrorInvalidValue;
                 } else {
                     *nblocks = cdiv(g.xrows, XFused<PLI, PLF, 64>::R);
+                    if (*nblocks > slots) return hipErrorInvalidValue;
                     const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
                     const AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial, add ? 1 : 0};
                     hipLaunchKernelGGL((x_adj_r2c_kernel<T, PLI, PLF, is_pow2c(M), decltype(latc)::value>),
@@ -299,7 +300,8 @@ hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T
 
 template <typename T>
 hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu, const T *psi_n, const T *psi_np1,
-                                T *out, T c3, double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s)
+                                T *out, T c3, double *partial, int64_t slots, bool add, int64_t *nblocks, const cx<T> *tw,
+                                hipStream_t s)
 {
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.M, [&](auto Mc) -> hipError_t {
@@ -312,6 +314,7 @@ hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu,
                 constexpr int ROWS = decltype(rowsc)::value;
                 const int64_t nb = cdiv(g.xrows, ROWS);
                 *nblocks = nb;
+                if (nb > slots) return hipErrorInvalidValue;
                 const dim3 grid((unsigned)nb), block(ROWS * PL::Tp);
                 const T sc = (T)(1.0 / ((double)g.M * (double)g.n0 * (double)g.nrows));
                 AdjEpi<T> ea{nu, psi_n, psi_np1, c3, partial, add ? 1 : 0};
@@ -322,6 +325,7 @@ hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu,
             using P2 = typename X2InvPlan<M>::type;
             using P3 = typename XInvPlan<M>::type;
             if (g.ndim == 2) return run(P2{}, std::integral_constant<int, XInvRows<P2>::value>{}, std::true_type{});  // as launch_x_r2c
+            static_assert(XRows<P3>::value >= kAdjRows3, "the plan counts the partials by it");
             return run(P3{}, std::integral_constant<int, XRows<P3>::value>{}, std::false_type{});
         }
     });
@@ -627,11 +631,11 @@ hipError_t launch_export(const Geom &g, const cx<T> *state, cx<T> *out, hipStrea
     template hipError_t launch_x_r2c<T>(const Geom &, const T *, cx<T> *, bool, const cx<T> *, hipStream_t, int);     \
     template hipError_t launch_x_c2r<T>(const Geom &, const cx<T> *, T *, const cx<T> *, hipStream_t, int);           \
     template hipError_t launch_x_c2r_adjoint<T>(const Geom &, const cx<T> *, const cx<T> *, const T *, const T *, T *, \
-                                                T, double *, bool, int64_t *, const cx<T> *, hipStream_t);
+                                                T, double *, int64_t, bool, int64_t *, const cx<T> *, hipStream_t);
 #define PFC_INSTANTIATE_XF(T)                                                                                         \
     template hipError_t launch_x_c2r_r2c<T>(const Geom &, cx<T> *, T *, const cx<T> *, hipStream_t);                  \
     template hipError_t launch_x_adj_r2c<T>(const Geom &, cx<T> *, const cx<T> *, const T *, const T *, T, double *,  \
-                                            bool, int64_t *, const cx<T> *, hipStream_t);                             \
+                                            int64_t, bool, int64_t *, const cx<T> *, hipStream_t);                    \
     template bool x_fused_ok<T>(const Geom &);
 #define PFC_INSTANTIATE_Y(T)                                                                                          \
     template hipError_t launch_y_c2c<T>(const Geom &, cx<T> *, int, const cx<T> *, hipStream_t, int);                 \

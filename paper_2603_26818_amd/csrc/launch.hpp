@@ -69,7 +69,7 @@ hipError_t launch_x_c2r_r2c(const Geom &g, cx<T> *data, T *real, const cx<T> *tw
 // the same between two adjoint steps: lambda_n as launch_x_c2r_adjoint, not stored, then its x r2c into data
 template <typename T>
 hipError_t launch_x_adj_r2c(const Geom &g, cx<T> *data, const cx<T> *nu, const T *psi_n, const T *psi_np1, T c3,
-                            double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
+                            double *partial, int64_t slots, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
 template <typename T>
 bool x_fused_ok(const Geom &g);
 // whether the last-axis passes can address blocks of 2^zs z planes (their element steps are
@@ -78,10 +78,13 @@ template <typename T>
 bool z_blocks_ok(const Geom &g, int zs);
 
 // adjoint epilogue: out = mu - c3 psi_n^2 nu; partial[block] = (add: +=) sum nu psi_np1.  Returns the
-// number of partials through *nblocks.
+// number of partials through *nblocks; nothing is launched if they are more than `slots`.
 template <typename T>
 hipError_t launch_x_c2r_adjoint(const Geom &g, const cx<T> *mu, const cx<T> *nu, const T *psi_n, const T *psi_np1,
-                                T *out, T c3, double *partial, bool add, int64_t *nblocks, const cx<T> *tw, hipStream_t s);
+                                T *out, T c3, double *partial, int64_t slots, bool add, int64_t *nblocks, const cx<T> *tw,
+                                hipStream_t s);
+// rows per workgroup, at least, of the adjoint epilogue's pass in 3D
+constexpr int kAdjRows3 = 4;
 
 // y-axis (3D middle axis) complex FFT, in place; dir = -1 forward, +1 inverse.
 template <typename T>

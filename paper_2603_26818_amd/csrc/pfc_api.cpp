@@ -594,6 +594,7 @@ pfc_status do_backward(pfc_plan *p, const void *psi0, const void *traj, const vo
     gn.zs = 0;
     const T c3 = (p->d.flags & PFC_FLAG_LINEAR_ONLY) ? T(0) : (T)(3.0 * p->d.dt);
     double *partial[2] = {b.partial, b.partial + g.xrows};  // fused and separate x passes
+    const int64_t slots[2] = {g.xrows, (int64_t)p->n_partials - g.xrows};
     int64_t used[2] = {0, 0};
     for (int64_t n = nsteps - 1; n >= 0; --n) {
         if (n == nsteps - 1 || !p->x_fused) {
@@ -611,13 +612,12 @@ pfc_status do_backward(pfc_plan *p, const void *psi0, const void *traj, const vo
         const int sep = (n == 0 || !p->x_fused) ? 1 : 0;
         int64_t nb = 0;
         if (sep)
-            PFC_TRY(pfc::launch_x_c2r_adjoint<T>(g, b.scratch, nu, pn, pn1, (T *)lam_n, c3, partial[1], used[1] > 0, &nb, b.tw, s),
+            PFC_TRY(pfc::launch_x_c2r_adjoint<T>(g, b.scratch, nu, pn, pn1, (T *)lam_n, c3, partial[1], slots[1], used[1] > 0,
+                                                 &nb, b.tw, s),
                     "x_c2r adjoint launch");
         else
-            PFC_TRY(pfc::launch_x_adj_r2c<T>(g, b.scratch, nu, pn, pn1, c3, partial[0], used[0] > 0, &nb, b.tw, s),
+            PFC_TRY(pfc::launch_x_adj_r2c<T>(g, b.scratch, nu, pn, pn1, c3, partial[0], slots[0], used[0] > 0, &nb, b.tw, s),
                     "adjoint x pass launch");
-        if (nb > (sep ? (int64_t)p->n_partials - g.xrows : g.xrows))
-            return fail(PFC_ERR_INTERNAL, "partials buffer too small");
         used[sep] = nb;
     }
     for (int k = 0; k < 2; ++k)
@@ -1032,8 +1032,9 @@ pfc_status pfc_plan_create(pfc_plan **out, const pfc_plan_desc *d)
     while ((int64_t(1) << g.lt_shift) < Lt) ++g.lt_shift;
     const size_t cs = cx_size(p);
     // do_backward keeps a slot per workgroup of its fused x pass (at most one per row) and, after those, of
-    // the separate one (the same in 2D, at least four rows each in 3D)
-    p->n_partials = (size_t)std::max<int64_t>(2 * pfc::kReduceBlocks, g.xrows + (d->ndim == 2 ? g.xrows : (g.xrows + 3) / 4));
+    // the separate one (the same in 2D, at least kAdjRows3 rows each in 3D)
+    const int64_t sep = d->ndim == 2 ? g.xrows : (g.xrows + pfc::kAdjRows3 - 1) / pfc::kAdjRows3;
+    p->n_partials = (size_t)std::max<int64_t>(2 * pfc::kReduceBlocks, g.xrows + sep);
     // Layout of the packed spectra (Pack in types.hpp), 3D only: rows longer than one 128-byte line
     // padded to whole lines, so that every column tile of the strided passes is line-aligned; and
     // blocks of Z consecutive z planes interleaved by line, so that the z pass reads Z lines in a
