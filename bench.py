@@ -141,8 +141,8 @@ def bench_amplitude(nsteps, shape=(256, 256, 256), lattice="bcc", seed=7):
     """Complex-amplitude form: the amplitudes of a lattice (6 bcc amplitudes on 256^3, or 3
     triangular ones on 2048^2), FP32 (dB = -0.15, Bx = 1, t = 0.3, v = 1, dt = 0.5, dx = pi/2),
     amplitudes 0.1 + U(-0.05, 0.05) (1 + i).  Algorithmic reads or writes of the complex fields: 4 per
-    step for the fused last axis, 4 more for y in 3D, and for x and the nonlinearity 2 per step and 2
-    per call where they are one pass (rows of at most 1024 points), else 6 per step."""
+    step for the fused last axis, 4 more for y in 3D, and those of x and the nonlinearity
+    (amplitude_x_passes)."""
     import torch
 
     import paper_2603_26818_amd as pfc
@@ -165,15 +165,21 @@ def bench_amplitude(nsteps, shape=(256, 256, 256), lattice="bcc", seed=7):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / nsteps
     finite = bool(torch.isfinite(torch.view_as_real(eta)).all().item())
+    x_units = amplitude_x_passes(obj, nsteps)
     del eta, S, obj
     torch.cuda.empty_cache()
-    x_units = 2.0 + 2.0 / nsteps if shape[-1] <= 1024 else 6.0
     alg = ((8.0 if len(shape) == 3 else 4.0) + x_units) * len(k) * npts * 8
     dims = "x".join(str(v) for v in shape)
     return {"workload": f"complex-amplitude PFC, {len(k)} {lattice} amplitudes on {dims}, FP32, dB=-0.15 Bx=1 "
                         f"t=0.3 v=1, dt=0.5, seed {seed}", "steps": nsteps, "ms_per_step": round(ms, 3),
             "steps_per_s": round(1000.0 / ms, 2), "alg_gbps": round(alg / ms / 1e6, 1),
             "frac": round(alg / ms / 1e6 / PEAK_HBM_GBPS, 4), "fields_finite": finite}
+
+
+def amplitude_x_passes(obj, nsteps):
+    """Reads or writes of the complex fields per step of a call of `nsteps` steps for the x transforms and the
+    nonlinearity: 2 per step and 2 per call where they are one pass (pfc_apfc_x_fused), else 6 per step."""
+    return 2.0 + 2.0 / nsteps if obj.x_fused else 6.0
 
 
 def step_passes_hbm(plan, nsteps):

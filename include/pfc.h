@@ -413,6 +413,11 @@ pfc_status pfc_apfc_state_init(pfc_apfc *p, const void *eta, void *eta_hat, void
  * (formula above). */
 pfc_status pfc_apfc_step(pfc_apfc *p, void *eta, void *eta_hat, int64_t nsteps, void *stream);
 
+/* 1 where pfc_apfc_step runs the x transforms and the nonlinearity between them as one pass (rows of 16 ..
+ * 1024 points, powers of two, whose fields fit one workgroup), else 0.  Source: the update of Listing 1
+ * applied to every amplitude (which passes a step is). */
+int pfc_apfc_x_fused(const pfc_apfc *p);
+
 /* Frees the object's host memory.  Source: none in the paper (resource handling). */
 pfc_status pfc_apfc_destroy(pfc_apfc *p);
 

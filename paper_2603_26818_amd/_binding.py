@@ -130,6 +130,7 @@ _SIGS = {
     "pfc_apfc_nonlinear": (ctypes.c_int, [ctypes.c_void_p] * 4),
     "pfc_apfc_state_init": (ctypes.c_int, [ctypes.c_void_p] * 4),
     "pfc_apfc_step": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]),
+    "pfc_apfc_x_fused": (ctypes.c_int, [ctypes.c_void_p]),
     "pfc_apfc_destroy": (ctypes.c_int, [ctypes.c_void_p]),
     "pfc_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "pfc_last_error": (ctypes.c_char_p, []),
@@ -716,6 +717,11 @@ class Apfc:
         np_, nt_ = ctypes.c_int(), ctypes.c_int()
         _check(self._lib.pfc_apfc_terms(self._h, int(j), ctypes.byref(np_), ctypes.byref(nt_)), "pfc_apfc_terms")
         return np_.value, nt_.value
+
+    @property
+    def x_fused(self):
+        """Whether step() runs the x transforms and the nonlinearity as one pass (pfc_apfc_x_fused)."""
+        return bool(self._lib.pfc_apfc_x_fused(self._h))
 
     def fft(self, x, dir=-1, out=None):
         out = self.empty() if out is None else out

@@ -1932,6 +1932,12 @@ pfc_status pfc_apfc_set_workspace(pfc_apfc *p, void *dev_ptr, size_t bytes)
     return PFC_OK;
 }
 
+int pfc_apfc_x_fused(const pfc_apfc *p)
+{
+    if (!p) return 0;
+    return (p->d.dtype == PFC_F64 ? pfc::apfc_x_ok<double>(p->nx, p->d.nfields) : pfc::apfc_x_ok<float>(p->nx, p->d.nfields)) ? 1 : 0;
+}
+
 pfc_status pfc_apfc_terms(const pfc_apfc *p, int j, int *npairs, int *ntriples)
 {
     if (!p) return fail(PFC_ERR_INVALID_ARG, "object is NULL");
