@@ -35,12 +35,13 @@ def _x_fused(shape, kvec, dtype):
         lib.pfc_apfc_destroy(h)
 
 
-# rows of a power of two up to 1024, at most 512 threads (a row of 1024 takes 128 for bcc's six fields) and
-# 64 KB of LDS
+# rows of a power of two from 16 to 1024; 64 threads per field, at most 512; 512 values (1024 for the longest
+# rows) and their padding per field in at most 64 KB of LDS: 4.25 KB in FP32, twice that in FP64
 @pytest.mark.parametrize("shape,lattice,dtype,fused", [
-    ((256, 256, 256), "bcc", 0, True), ((256, 256, 256), "bcc", 1, True), ((16, 16, 512), "bcc", 0, True),
-    ((16, 16, 1024), "bcc", 0, False), ((64, 1024), "triangular", 0, True), ((2048, 2048), "triangular", 0, False),
-    ((64, 60), "triangular", 0, False), ((64, 750), "square", 1, False), ((64, 8), "square", 0, False)], ids=str)
+    ((256, 256, 256), "bcc", 0, True), ((256, 256, 256), "bcc", 1, True), ((16, 16, 1024), "bcc", 0, True),
+    ((16, 16, 1024), "bcc", 1, False), ((64, 1024), "triangular", 1, True), ((2048, 2048), "triangular", 0, False),
+    ((64, 64), "triangular12", 0, False), ((64, 60), "triangular", 0, False), ((64, 750), "square", 1, False),
+    ((64, 8), "square", 0, False), ((64, 16), "square", 0, True)], ids=str)
 def test_passes_follow_the_object(shape, lattice, dtype, fused):
     kvec = pfc_inputs.lattice_vectors(lattice)
 
