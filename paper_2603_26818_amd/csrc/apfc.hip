@@ -30,7 +30,7 @@ hipError_t launch_apfc_rows(int64_t L, const cx<T> *in, cx<T> *out, int64_t nrow
 {
     return by_length(L, [&](auto Lc) -> hipError_t {
         constexpr int LL = decltype(Lc)::value;
-        if constexpr (LL < 4) {
+        if constexpr (!axis_length(LL)) {
             return hipErrorInvalidValue;
         } else {
             using P0 = typename DefaultPlan<LL>::type;
@@ -103,7 +103,7 @@ hipError_t launch_apfc_last_step(int64_t L, int nf, ApfcStepArgs<T> a, hipStream
 {
     return by_length(L, [&](auto Lc) -> hipError_t {
         constexpr int LL = decltype(Lc)::value;
-        if constexpr (LL < 4) {
+        if constexpr (!axis_length(LL)) {
             return hipErrorInvalidValue;
         } else {
             using TL = PencilTile<T, LL>;

@@ -217,7 +217,7 @@ template <typename T, class F>
 hipError_t batch_y_tile(const BatchGroup &g, F &&f)
 {
     return batch_length(g.n0, [&](auto Lc) -> hipError_t {
-        constexpr int L = decltype(Lc)::value;
+        constexpr int L = decltype(Lc)::value < 32 ? 32 : decltype(Lc)::value;  // (16 only as x / 2)
         return with_plan<typename Last2Cands<L>::type>(g.vy, [&](auto plc) -> hipError_t {
             using P0 = decltype(plc);
             using TL = PencilTile<T, L>;

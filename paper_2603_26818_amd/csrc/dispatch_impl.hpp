@@ -40,12 +40,17 @@ static hipError_t by_length(int64_t L, F &&f)
 
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Calls f(std::bool_constant<nt>).
-template <class F>
+// Calls f(std::bool_constant<nt>); CAN: whether nt can be true at all, else only one instance is compiled.
+template <bool CAN = true, class F>
 static hipError_t with_nt(bool nt, F &&f)
 {
-    return nt ? f(std::true_type{}) : f(std::false_type{});
+    if constexpr (CAN)
+        if (nt) return f(std::true_type{});
+    return f(std::false_type{});
 }
+
+// Lengths of by_length that a strided axis (y, last) can have: those of x / 2 include 2 and odd ones.
+static constexpr bool axis_length(int L) { return L >= 4 && L % 2 == 0; }
 
 // Every element step of the schedule PL (b Tp + r L / R for its first and last radix) is a
 // multiple of the layout's plane block 2^zs, as the last-axis addressing requires (AxisMap, Pack).
@@ -103,7 +108,7 @@ static hipError_t with_cands(const Geom &g, int variant, F &&f)
 }
 
 // Largest even width <= w (w >= 2).
-static inline int even_width(int w) { return w > 1 ? (w & ~1) : w; }
+static constexpr int even_width(int w) { return w > 1 ? (w & ~1) : w; }
 
 // Workgroups per 128-byte line for column tiles of W complex values (1 for whole-line tiles).
 template <typename T>
@@ -150,7 +155,7 @@ hipError_t launch_x_r2c(const Geom &g, const T *in, cx<T> *out, bool cube, const
                 // non-temporal hints measured faster at M = 256 and slower at M = 1024; mixed-radix
                 // rows are not whole lines (their partial lines then reach HBM unmerged).  Padded
                 // LDS rows (power-of-two M): 512^3 FP64 x r2c 0.360 against 0.389 ms, FP32 even.
-                return with_nt(g.nt && M < 1024 && is_pow2c(M), [&](auto ntc) -> hipError_t {
+                return with_nt<(M < 1024 && is_pow2c(M))>(g.nt, [&](auto ntc) -> hipError_t {
                     hipLaunchKernelGGL((x_r2c_kernel<T, PL, ROWS, CUBE, is_pow2c(M), decltype(ntc)::value>), grid, block, 0,
                                        s, in, out, g.xrows, tw + g.tw_x, g.lt_shift, pack_of(g));
                     return hipGetLastError();
@@ -190,7 +195,7 @@ hipError_t launch_x_c2r(const Geom &g, const cx<T> *in, T *out, const cx<T> *tw,
                 }
                 // unpadded LDS rows: padded ones measured slower here (512^3 FP32 0.224 against
                 // 0.215 ms, FP64 0.419 against 0.396 ms, 2048^3 FP32 18.5 against 18.0 ms)
-                return with_nt(g.nt && is_pow2c(M), [&](auto ntc) -> hipError_t {
+                return with_nt<is_pow2c(M)>(g.nt, [&](auto ntc) -> hipError_t {
                     hipLaunchKernelGGL((x_c2r_kernel<T, PL, ROWS, EPI_PLAIN, false, false, decltype(ntc)::value>), grid,
                                        block, 0, s, in, out, g.xrows, tw + g.tw_x, g.lt_shift, sc, ea, pack_of(g));
                     return hipGetLastError();
@@ -337,7 +342,7 @@ hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hi
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.n1, [&](auto Lc) -> hipError_t {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
+        if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
             auto run = [&](auto plc) -> hipError_t {
@@ -370,7 +375,7 @@ hipError_t launch_y_c2c(const Geom &g, cx<T> *data, int dir, const cx<T> *tw, hi
                 // grouped power-of-two tiles (2048 points), where it measured slower
                 const int xg = (line_group<T>(W) == 1 && (TL::G == 1 || !is_pow2c(L))) ? 0 : line_group<T>(W);
                 // non-temporal only with whole-line tiles (measured slower on 64-byte tiles)
-                return with_nt(g.nt && xg <= 1, [&](auto ntc) -> hipError_t {
+                return with_nt<line_group<T>(WM) == 1>(g.nt && xg <= 1, [&](auto ntc) -> hipError_t {
                     constexpr bool NT = decltype(ntc)::value;
                     const AxisMap am = y_map(g);
                     if (dir < 0)
@@ -402,7 +407,7 @@ hipError_t launch_last_c2c(const Geom &g, const cx<T> *src, cx<T> *dst, int dir,
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.n0, [&](auto Lc) -> hipError_t {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
+        if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
             constexpr int WM = WMax<T, L>::value;
@@ -457,7 +462,7 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.n0, [&](auto Lc) -> hipError_t {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
+        if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
             constexpr int WM = WMax<T, L>::value;
@@ -505,7 +510,7 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
             using P2 = typename Last2Plan<L>::type;
             switch (mode) {
             case LAST_STEP: {
-                auto run = [&](auto plc) -> hipError_t {
+                auto run = [&](auto plc, auto twoc) -> hipError_t {
                     using TO = TileOf<T, decltype(plc)>;
                     using TL = typename TO::tile;
                     using PL = SpreadIf<typename TO::plan, TL::E>;
@@ -516,7 +521,9 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                     if (variant == 0 && g.nrows * b.tiles_per_row < kFillTiles)
                         return narrow(typename TO::plan{}, std::integral_constant<int, LA_STEP>{});
                     const int64_t nb = (g.nrows == 1) ? b.tiles_per_row : g.nrows * b.tiles_per_row;
-                    return with_nt(g.nt && line_group<T>(b.W) == 1, [&](auto ntc) -> hipError_t {
+                    // (no 2D grid is large enough for non-temporal accesses)
+                    constexpr bool CAN = !decltype(twoc)::value && line_group<T>(even_width(TL::W)) == 1;
+                    return with_nt<CAN>(g.nt && line_group<T>(b.W) == 1, [&](auto ntc) -> hipError_t {
                         hipLaunchKernelGGL((last_axis_kernel<T, PL, TL::W, LA_STEP, 1, TL::PF, ORD_XCD_ROW,
                                                              decltype(ntc)::value, TL::G>),
                                            dim3((unsigned)nb), dim3(TL::W * PL::Tp), 0, s, b);
@@ -525,7 +532,9 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                 };
                 // 3D: the z candidates (wider tiles at some lengths); 2D: the list the batched
                 // kernel shares, so that its instances stay bitwise equal to single plans
-                return with_cands<typename Last2Cands<L>::type, typename ZCandsOf<T, L>::type>(g, variant, run);
+                if (g.ndim == 2)
+                    return with_plan<typename Last2Cands<L>::type>(variant, [&](auto plc) { return run(plc, std::true_type{}); });
+                return with_plan<typename ZCandsOf<T, L>::type>(variant, [&](auto plc) { return run(plc, std::false_type{}); });
             }
             // natural layout (rows of M + 1, not line-aligned): whole rows per XCD, so the lines two
             // tiles share meet in one L2 (measured at 512^3: r2c 403 -> 348 us, c2r 274 -> 262 us)
@@ -560,7 +569,7 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                     constexpr std::integral_constant<int, LA_C2R_NATURAL> m{};
                     return g.ndim == 2 ? narrow(P2{}, m) : narrow(P0{}, m);
                 }
-                return with_nt(g.nt && line_group<T>(a.W) == 1, [&](auto ntc) -> hipError_t {
+                return with_nt<line_group<T>(even_width(WM)) == 1>(g.nt && line_group<T>(a.W) == 1, [&](auto ntc) -> hipError_t {
                     hipLaunchKernelGGL(
                         (last_axis_kernel<T, P0, WM, LA_C2R_NATURAL, 1, true, ORD_XCD_ROW, decltype(ntc)::value>), grid,
                         dim3(WM * P0::Tp), 0, s, a);

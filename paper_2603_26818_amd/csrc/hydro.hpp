@@ -390,7 +390,7 @@ hipError_t hydro_last_op(const Geom &g, HydroLastArgs<T> a, hipStream_t s)
 {
     return by_length(g.n0, [&](auto Lc) -> hipError_t {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
+        if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
             auto run = [&](auto plc, auto wc, auto lpc, auto ntc) -> hipError_t {
@@ -414,7 +414,7 @@ hipError_t hydro_last_op(const Geom &g, HydroLastArgs<T> a, hipStream_t s)
             if (g.ndim == 2) return narrow(typename Last2Plan<L>::type{});
             const int W = even_width(g.M < wm.value ? (int)g.M : wm.value);
             if (g.nrows * cdiv(g.M, W) < kFillTiles) return narrow(P3{});
-            return with_nt(g.nt && line_group<T>(W) == 1,
+            return with_nt<line_group<T>(even_width(wm.value)) == 1>(g.nt && line_group<T>(W) == 1,
                            [&](auto ntc) -> hipError_t { return run(P3{}, wm, std::false_type{}, ntc); });
         }
     });
@@ -445,7 +445,7 @@ hipError_t launch_hydro_y(const Geom &g, cx<T> *data, cx<T> *dk, double fk, cons
     if (!layout_ok(g)) return hipErrorInvalidValue;
     return by_length(g.n1, [&](auto Lc) -> hipError_t {
         constexpr int L = decltype(Lc)::value;
-        if constexpr (L < 4) {
+        if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
             using TO = TileOf<T, typename ListAt<0, typename AxisCands<L>::type>::type>;
@@ -468,7 +468,7 @@ hipError_t launch_hydro_y(const Geom &g, cx<T> *data, cx<T> *dk, double fk, cons
             }
             const int xg = (line_group<T>(W) == 1 && (TL::G == 1 || !is_pow2c(L))) ? 0 : line_group<T>(W);
             constexpr bool BOTH = TL::G == 1 && PL::Rmax <= 20;
-            return with_nt(g.nt && xg <= 1 && BOTH, [&](auto ntc) -> hipError_t {
+            return with_nt<BOTH && line_group<T>(WM) == 1>(g.nt && xg <= 1, [&](auto ntc) -> hipError_t {
                 hipLaunchKernelGGL((hydro_y_kernel<T, PL, WM, decltype(ntc)::value, TL::G, false, BOTH>),
                                    dim3((unsigned)(tiles * g.n0)), dim3(WM * PL::Tp), 0, s, data, dk, W, g.M, am, tiles,
                                    tw + g.tw_y, g.lt_shift, xg, fk);
