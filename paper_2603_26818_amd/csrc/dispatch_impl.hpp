@@ -494,7 +494,7 @@ hipError_t launch_last(const Geom &g, int mode, const cx<T> *src, cx<T> *dst, cx
                 b.W = even_width(g.M < WN ? (int)g.M : WN);
                 b.tiles_per_row = (int)cdiv(g.M, b.W);
                 b.xg = line_group<T>(b.W);
-                constexpr bool PF = is_pow2c(L) && PN::Rmax <= 16;
+                constexpr bool PF = is_pow2c(L) && PN::Rmax <= 16;  // (mixed lengths as PencilTile)
                 hipLaunchKernelGGL((last_axis_kernel<T, PN, WN, decltype(modec)::value, 1, PF, ORD_XCD_ROW, false, 1, true>),
                                    dim3((unsigned)(g.nrows * b.tiles_per_row)), dim3(WN * PN::Tp), 0, s, b);
                 return hipGetLastError();

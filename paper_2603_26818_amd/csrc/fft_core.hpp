@@ -537,7 +537,9 @@ static_assert(ZCandsOf<float, 512>::type::size == ZCands<512>::type::size, "one 
 // 2D grids (single plans and batched instances, which share these lists).  A 2D pass has at most a few
 // hundred pencils or rows, so it is bound by the latency of one workgroup's chain, not by bandwidth:
 // the default holds 8 elements per thread where the 3D lists hold 16, which halves the chain, and the
-// 3D default moves to the end (candidate numbers in between keep their meaning).
+// 3D default moves to the end (candidate numbers in between keep their meaning).  At 256 points candidate 1
+// is the default's schedule too, but not its passes: only candidate 0 takes narrow y tiles, and only x passes
+// of candidate 0 are fused between steps.
 template <int M> struct X2FwdCands { using type = typename XFwdCands<M>::type; };
 template <int M> struct X2InvCands { using type = typename XInvCands<M>::type; };
 template <int L> struct Last2Cands { using type = typename LastCands<L>::type; };
@@ -656,7 +658,7 @@ struct StageTw {
     static constexpr int n = off(PL::nst);
     cx<T> w[n > 0 ? n : 1];
 };
-// ... as long as they are few: at most 8 FP32 elements per thread, or 4 FP64 registers' worth
+// ... as long as they are few: for at most 16 FP32 or 8 FP64 elements per thread
 template <typename T, class PL>
 constexpr bool preload_tw() { return (int)sizeof(T) * PL::Rmax <= 64; }
 

@@ -436,8 +436,6 @@ __global__ __launch_bounds__(ROWS *PL::Tp) void x_c2r_kernel(const cx<T> *in, T 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Pencils per workgroup of the strided passes: 128-byte rows (16 FP32 / 8 FP64 complex) as long as
-// the workgroup's LDS tile stays within 128 KB.
 // x pass between two steps (batched runs, and the single-plan step within one call): the inverse x
 // transform of one step (x c2r) and the forward x transform with the cube of the next (x r2c), over
 // the same rows, with the field between them kept in LDS: a workgroup takes R rows, runs the c2r
@@ -534,7 +532,8 @@ x_adj_r2c_kernel(cx<T> *data, int64_t nrows, const cx<T> *__restrict__ tw, int l
     adj_partial(ea, acc, bid);
 }
 
-
+// Pencils per workgroup of the strided passes: 128-byte rows (16 FP32 / 8 FP64 complex) as long as
+// the workgroup's LDS tile stays within 128 KB.
 template <typename T, int L>
 struct WMax {
     static constexpr int pref = 128 / (int)sizeof(cx<T>);
@@ -552,7 +551,10 @@ struct WMax {
 template <typename T, int L>
 struct PencilTile {
     static constexpr int W = WMax<T, L>::value, E = 0, G = 1;
-    static constexpr bool PF = is_pow2c(L);  // mixed radices hold up to 30 elements per thread
+    // Lengths with factors 3, 5, 7 load the state after the forward transform: at 375 points and more they
+    // hold 15 to 30 elements per thread (750: 20, where 20 more pass the 128 registers that 13 waves per CU
+    // allow), and for the shorter ones, of 6 to 20 elements, the prefetch has not been measured.
+    static constexpr bool PF = is_pow2c(L);
 };
 template <>
 struct PencilTile<float, 1024> {

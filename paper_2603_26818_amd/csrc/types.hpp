@@ -110,7 +110,7 @@ struct ModelParams {
     int model;
 };
 
-// Hydrodynamic PFC spectral updates (kernels.hpp).
+// Hydrodynamic PFC spectral updates (hydro.hpp).
 // Parameters, in FP64.  fk[0]: last-axis (index e), fk[1]: rows (3D y),
 // fk[2]: x wavenumber steps.
 struct HydroArgs {
