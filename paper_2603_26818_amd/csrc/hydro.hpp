@@ -83,9 +83,15 @@ __global__ __launch_bounds__(WMAX *PL::Tp) void hydro_last_kernel(HydroLastArgs<
     // the state is loaded ahead of the forward transforms where its registers fit beside theirs
     constexpr bool PF = OP != HYDRO_DERIV && (int)sizeof(T) * Rmax <= (OP == HYDRO_PSI ? 32 : 64);
     __shared__ cx<T> sh[hy_lds<T, PL, WMAX, OP, LP>()];
-    const int64_t bid = LP && a.nrows == 1 ? xcd_tile_order(blockIdx.x, gridDim.x, a.xg) : blockIdx.x;
     const int tid = threadIdx.x, p = tid % WMAX, t = tid / WMAX, W = a.W;
     const int64_t nrows = a.nrows, M = a.M;
+    int64_t bid = blockIdx.x;
+    if constexpr (LP) {
+        if (nrows == 1)
+            bid = xcd_tile_order(bid, gridDim.x, a.xg);
+        else if (a.tiles_per_row == 1)
+            bid = la_pair_order(bid, nrows, 2 * a.xg);
+    }
     const SlotInfo si = la_slot<ORD_XCD_ROW, false>(nrows, a.tiles_per_row, W, p < W ? p : 0, bid);
     const bool valid = p < W && si.kx < M;
     auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * WMAX + p]; };
@@ -413,6 +419,18 @@ hipError_t hydro_last_op(const Geom &g, HydroLastArgs<T> a, hipStream_t s)
             // 2D grids never have kFillTiles tiles
             if (g.ndim == 2) return narrow(typename Last2Plan<L>::type{});
             const int W = even_width(g.M < wm.value ? (int)g.M : wm.value);
+            // Rows of a quarter of a line at most (x = 4, FP32 also 8) would leave most of the tile's lanes idle:
+            // tiles of a row's half and its mirror's, mixed lengths over more threads as in 2D.  Two steps, in
+            // ms, of separate passes (whose tiles cross rows), full tiles, these: 1024 x 1024 x 8 FP32 2.77, 3.95,
+            // 2.69, 1400 x 1400 x 8 7.20, 9.27, 6.47, 700 x 2048 x 4 3.12, 5.55, 3.14, FP64 2.94, 4.13, 2.60;
+            // 1024 x 2048 x 4 FP32 4.11, 7.03, 4.61 and 2048 x 2048 x 4 8.16, 9.17, 9.21, where the folded
+            // pencils' LDS leaves one to three workgroups per CU.
+            if (4 * W <= WMax<T, L>::pref) {
+                using PS = std::conditional_t<is_pow2c(L), P3, typename Last2Plan<L>::type>;
+                if constexpr (sizeof(T) == 4 && NarrowTile<PS>::W < 4)
+                    if (W == 4) return run(PS{}, std::integral_constant<int, 4>{}, std::true_type{}, std::false_type{});
+                return narrow(PS{});
+            }
             if (g.nrows * cdiv(g.M, W) < kFillTiles) return narrow(P3{});
             return with_nt<line_group<T>(even_width(wm.value)) == 1>(g.nt && line_group<T>(W) == 1,
                            [&](auto ntc) -> hipError_t { return run(P3{}, wm, std::false_type{}, ntc); });

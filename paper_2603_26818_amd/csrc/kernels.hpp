@@ -823,6 +823,15 @@ __device__ __forceinline__ SlotInfo la_slot(int64_t nrows, int TR, int W, int p,
     return s;
 }
 
+// Order of the pair tiles of la_slot where they are all there is (rows of at most W columns): the G tiles that
+// share the lines of neighbouring rows run on one XCD (xcd_tile_order).  The tile of pair i and half h in
+// the place that la_slot gives it.
+__device__ __forceinline__ int64_t la_pair_order(int64_t bid, int64_t nrows, int G)
+{
+    const int64_t u = xcd_tile_order(bid, nrows, G), i = u >> 1, h = u & 1;
+    return u < nrows - nrows % 16 ? ((i >> 3) << 4) + (h << 3) + (i & 7) : u;
+}
+
 // G > 1 (STEP only): the pencils form G groups of WMAX / G adjacent slots that take turns in an LDS
 // area of L * WMAX / G values (see fft_stages); pair tiles then interleave their two rows.
 template <typename T, class PL, int WMAX, int MODE, bool PF = true, int ORD = ORD_TILE, bool NT = false, int G = 1,

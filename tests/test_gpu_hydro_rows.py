@@ -1,6 +1,7 @@
 """Rows whose threads do not divide a wavefront (x = 1500: 750 packed points over 25 threads, two rows and
 50 threads per workgroup) in the x passes of the hydrodynamic step: even and odd numbers of workgroups, 2D
-and 3D.  Two steps, against the oracle."""
+and 3D.  The shortest rows, whose last-axis tiles are half a row and its mirror's, at row counts with and
+without a last incomplete group.  Two steps, against the oracle."""
 import numpy as np
 import pytest
 
@@ -36,5 +37,16 @@ def _run(shape, dtype):
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("shape", [(4, 1500), (6, 1500), (64, 1500), (4, 6, 1500), (6, 10, 1500), (16, 4, 1500)], ids=str)
 def test_rows_of_750(shape, dtype):
+    for a, b in zip(*_run(shape, dtype)):
+        assert parity_err(a, b) < TOL_STEP[dtype]
+
+
+SHORT = [(700, 20, 4), (750, 14, 8), (1400, 6, 8), (1400, 12, 4), (1024, 20, 8), (2048, 6, 4), (256, 60, 8), (128, 150, 4),
+         (512, 30, 8), (60, 128, 4), (64, 256, 8)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape", SHORT, ids=str)
+def test_short_rows(shape, dtype):
     for a, b in zip(*_run(shape, dtype)):
         assert parity_err(a, b) < TOL_STEP[dtype]
