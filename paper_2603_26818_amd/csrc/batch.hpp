@@ -1,8 +1,9 @@
 // batch.hpp -- batched 2D runs: the passes of the single-plan step over many independent instances.
 //
 // Instances of one shape and one choice of schedules form a group.  A unit is what shares its launches: one
-// group, or the small groups of one class of y lengths (batch_y_class).  A pass of a unit is one launch; a
-// workgroup takes one row group or column tile of one instance, an entry of the device table.  Units do not
+// group, or small groups together (batch_unit).  A pass of a unit is one launch (on tuned schedules one per
+// length and schedule); a workgroup takes one row group or column tile of one
+// instance, an entry of the device table.  Units do not
 // depend on each other, so the host runs them on two streams (pfc_api.cpp).  The kernels are the single-plan
 // blocks on the same schedules, so every instance is bitwise equal to its own plan.  Between two steps the
 // x c2r of one and the x r2c of the next are one pass, as in the single plan.
@@ -107,8 +108,8 @@ __global__ __launch_bounds__(WM *PL::Tp) void batch_y_kernel(const BatchInst<T> 
     batch_y_block<T, PL, WM, PF, G, LP>(inst[blockIdx.y], W, blockIdx.x, (int)gridDim.x, xg, tw, lt_shift, sh);
 }
 
-// Several groups in one launch, on the default schedules.  The workgroup's group is the last one that begins
-// at or before it; all counts are powers of two.
+// Several groups in one launch.  The workgroup's group is the last one that begins at or before it; all counts
+// are powers of two.
 struct BatchTiles {
     struct Group {
         int begin;  // its first workgroup
@@ -193,6 +194,26 @@ __global__ __launch_bounds__(batch_y_threads<K0>()) void batch_y_many_kernel(Bat
     });
 }
 
+// The same for groups on tuned schedules: one length and schedule, any number of shapes.
+template <typename T, int PASS, class PLI, class PLF>
+__global__ __launch_bounds__((BatchX<T, PASS, PLI, PLF>::threads)) void
+batch_x_set_kernel(BatchTiles b, const BatchInst<T> *table, const cx<T> *__restrict__ tw, int lt_shift)
+{
+    __shared__ cx<T> sh[BatchX<T, PASS, PLI, PLF>::slots];
+    const BatchPlace w = batch_place(b);
+    BatchX<T, PASS, PLI, PLF>::run(table[w.inst], w.tile, tw, lt_shift, sh);
+}
+template <typename T, class PL>
+__global__ __launch_bounds__(NarrowTile<PL>::W *PL::Tp) void batch_y_set_kernel(BatchTiles b, const BatchInst<T> *table,
+                                                                                const cx<T> *__restrict__ tw, int lt_shift)
+{
+    constexpr int W = NarrowTile<PL>::W;
+    constexpr bool PF = PL::Rmax <= 16;
+    __shared__ cx<T> sh[batch_y_slots<PL, W, PF, 1, true>()];
+    const BatchPlace w = batch_place(b);
+    batch_y_block<T, PL, W, PF, 1, true>(table[w.inst], W, w.tile, w.tiles, line_group<T>(W), tw, lt_shift, sh);
+}
+
 // Calls f(std::integral_constant<int, L>) for a length of the batched form: y (32 .. 1024) or x / 2.
 template <class F>
 hipError_t batch_length(int L, F &&f)
@@ -248,22 +269,45 @@ int64_t batch_y_workgroups(const BatchGroup &g)
     return n;
 }
 
-// Class of y lengths whose small groups share their launches (the largest length of the class), or 0.  A
-// group is small where it takes narrow tiles, which are then of one form within the class; on tuned schedules
-// it keeps its own.  Apart, every shape costs two launches of 5 to 9 us per step, one after the other.  50
-// steps, us per step, in the persistent kernel, apart, together: all 36 shapes, one instance each, FP32 122,
-// 237, 53, FP64 204, 289, 72, four of each FP32 254, 300, 157, FP64 660, 422, 256; 9 shapes up to 128 x 128,
-// 16 of each, FP32 70, 59, 20; 4 squares of 128 .. 1024, 12 of each, FP32 230, 106, 106.
+inline bool batch_tuned(const BatchGroup &g) { return g.vx != 0 || g.vy != 0 || g.vc != 0; }
+
+// The unit that a group shares its launches in, or 0.  A group is small where it takes narrow tiles.  Small
+// groups on the default schedules run together by class of y lengths (up to 256, 512, 1024 points), whose
+// narrow tiles are of one form; those on tuned schedules are one unit, with a launch per length and schedule.
+// Apart, every shape costs two launches of 5 to 9 us per step, one after the other.  50 steps, us per step,
+// in the persistent kernel, apart, together: all 36 shapes, one instance each, FP32 122, 237, 53, FP64 204,
+// 289, 72, four of each FP32 254, 300, 157, FP64 660, 422, 256; 9 shapes up to 128 x 128, 16 of each, FP32
+// 70, 59, 20; 4 squares of 128 .. 1024, 12 of each, FP32 230, 106, 106.
 template <typename T>
-int batch_y_class(const BatchGroup &g)
+int batch_unit(const BatchGroup &g)
 {
-    if (g.vx != 0 || g.vy != 0 || g.vc != 0) return 0;
     bool narrow = false;
     (void)batch_y_tile<T>(g, [&](auto plc, auto wc, auto, auto, auto lpc) -> hipError_t {
         narrow = decltype(lpc)::value && wc.value == NarrowTile<decltype(plc)>::W;
         return hipSuccess;
     });
-    return !narrow ? 0 : g.n0 <= 256 ? 256 : g.n0;
+    return !narrow ? 0 : batch_tuned(g) ? 1 : g.n0 <= 256 ? 256 : g.n0;
+}
+
+// Calls f(groups, number) for the groups of each value of key(group), at most kBatchUnitGroups at a time.
+template <class Key, class F>
+hipError_t batch_by_key(const BatchGroup *g, int ng, Key &&key, F &&f)
+{
+    if (ng > kBatchMaxInstHost) return hipErrorInvalidValue;
+    bool done[kBatchMaxInstHost] = {};
+    for (int i = 0; i < ng; ++i) {
+        if (done[i]) continue;
+        BatchGroup sub[kBatchUnitGroups];
+        int n = 0;
+        for (int j = i; j < ng && n < kBatchUnitGroups; ++j)
+            if (!done[j] && key(g[j]) == key(g[i])) {
+                sub[n++] = g[j];
+                done[j] = true;
+            }
+        const hipError_t e = f((const BatchGroup *)sub, n);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The launch's table for groups of `tiles(g)` workgroups per instance and pass length `len(g)`, and its
@@ -275,7 +319,7 @@ bool batch_tiles(const BatchGroup *g, int ng, Tiles &&tiles, Len &&len, BatchTil
     *total = 0;
     for (int i = 0; i < ng; ++i) {
         const int64_t n = tiles(g[i]);
-        if (n < 1 || (n & (n - 1)) != 0 || g[i].vx != 0 || g[i].vy != 0 || g[i].vc != 0) return false;
+        if (n < 1 || (n & (n - 1)) != 0) return false;
         int shift = 0;
         while ((int64_t(1) << shift) < n) ++shift;
         b->g[i] = {(int)*total, g[i].first, shift, len(g[i])};
@@ -298,6 +342,27 @@ hipError_t launch_batch_y(const BatchGroup *g, int ng, const BatchInst<T> *table
                                line_group<T>(W), tw, lt_shift);
             return hipGetLastError();
         });
+    if (batch_tuned(*g))
+        return batch_by_key(
+            g, ng, [](const BatchGroup &q) { return q.n0 * 8 + q.vy; },
+            [&](const BatchGroup *sub, int n) -> hipError_t {
+                if (n == 1) return launch_batch_y<T>(sub, 1, table, tw, lt_shift, s);
+                return batch_length(sub->n0, [&](auto Lc) -> hipError_t {
+                    constexpr int L = decltype(Lc)::value < 32 ? 32 : decltype(Lc)::value;
+                    return with_plan<typename Last2Cands<L>::type>(sub->vy, [&](auto plc) -> hipError_t {
+                        using PL = decltype(plc);
+                        constexpr int W = NarrowTile<PL>::W;
+                        BatchTiles b{};
+                        int64_t total = 0;
+                        if (!batch_tiles(sub, n, [](const BatchGroup &q) -> int64_t { return q.M / W; },
+                                         [](const BatchGroup &q) { return q.n0; }, &b, &total))
+                            return hipErrorInvalidValue;
+                        hipLaunchKernelGGL((batch_y_set_kernel<T, PL>), dim3((unsigned)total), dim3(W * PL::Tp), 0, s, b, table,
+                                           tw, lt_shift);
+                        return hipGetLastError();
+                    });
+                });
+            });
     auto run = [&](auto k0, auto k1) -> hipError_t {
         constexpr int K0 = decltype(k0)::value, K1 = decltype(k1)::value;
         BatchTiles b{};
@@ -326,10 +391,53 @@ hipError_t launch_batch_y(const BatchGroup *g, int ng, const BatchInst<T> *table
     return g->n0 <= 256 ? run(k5, k8) : g->n0 == 512 ? run(k9, k9) : run(k10, k10);
 }
 
+// Calls f(std::integral_constant<int, pass>, PLI{}, PLF{}) with a group's x schedules (of the passes that have
+// one of the two, it is given twice).
+template <typename T, class F>
+hipError_t batch_x_schedule(const BatchGroup &g, int pass, F &&f)
+{
+    return batch_length(g.M, [&](auto Mc) -> hipError_t {
+        constexpr int M = decltype(Mc)::value;
+        if constexpr (M > 512) {
+            return hipErrorInvalidValue;
+        } else {
+            if (pass == BATCH_X_FWD)
+                return with_plan<typename X2FwdCands<M>::type>(
+                    g.vx, [&](auto pf) { return f(std::integral_constant<int, BATCH_X_FWD>{}, pf, pf); });
+            return with_plan<typename X2InvCands<M>::type>(g.vc, [&](auto pi) -> hipError_t {
+                if (pass == BATCH_X_INV) return f(std::integral_constant<int, BATCH_X_INV>{}, pi, pi);
+                return with_plan<typename X2FwdCands<M>::type>(
+                    g.vx, [&](auto pf) { return f(std::integral_constant<int, BATCH_X_FUSED>{}, pi, pf); });
+            });
+        }
+    });
+}
+
 template <typename T>
 hipError_t launch_batch_x(const BatchGroup *g, int ng, int pass, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
                           hipStream_t s)
 {
+    if (ng > 1 && batch_tuned(*g))
+        return batch_by_key(
+            g, ng,
+            [&](const BatchGroup &q) { return (q.M * 8 + (pass == BATCH_X_INV ? 0 : q.vx)) * 8 + (pass == BATCH_X_FWD ? 0 : q.vc); },
+            [&](const BatchGroup *sub, int n) -> hipError_t {
+                if (n == 1) return launch_batch_x<T>(sub, 1, pass, table, tw, lt_shift, s);
+                return batch_x_schedule<T>(*sub, pass, [&](auto passc, auto pic, auto pfc) -> hipError_t {
+                    using PLI = decltype(pic);
+                    using PLF = decltype(pfc);
+                    constexpr int PASS = decltype(passc)::value;
+                    using X = BatchX<T, PASS, PLI, PLF>;
+                    BatchTiles b{};
+                    int64_t total = 0;
+                    if (!batch_tiles(sub, n, [](const BatchGroup &q) -> int64_t { return cdiv(q.n0, X::rows); },
+                                     [](const BatchGroup &q) { return q.M; }, &b, &total))
+                        return hipErrorInvalidValue;
+                    hipLaunchKernelGGL((batch_x_set_kernel<T, PASS, PLI, PLF>), dim3((unsigned)total), dim3(X::threads), 0, s, b,
+                                       table, tw, lt_shift);
+                    return hipGetLastError();
+                });
+            });
     if (ng > 1) {
         auto run = [&](auto passc) -> hipError_t {
             constexpr int PASS = decltype(passc)::value;
@@ -355,29 +463,14 @@ hipError_t launch_batch_x(const BatchGroup *g, int ng, int pass, const BatchInst
         if (pass == BATCH_X_INV) return run(std::integral_constant<int, BATCH_X_INV>{});
         return run(std::integral_constant<int, BATCH_X_FUSED>{});
     }
-    return batch_length(g->M, [&](auto Mc) -> hipError_t {
-        constexpr int M = decltype(Mc)::value;
-        if constexpr (M > 512) {
-            return hipErrorInvalidValue;
-        } else {
-            auto run = [&](auto passc, auto pic, auto pfc) -> hipError_t {
-                using PLI = decltype(pic);
-                using PLF = decltype(pfc);
-                constexpr int PASS = decltype(passc)::value;
-                using X = BatchX<T, PASS, PLI, PLF>;
-                hipLaunchKernelGGL((batch_x_kernel<T, PASS, PLI, PLF>), dim3((unsigned)cdiv(g->n0, X::rows), (unsigned)g->count),
-                                   dim3(X::threads), 0, s, table + g->first, tw, lt_shift);
-                return hipGetLastError();
-            };
-            if (pass == BATCH_X_FWD)
-                return with_plan<typename X2FwdCands<M>::type>(
-                    g->vx, [&](auto pf) { return run(std::integral_constant<int, BATCH_X_FWD>{}, pf, pf); });
-            return with_plan<typename X2InvCands<M>::type>(g->vc, [&](auto pi) -> hipError_t {
-                if (pass == BATCH_X_INV) return run(std::integral_constant<int, BATCH_X_INV>{}, pi, pi);
-                return with_plan<typename X2FwdCands<M>::type>(
-                    g->vx, [&](auto pf) { return run(std::integral_constant<int, BATCH_X_FUSED>{}, pi, pf); });
-            });
-        }
+    return batch_x_schedule<T>(*g, pass, [&](auto passc, auto pic, auto pfc) -> hipError_t {
+        using PLI = decltype(pic);
+        using PLF = decltype(pfc);
+        constexpr int PASS = decltype(passc)::value;
+        using X = BatchX<T, PASS, PLI, PLF>;
+        hipLaunchKernelGGL((batch_x_kernel<T, PASS, PLI, PLF>), dim3((unsigned)cdiv(g->n0, X::rows), (unsigned)g->count),
+                           dim3(X::threads), 0, s, table + g->first, tw, lt_shift);
+        return hipGetLastError();
     });
 }
 

@@ -3,7 +3,7 @@
 
 namespace pfc {
 template int64_t batch_y_workgroups<float>(const BatchGroup &);
-template int batch_y_class<float>(const BatchGroup &);
+template int batch_unit<float>(const BatchGroup &);
 template hipError_t launch_batch_y<float>(const BatchGroup *, int, const BatchInst<float> *, const cx<float> *, int, hipStream_t);
 template hipError_t launch_batch_x<float>(const BatchGroup *, int, int, const BatchInst<float> *, const cx<float> *, int,
                                         hipStream_t);

@@ -149,13 +149,14 @@ hipError_t launch_accumulate(const double *partial, int np, double coef, double 
 struct BatchGroup {
     int n0, M, vx, vy, vc, first, count;
 };
-// Small groups of one class of y lengths share their launches: at most 4 y lengths with 6 of x.  The class of
-// a group, 0 where it has launches of its own.
-constexpr int kBatchUnitGroups = 24;
+// Small groups share their launches, those on the default schedules by class of y lengths, those on tuned ones
+// all together: the unit of a group, 0 where it has launches of its own.
 template <typename T>
-int batch_y_class(const BatchGroup &g);
+int batch_unit(const BatchGroup &g);
+// groups of a launch: a class has at most 4 y lengths with 6 of x
+constexpr int kBatchUnitGroups = 24;
 enum { BATCH_X_FWD = 0, BATCH_X_INV = 1, BATCH_X_FUSED = 2 };  // x r2c with the cube, x c2r, both between steps
-// one pass of the unit g[0 .. ng): a group, or groups of one class
+// one pass of the unit g[0 .. ng)
 template <typename T>
 hipError_t launch_batch_x(const BatchGroup *g, int ng, int pass, const BatchInst<T> *table, const cx<T> *tw, int lt_shift,
                           hipStream_t s);

@@ -816,11 +816,11 @@ pfc_status batch_upload_table(pfc_batch *b)
     }
     PFC_TRY(hipMemcpy(b->ws + b->inst_off, table.data(), table.size() * sizeof(table[0]), hipMemcpyHostToDevice),
             "instance table upload");
-    // units: every group by itself, but small groups of one class of y lengths together
+    // units: every group by itself, but small groups together (batch_unit)
     std::vector<std::vector<pfc::BatchGroup>> units;
     std::map<int, size_t> unit_of;
     for (const pfc::BatchGroup &g : groups) {
-        const int c = pfc::batch_y_class<T>(g);
+        const int c = pfc::batch_unit<T>(g);
         auto it = c ? unit_of.find(c) : unit_of.end();
         if (it != unit_of.end()) {
             units[it->second].push_back(g);

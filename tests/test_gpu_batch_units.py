@@ -19,6 +19,8 @@ CASES = {
     # several instances, out of order; 5 of 256 x 512 fill the chip by themselves; two tuned instances
     "mixed": ([(32, 32), (1024, 64), (256, 512), (64, 1024), (256, 512), (32, 32), (512, 32), (256, 512), (32, 256), (1024, 64),
                (512, 512), (256, 512), (128, 32), (32, 32), (256, 512), (1024, 1024), (64, 64), (128, 32)], {6: [0, 1, 0], 13: [1, 0, 1]}),
+    "all tuned": (ALL, {i: [1, 1, 1] for i in range(len(ALL))}),
+    "tunings mixed": (ALL + ALL[::5], {i: [i % 2, i // 2 % 2, i // 4 % 2] for i in range(len(ALL) + 8)}),
     "one class": ([(64, 128), (128, 64), (256, 32)], {}),
     "one length": ([(512, 32), (512, 64), (512, 64)], {}),
 }
@@ -55,11 +57,14 @@ def test_units_equal_own_plans(case, dtype):
         assert torch.equal(b.psi[k], x) and torch.equal(b.state[k], s), f"instance {k} {shapes[k]} differs"
 
 
+# three passes of at most a class each for y up to 256, 512 and 1024 or, on tuned schedules, of a launch per
+# length, and of a few groups that fill the chip by themselves; one launch per shape and pass would be 108
+@pytest.mark.parametrize("tuning,most", [([0, 0, 0], 18), ([1, 1, 1], 24)], ids=str)
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
-def test_launches_of_many_shapes(dtype):
+def test_launches_of_many_shapes(dtype, tuning, most):
     import torch
 
-    pfc, b, _, _, _ = _setup(ALL, {}, dtype)
+    pfc, b, _, _, _ = _setup(ALL, {i: tuning for i in range(len(ALL))}, dtype)
     b.state_init()
     b.step(1)
     torch.cuda.synchronize()
@@ -73,9 +78,7 @@ def test_launches_of_many_shapes(dtype):
     assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
     assert lib.hipGraphDestroy(graph) == 0
     say(f"[batch units] {len(ALL)} shapes, one step: {n.value} launches")
-    # three passes of at most a class each for y up to 256, 512 and 1024, and of a few groups that fill the
-    # chip by themselves; one launch per shape and pass would be 108
-    assert n.value <= 18
+    assert n.value <= most
 
 
 def test_first_step_under_capture():
