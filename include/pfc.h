@@ -278,10 +278,10 @@ pfc_status pfc_hydro_step(pfc_plan *p, const pfc_hydro_params *hp, void *psi, vo
  * dt; all instances share the dtype and device.  A step is three passes (x r2c with cube, y forward +
  * update + y inverse, x c2r; between two steps of one call the two x passes are one); instances of one
  * shape and one choice of schedules share each pass's launch, and so do small groups of different shapes,
- * by class of y lengths or, on tuned schedules, by length and schedule.  Where it pays, part of them runs on a stream of the
- * batch's own (created by pfc_batch_bind), which starts after the caller's earlier work and which the
- * caller's stream waits for before pfc_batch_step's end on it.  pfc_batch_step may be captured, also as
- * the first call after pfc_batch_bind. */
+ * by class of y lengths or, on tuned schedules, by length and schedule.  Where it pays, part of them runs
+ * on a stream of the batch's own (created by pfc_batch_bind), which starts after the caller's earlier work
+ * and which the caller's stream waits for before pfc_batch_step's end on it.  pfc_batch_step may be
+ * captured, also as the first call after pfc_batch_bind. */
 typedef struct pfc_batch pfc_batch;
 
 /* Validate `count` (1..256) 2D descriptors and create a batch (host memory only).  Source: each
