@@ -73,8 +73,8 @@ constexpr int hy_lds()
 }
 
 // Last-axis pass (tiles and pairs as last_axis_block).  A workgroup holds all of its pencils' elements
-// before it stores, so o0 may be one of the inputs.
-template <typename T, class PL, int WMAX, int OP, bool NT, bool LP>
+// before it stores, so o0 may be one of the inputs.  SHORT: 3D rows of one tile, in the order of la_pair_order.
+template <typename T, class PL, int WMAX, int OP, bool NT, bool LP, bool SHORT = false>
 __global__ __launch_bounds__(WMAX *PL::Tp) void hydro_last_kernel(HydroLastArgs<T> a)
 {
     constexpr int L = PL::L, Tp = PL::Tp, Rmax = PL::Rmax, R0 = PL::first, Rl = PL::last;
@@ -83,15 +83,11 @@ __global__ __launch_bounds__(WMAX *PL::Tp) void hydro_last_kernel(HydroLastArgs<
     // the state is loaded ahead of the forward transforms where its registers fit beside theirs
     constexpr bool PF = OP != HYDRO_DERIV && (int)sizeof(T) * Rmax <= (OP == HYDRO_PSI ? 32 : 64);
     __shared__ cx<T> sh[hy_lds<T, PL, WMAX, OP, LP>()];
+    const int64_t bid = SHORT                 ? la_pair_order(blockIdx.x, a.nrows, 2 * a.xg)
+                        : LP && a.nrows == 1 ? xcd_tile_order(blockIdx.x, gridDim.x, a.xg)
+                                             : blockIdx.x;
     const int tid = threadIdx.x, p = tid % WMAX, t = tid / WMAX, W = a.W;
     const int64_t nrows = a.nrows, M = a.M;
-    int64_t bid = blockIdx.x;
-    if constexpr (LP) {
-        if (nrows == 1)
-            bid = xcd_tile_order(bid, gridDim.x, a.xg);
-        else if (a.tiles_per_row == 1)
-            bid = la_pair_order(bid, nrows, 2 * a.xg);
-    }
     const SlotInfo si = la_slot<ORD_XCD_ROW, false>(nrows, a.tiles_per_row, W, p < W ? p : 0, bid);
     const bool valid = p < W && si.kx < M;
     auto lds = [&](int e) -> cx<T> & { return sh[pencil_slot<LP>(e) * WMAX + p]; };
@@ -399,41 +395,46 @@ hipError_t hydro_last_op(const Geom &g, HydroLastArgs<T> a, hipStream_t s)
         if constexpr (!axis_length(L)) {
             return hipErrorInvalidValue;
         } else {
-            auto run = [&](auto plc, auto wc, auto lpc, auto ntc) -> hipError_t {
+            auto run = [&](auto plc, auto wc, auto lpc, auto ntc, auto shortc) -> hipError_t {
                 using PL = decltype(plc);
                 constexpr int WM = decltype(wc)::value;
                 if (!z_steps_ok<PL>(g.zs)) return hipErrorInvalidValue;
                 a.W = even_width(g.M < WM ? (int)g.M : WM);
                 a.tiles_per_row = (int)cdiv(g.M, a.W);
                 a.xg = line_group<T>(a.W);
-                hipLaunchKernelGGL((hydro_last_kernel<T, PL, WM, OP, decltype(ntc)::value, decltype(lpc)::value>),
+                if (decltype(shortc)::value && (g.nrows == 1 || a.tiles_per_row != 1)) return hipErrorInvalidValue;
+                hipLaunchKernelGGL((hydro_last_kernel<T, PL, WM, OP, decltype(ntc)::value, decltype(lpc)::value,
+                                                      decltype(shortc)::value>),
                                    dim3((unsigned)(g.nrows * a.tiles_per_row)), dim3(WM * PL::Tp), 0, s, a);
                 return hipGetLastError();
             };
             auto narrow = [&](auto plc) -> hipError_t {
                 return run(plc, std::integral_constant<int, NarrowTile<decltype(plc)>::W>{}, std::true_type{},
-                           std::false_type{});
+                           std::false_type{}, std::false_type{});
             };
             using P3 = typename AxisPlan<L>::type;
             constexpr std::integral_constant<int, WMax<T, L>::value> wm{};
             // 2D grids never have kFillTiles tiles
             if (g.ndim == 2) return narrow(typename Last2Plan<L>::type{});
             const int W = even_width(g.M < wm.value ? (int)g.M : wm.value);
-            // Rows of a quarter of a line at most (x = 4, FP32 also 8) would leave most of the tile's lanes idle:
-            // tiles of a row's half and its mirror's, mixed lengths over more threads as in 2D.  Two steps, in
-            // ms, of separate passes (whose tiles cross rows), full tiles, these: 1024 x 1024 x 8 FP32 2.77, 3.95,
-            // 2.69, 1400 x 1400 x 8 7.20, 9.27, 6.47, 700 x 2048 x 4 3.12, 5.55, 3.14, FP64 2.94, 4.13, 2.60;
-            // 1024 x 2048 x 4 FP32 4.11, 7.03, 4.61 and 2048 x 2048 x 4 8.16, 9.17, 9.21, where the folded
-            // pencils' LDS leaves one to three workgroups per CU.
-            if (4 * W <= WMax<T, L>::pref) {
-                using PS = std::conditional_t<is_pow2c(L), P3, typename Last2Plan<L>::type>;
-                if constexpr (sizeof(T) == 4 && NarrowTile<PS>::W < 4)
-                    if (W == 4) return run(PS{}, std::integral_constant<int, 4>{}, std::true_type{}, std::false_type{});
-                return narrow(PS{});
-            }
             if (g.nrows * cdiv(g.M, W) < kFillTiles) return narrow(P3{});
+            // Rows of a quarter of a line at most (x = 4, FP32 also 8) would leave most of the tile's lanes idle, and
+            // from 256 points up that shows: tiles of a row's half and its mirror's, mixed lengths over more
+            // threads as in 2D.  Two steps, in ms, of separate passes (whose tiles cross rows), full tiles, these:
+            // 1024 x 1024 x 8 FP32 2.77, 3.95, 2.69, 1400 x 1400 x 8 7.20, 9.27, 6.47, 700 x 2048 x 4 3.12, 5.55,
+            // 3.14, FP64 2.94, 4.13, 2.60; 1024 x 2048 x 4 FP32 4.11, 7.03, 4.61 and 2048 x 2048 x 4 8.16, 9.17,
+            // 9.21, where the folded pencils' LDS leaves one to three workgroups per CU.
+            if constexpr (L >= 256) {
+                using PS = std::conditional_t<is_pow2c(L), P3, typename Last2Plan<L>::type>;
+                auto rows_of = [&](auto wc) {
+                    return run(PS{}, wc, std::true_type{}, std::false_type{}, std::true_type{});
+                };
+                if (g.M == 2) return rows_of(std::integral_constant<int, 2>{});
+                if constexpr (sizeof(T) == 4)
+                    if (g.M == 4) return rows_of(std::integral_constant<int, 4>{});
+            }
             return with_nt<line_group<T>(even_width(wm.value)) == 1>(g.nt && line_group<T>(W) == 1,
-                           [&](auto ntc) -> hipError_t { return run(P3{}, wm, std::false_type{}, ntc); });
+                           [&](auto ntc) -> hipError_t { return run(P3{}, wm, std::false_type{}, ntc, std::false_type{}); });
         }
     });
 }
